@@ -43,7 +43,8 @@ def build(verbose: bool = False) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
     cc = hipcc()
     objs = []
-    for src, device in (("pp_kernels.hip", True), ("pp_host.cpp", False)):
+    for src, device in (("pp_kernels.hip", True), ("pp_reduce.hip", True),
+                        ("pp_host.cpp", False)):
         obj = os.path.join(BUILD_DIR, src + ".o")
         cmd = [cc, f"--offload-arch={ARCH}", *COMMON, *DEVICE_FLAGS, "-c",
                os.path.join(CSRC, src), "-o", obj]

@@ -100,6 +100,12 @@ struct DevBuf {
 struct TreeLayout {
   int32_t n = 0;
   std::vector<int32_t> order, nextpos;
+  // level order of the reduced solve (DevState::lvslot ...); empty where the
+  // tree is beyond its limits
+  std::vector<int32_t> lvslot, lvtab;
+  std::vector<uint32_t> lvpos;
+  std::vector<uint16_t> lvpar;
+  int32_t lv_bits = 0, lv_clip = 0;
   // the backtrack's skip chains inside 32-row windows [32w, 32w + 32), as
   // ce[4q] = chain mask, ce[4q + 1] = exit row, ce[4q + 2] = the exit row's
   // own chain mask, ce[4q + 3] = 0: the mask has bit r set for every row
@@ -128,6 +134,8 @@ struct TreeLayout {
 
 int layout_sweep(TreeLayout& t);
 int layout_sweep_spilled(TreeLayout& t, int32_t pad, int32_t nsteps);
+void layout_levels(TreeLayout& t, const int32_t* parent, const std::vector<int32_t>& posof,
+                   const std::vector<int32_t>& head);
 
 int build_tree(int32_t n, const int32_t* parent, TreeLayout& t) {
   for (int32_t v = 0; v < n; ++v) {
@@ -171,6 +179,7 @@ int build_tree(int32_t n, const int32_t* parent, TreeLayout& t) {
     t.nextpos[q] = q + size[q];
     if (t.order[q] != q) t.identity = false;
   }
+  layout_levels(t, parent, posof, head);
   const size_t ce_rows = ((size_t)n + kCeBlock - 1) / kCeBlock * kCeBlock + kCeBlock;
   t.ce.assign(4 * ce_rows, 0);
   for (size_t q = n; q < ce_rows; ++q) t.ce[4 * q + 1] = kCeEnd;
@@ -189,6 +198,68 @@ int build_tree(int32_t n, const int32_t* parent, TreeLayout& t) {
     }
   }
   return layout_sweep(t);
+}
+
+// Level order for the reduced solve, left empty beyond its limits: depth,
+// nodes, 16-bit internal numbers, and child sums of k_ladder that fit 31
+// bits with at least 8 bits below one price (its clip is more than one price
+// per level, and a node adds up to max degree + 1 clipped values).
+void layout_levels(TreeLayout& t, const int32_t* parent, const std::vector<int32_t>& posof,
+                   const std::vector<int32_t>& head) {
+  const int32_t n = t.n;
+  if (n > kLadderSlots) return;
+  std::vector<uint8_t> depth(n);
+  int32_t maxd = 0;
+  int64_t maxdeg = 0;
+  for (int32_t q = 0; q < n; ++q) {
+    const int32_t v = t.order[q], p = parent[v];
+    const int32_t dep = p >= 0 ? depth[posof[p]] + 1 : 0;
+    if (dep > kReduceMaxDepth) return;
+    depth[q] = (uint8_t)dep;
+    maxd = std::max(maxd, dep);
+    maxdeg = std::max<int64_t>(maxdeg, head[v + 1] - head[v]);
+  }
+  const int64_t clip = ((int64_t)1 << 31) / (maxdeg + 2) - 4;
+  int bits = 0;
+  while (bits < 20 && ((int64_t)(maxd + 4) << (bits + 1)) < clip) ++bits;
+  if (bits < 8) return;
+  // internal nodes level by level, each level from a multiple of 64 on, then
+  // the leaves
+  std::vector<int32_t> tab(maxd + 2, 0);
+  int32_t levels = 0, leaves = 0;
+  for (int32_t q = 0; q < n; ++q) {
+    if (t.nextpos[q] == q + 1) {
+      ++leaves;
+    } else {
+      ++tab[depth[q]];
+      levels = std::max<int32_t>(levels, depth[q] + 1);
+    }
+  }
+  int32_t slot = 0;
+  for (int32_t l = 0; l < levels; ++l) {
+    const int32_t count = tab[l];
+    tab[l] = slot;
+    slot += (count + 63) / 64 * 64;
+  }
+  tab.resize(levels + 1);
+  tab[levels] = slot;
+  const int32_t nlv = slot + (leaves + 63) / 64 * 64;
+  if (nlv > kLadderSlots || slot >= 0xFFFF) return;
+  std::vector<int32_t> at(tab);
+  t.lvslot.resize(n);
+  t.lvpos.assign(nlv, 0);
+  t.lvpar.assign(nlv, 0xFFFF);
+  for (int32_t q = 0; q < n; ++q) {
+    const bool leaf = t.nextpos[q] == q + 1;
+    const int32_t s = at[leaf ? levels : depth[q]]++;
+    t.lvslot[q] = s;
+    t.lvpos[s] = (uint32_t)q | (leaf ? 255u : (uint32_t)depth[q]) << 24;
+    const int32_t p = parent[t.order[q]];
+    if (p >= 0) t.lvpar[s] = (uint16_t)t.lvslot[posof[p]];
+  }
+  t.lvtab = std::move(tab);
+  t.lv_bits = bits;
+  t.lv_clip = (int32_t)clip;
 }
 
 // DP metadata.  Rows are 1-based positions i; nx(i) = next(i); row i is
@@ -545,7 +616,8 @@ struct pp_ctx {
   // problem, preorder layout
   DevBuf lam, w, f, meta;
   // tree tables in one allocation (one upload): next positions, preorder
-  // (position -> caller id) and the backtrack's skip-chain table
+  // (position -> caller id), the backtrack's skip-chain table and, in
+  // `lvl`, the reduced solve's level order
   DevBuf tree;
   int32_t* nextpos = nullptr;
   int32_t* order = nullptr;
@@ -554,12 +626,14 @@ struct pp_ctx {
   DevBuf up_lam, up_w, up_f, up_u8;
   // per-slot state
   DevBuf tgt, v1, v2, h1, profit, sel, bits, ring, cs;
+  DevBuf lvl, key_lv, lad_bits, lad_pre, lad_stat, lad_list;  // the reduced solve
   DevBuf sel0;  // standalone selections, [m][npad/32] (greedy position 0)
   DevBuf partial, flag, gx, gxp;
   DevBuf sp_lists, spill;  // spilled skip rows of deep trees
   uint32_t epoch = 0;
   std::vector<uint32_t> meta_host;  // source of the last metadata upload
   std::vector<uint8_t> tree_host;   // and of the last tree tables
+  std::vector<uint8_t> lvl_host;    // and of the last level order
   std::vector<hipEvent_t> events;
   // pinned host copy of the chain states read back after each refinement
   // launch (a direct device-to-host copy)
@@ -583,7 +657,8 @@ struct pp_ctx {
     if (val_pin) (void)hipHostFree(val_pin);
     for (DevBuf* b : {&lam, &w, &f, &tree, &meta, &up_lam, &up_w,
                       &up_f, &up_u8, &tgt, &v1, &v2, &h1, &profit, &sel, &sel0, &bits,
-                      &ring, &cs, &partial, &flag, &gx, &gxp, &sp_lists, &spill})
+                      &ring, &cs, &partial, &flag, &gx, &gxp, &sp_lists, &spill,
+                      &lvl, &key_lv, &lad_bits, &lad_pre, &lad_stat, &lad_list})
       b->release();
     for (hipEvent_t e : events) (void)hipEventDestroy(e);
     if (own) (void)hipStreamDestroy(own);
@@ -763,6 +838,7 @@ struct Engine {
   int resident;       // DP blocks resident at once
   uint32_t spin_limit;
   int fmax = 0;  // every DP value < 2^62: max via v_max_f64
+  int reduce_lds = 0;  // LDS of a reduced solve's block, 0: sweep every update
   hipStream_t st;
   Timer timer;
 
@@ -812,13 +888,31 @@ struct Engine {
     return PP_OK;
   }
 
-  // One worker update (gains, DP sweep, accept + backtrack, commit) for
-  // every chain of `set`.
+  // The reduced solve of every chain (k_reduce); what it leaves unsolved is
+  // the sweep's.
+  int reduce(const ChainSet& set, int mode) {
+    if (!reduce_lds) return PP_OK;
+    PP_TRY(timer_mark(c, timer, true, st));
+    PP_HIP(launch_reduce(set, d, mode, reduce_lds, st));
+    return timer_mark(c, timer, false, st);
+  }
+
+  // The DP of every chain of `set` (its profits are in place) and the walk:
+  // the reduced solve, then the sweep and the walk, which pass the chains
+  // it has solved over.
+  int solve(const ChainSet& set, int mode) {
+    PP_TRY(reduce(set, mode));
+    PP_TRY(dp(set, 1));
+    PP_HIP(launch_backtrack(set, d, mode, st));
+    return PP_OK;
+  }
+
+  // One worker update (gains, DP, accept + backtrack, commit) for every
+  // chain of `set`.
   int update(const ChainSet& set, int mode) {
     if (set.count == 0) return PP_OK;
     PP_HIP(launch_gains(set, d, st, kGainsMarginal, mode == kModeRefine ? 1 : 0));
-    PP_TRY(dp(set, 1));
-    PP_HIP(launch_backtrack(set, d, mode, st));
+    PP_TRY(solve(set, mode));
     if (d.f64) PP_HIP(launch_gexact(set, d, mode, st));  // exact G and the decision
     PP_HIP(launch_commit(set, d, mode, st));
     return PP_OK;
@@ -861,6 +955,63 @@ int choose_cells(int32_t total_stage_cells_c1, int dev, int32_t slots_lds) {
     }
   }
   return best ? best : most;
+}
+
+// Dynamic LDS of a reduced solve's block on this tree, 0 where every update
+// is swept: trees of at least kReduceMinN nodes (below, the n row steps of a
+// sweep take less than the reduced solve's fixed passes) with a level order
+// whose tables fit.  Forcing the sweep's lane width or its spin limit (test
+// hooks) asks for the sweep itself.
+constexpr int32_t kReduceMinN = 1024;
+int reduce_lds_for(const TreeLayout& t, int dev) {
+  if (std::getenv("PP_DP_CELLS") || std::getenv("PP_SPIN_LIMIT")) return 0;
+  if (t.lvtab.empty() || t.n < env_int("PP_REDUCE_MIN_N", kReduceMinN)) return 0;
+  int lds = 0;
+  if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
+    return 0;
+  return (size_t)lds >= reduce_lds_min(t.n, (int32_t)t.lvpos.size(),
+                                       (int32_t)t.lvtab.size() - 1, t.lvtab.back())
+             ? lds
+             : 0;
+}
+
+// The reduced solve's tables and per-slot scratch for `slots` chain slots.
+int ensure_reduce(pp_ctx* c, const TreeLayout& t, DevState& d, int32_t slots, hipStream_t st) {
+  const size_t n = (size_t)t.n, nlv = t.lvpos.size(), levels = t.lvtab.size() - 1;
+  const size_t a = (n * 4 + 255) & ~(size_t)255, b = a + ((nlv * 4 + 255) & ~(size_t)255),
+               e = b + ((nlv * 2 + 255) & ~(size_t)255);
+  std::vector<uint8_t>& h = c->lvl_host;
+  h.assign(e + (levels + 1) * 4, 0);
+  std::memcpy(h.data(), t.lvslot.data(), n * 4);
+  std::memcpy(h.data() + a, t.lvpos.data(), nlv * 4);
+  std::memcpy(h.data() + b, t.lvpar.data(), nlv * 2);
+  std::memcpy(h.data() + e, t.lvtab.data(), (levels + 1) * 4);
+  PP_TRY(c->lvl.ensure(h.size()));
+  PP_TRY(stage_h2d(c, c->lvl.p, h.data(), h.size(), st));
+  PP_TRY(c->key_lv.ensure(slots * nlv * 4));
+  // the padding slots between levels are never written and hold no profit
+  PP_HIP(hipMemsetAsync(c->key_lv.p, 0, slots * nlv * 4, st));
+  PP_TRY(c->lad_pre.ensure(slots * (size_t)kLadderRungs * (nlv / 16)));
+  PP_TRY(c->lad_bits.ensure(slots * (size_t)kLadderRungs * (nlv / 8)));
+  PP_TRY(c->lad_stat.ensure(slots * (size_t)kLadderRungs * 12));
+  PP_TRY(c->lad_list.ensure(slots * (size_t)kReduceActive * 16));
+  const uint8_t* base = c->lvl.as<uint8_t>();
+  d.lvslot = (const int32_t*)base;
+  d.lvpos = (const uint32_t*)(base + a);
+  d.lvpar = (const uint16_t*)(base + b);
+  d.lvtab = (const int32_t*)(base + e);
+  d.levels = (int32_t)levels;
+  d.nlv = (int32_t)nlv;
+  d.leaf0 = t.lvtab.back();
+  d.lv_bits = t.lv_bits;
+  d.lv_clip = t.lv_clip;
+  d.key_lv = c->key_lv.as<uint32_t>();
+  d.lad_pre = c->lad_pre.as<uint32_t>();
+  d.lad_bits = c->lad_bits.as<uint32_t>();
+  d.lad_price = c->lad_stat.as<double>();
+  d.lad_count = (int32_t*)(c->lad_stat.as<double>() + slots * (size_t)kLadderRungs);
+  d.lad_list = c->lad_list.as<uint32_t>();
+  return PP_OK;
 }
 
 struct PlanResult {
@@ -934,8 +1085,7 @@ int run_safeguards(Engine& e, int32_t m, const std::vector<int32_t>& kp,
       const ChainSet set = chain_set(sl, wk, kk, lo, hi);
       PP_HIP(launch_init_slots(set, d, 0, st));
       PP_HIP(launch_gains(set, d, st, gm[q]));
-      PP_TRY(e.dp(set, 1));
-      PP_HIP(launch_backtrack(set, d, kModeGreedy, st));
+      PP_TRY(e.solve(set, kModeGreedy));
       PP_HIP(launch_assemble(set, d, cand_slot[q], st));
     }
   }
@@ -949,8 +1099,7 @@ int run_safeguards(Engine& e, int32_t m, const std::vector<int32_t>& kp,
     const std::vector<int32_t> s1 = {cand_slot[2]}, w1 = {h}, k1 = {kp[h]};
     const ChainSet set = chain_set(s1, w1, k1, 0, 1);
     PP_HIP(launch_gains(set, d, st, kGainsLocalDedup));
-    PP_TRY(e.dp(set, 1));
-    PP_HIP(launch_backtrack(set, d, kModeGreedy, st));
+    PP_TRY(e.solve(set, kModeGreedy));
     if (d.f64) PP_HIP(launch_gexact(set, d, kModeGreedy, st));  // adopts T'_h
     PP_HIP(launch_commit(set, d, kModeGreedy, st));
   }
@@ -1150,8 +1299,9 @@ int refine_starts(Engine& e, const std::vector<int32_t>& starts, int32_t spare_b
       set.kprime[k] = kp[items[k].worker];
     }
     PP_HIP(launch_gains(set, d, e.st, kGainsMarginal, 1));
-    PP_TRY(e.dp(set, 1));
-    PP_HIP(launch_backtrack(set, d, kModeRefine, e.st));
+    PP_TRY(e.reduce(set, kModeRefine));
+    if (!e.reduce_lds) PP_TRY(e.dp(set, 1));
+    PP_HIP(launch_backtrack(set, d, kModeRefine, e.st, e.reduce_lds ? 1 : 0));
     if (d.f64) PP_HIP(launch_gexact(set, d, kModeRefine, e.st));
     // the launch's results, to pinned memory in one copy: the starts' slots
     // (consecutive) through the last spare slot used (the slots between
@@ -1160,13 +1310,36 @@ int refine_starts(Engine& e, const std::vector<int32_t>& starts, int32_t spare_b
     PP_TRY(ensure_cs_pin(e.c, span));
     ChainState* own = e.c->cs_pin;
     ChainState* spare = e.c->cs_pin + (spare_base - starts[0]);
-    PP_HIP(hipMemcpyAsync(own, d.cs + starts[0], sizeof(ChainState) * span,
-                          hipMemcpyDeviceToHost, e.st));
-    PP_TRY(poll_stream(e.st));
     std::vector<ChainState> cs(items.size());
-    for (size_t k = 0; k < items.size(); ++k)
-      cs[k] = items[k].slot >= spare_base ? spare[items[k].slot - spare_base]
-                                          : own[items[k].slot - starts[0]];
+    auto read_states = [&]() -> int {
+      PP_HIP(hipMemcpyAsync(own, d.cs + starts[0], sizeof(ChainState) * span,
+                            hipMemcpyDeviceToHost, e.st));
+      PP_TRY(poll_stream(e.st));
+      for (size_t k = 0; k < items.size(); ++k)
+        cs[k] = items[k].slot >= spare_base ? spare[items[k].slot - spare_base]
+                                            : own[items[k].slot - starts[0]];
+      return PP_OK;
+    };
+    PP_TRY(read_states());
+    if (e.reduce_lds) {
+      // updates the reduced solve left: swept now
+      ChainSet rest;
+      std::memset(&rest, 0, sizeof rest);
+      for (int32_t k = 0; k < set.count; ++k)
+        if (!cs[k].skip && !cs[k].solved) {
+          const int32_t q = rest.count++;
+          rest.slot[q] = set.slot[k];
+          rest.src[q] = set.src[k];
+          rest.worker[q] = set.worker[k];
+          rest.kprime[q] = set.kprime[k];
+        }
+      if (rest.count > 0) {
+        PP_TRY(e.dp(rest, 1));
+        PP_HIP(launch_backtrack(rest, d, kModeRefine, e.st));
+        if (d.f64) PP_HIP(launch_gexact(rest, d, kModeRefine, e.st));
+        PP_TRY(read_states());
+      }
+    }
     // decisions, in each start's order
     std::vector<int32_t> csl, cwk, ckp;
     AdoptSet ad;
@@ -1357,6 +1530,7 @@ int run_plan_once(pp_ctx* c, const TreeLayout& t, int32_t m, const int32_t* cap,
     return fail(PP_E_UNSUPPORTED, "DP sweep cannot be resident (LDS stack of " +
                                       std::to_string(e.slots_lds) + " rows)");
   e.fmax = fmax_ok && env_int("PP_DP_NO_FMAX", 0) == 0;
+  e.reduce_lds = reduce_lds_for(t, c->device);
   res.lane_cells = cells;
   res.fmax = (e.fmax || f64) ? 1 : 0;
   PP_TRY(ensure_slots(c, d, slots, kmax, cells));
@@ -1368,6 +1542,7 @@ int run_plan_once(pp_ctx* c, const TreeLayout& t, int32_t m, const int32_t* cap,
   PP_TRY(upload_meta(c, t, cells, st));
   d.meta = c->meta.as<uint32_t>();  // upload_meta may have (re)allocated it
   PP_TRY(upload_spills(c, t, d, slots, st));
+  if (e.reduce_lds) PP_TRY(ensure_reduce(c, t, d, slots, st));
 
   // --- standalone scores: each worker against the empty placement
   res.standalone.assign(m, 0);
@@ -1394,8 +1569,7 @@ int run_plan_once(pp_ctx* c, const TreeLayout& t, int32_t m, const int32_t* cap,
       // the choice bits and the walk too: every start's first greedy update
       // is the standalone solve of its first worker
       const ChainSet s2 = chain_set(sl2, wk2, kk2, 0, sl2.size());
-      PP_TRY(e.dp(s2, 1));
-      PP_HIP(launch_backtrack(s2, d, kModeGreedy, st));
+      PP_TRY(e.solve(s2, kModeGreedy));
     }
   }
   // the standalone selections (slots 0..m-1) outlive the starts' use of
@@ -2283,10 +2457,13 @@ static int rooted_dp_impl(int32_t n, const int32_t* parent, const void* profit_v
     PP_TRY(upload_meta(c, t, cells, st));
     d.meta = c->meta.as<uint32_t>();  // upload_meta may have (re)allocated it
     PP_TRY(upload_spills(c, t, d, 1, st));
+    const int reduce_lds = reduce_lds_for(t, c->device);
+    if (reduce_lds) PP_TRY(ensure_reduce(c, t, d, 1, st));
     PP_TRY(c->up_lam.ensure((size_t)n * 8));
     PP_HIP(hipMemcpyAsync(c->up_lam.p, profit, (size_t)n * 8, hipMemcpyHostToDevice, st));
     PP_HIP(launch_gather(c->up_lam.as<int64_t>(), d.profit, 1, n,
                          c->order, st));
+    PP_HIP(launch_profit_keys(d, 0, st));
     std::vector<int32_t> sl{0}, wk{0}, kk{kp};
     ChainSet set = chain_set(sl, wk, kk, 0, 1);
     Engine e;
@@ -2296,6 +2473,7 @@ static int rooted_dp_impl(int32_t n, const int32_t* parent, const void* profit_v
     e.slots_lds = slots_lds;
     e.resident = dp_resident_blocks(cells, slots_lds, c->device);
     e.fmax = tot < kFmaxBound && env_int("PP_DP_NO_FMAX", 0) == 0;
+    e.reduce_lds = reduce_lds;
     if (e.resident <= 0) return fail(PP_E_UNSUPPORTED, "DP sweep cannot be resident");
     std::vector<uint32_t> pre(d.npad / 32);
     ChainState out{};
@@ -2303,8 +2481,7 @@ static int rooted_dp_impl(int32_t n, const int32_t* parent, const void* profit_v
       e.spin_limit = spin_limit_for(attempt);
       ChainState z{};
       PP_HIP(hipMemcpyAsync(d.cs, &z, sizeof z, hipMemcpyHostToDevice, st));
-      PP_TRY(e.dp(set, 1));
-      PP_HIP(launch_backtrack(set, d, kModeGreedy, st));
+      PP_TRY(e.solve(set, kModeGreedy));
       PP_HIP(hipMemcpyAsync(pre.data(), d.sel, pre.size() * 4, hipMemcpyDeviceToHost, st));
       PP_HIP(hipMemcpyAsync(&out, d.cs, sizeof out, hipMemcpyDeviceToHost, st));
       PP_TRY(poll_stream(st));

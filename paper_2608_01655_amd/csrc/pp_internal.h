@@ -182,7 +182,21 @@ struct ChainState {
   int32_t skips;           // updates resolved that way
   int64_t skipped_cells;   // their n * k' DP cells
   uint32_t dirty[8];       // one bit per worker (m <= 255)
+  // the current update's DP was solved by k_reduce: dpval and the selection
+  // are final, the sweep and the walk pass the chain over
+  int32_t solved;
+  int32_t pad;
 };
+
+// The early rejection of a real-valued refinement update (see k_backtrack): a
+// DP value of at most dv cannot make it acceptable, whatever the rounding.
+__host__ __device__ inline bool early_reject_f64(double dv, double inc, double wsum, int m,
+                                                 int kp, int n, double eps) {
+  const double u = 0x1p-53;
+  const double e = 1.25 * (m + 8.0 + 2.0 * kp) * u * wsum + 2.0 * u * eps +
+                   (double)n * (m + 4.0) * 0x1p-1070;
+  return dv + e < inc + eps;
+}
 
 // The chains of one launch, passed by value as a kernel argument.
 struct ChainSet {
@@ -214,6 +228,23 @@ struct DevState {
   const int64_t* w;         // [m][n]     recompute cost, preorder
   const int64_t* f;         // [m][m][n]  fetch cost [src][dst][pos]
   const int32_t* nextpos;   // [n]        0-based first position after subtree
+  // Level order of the reduced solve (key_lv = nullptr: not in use): slots of
+  // the internal nodes level by level from the roots, each level from a
+  // multiple of 64 on, then (from leaf0 on) every leaf.
+  const int32_t* lvslot;    // [n]        slot of each position
+  const uint32_t* lvpos;    // [nlv]      position | level << 24 (leaves: 255)
+  const uint16_t* lvpar;    // [nlv]      slot of the parent, 0xFFFF for roots
+  const int32_t* lvtab;     // [levels + 1] first slot of each level, leaf0
+  int32_t levels, nlv, leaf0;
+  int32_t lv_bits, lv_clip; // k_ladder's fixed point: bits below one price,
+                            // height at which values are clipped
+  uint32_t* key_lv;         // [slots][nlv]  upper halves of the profits as
+                            //            doubles, rounded up
+  uint32_t* lad_bits;       // [slots][kLadderRungs][nlv / 32] S_t per rung
+  uint32_t* lad_pre;        // [slots][kLadderRungs][nlv / 64] its prefix
+  double* lad_price;        // [slots][kLadderRungs]
+  int32_t* lad_count;       // [slots][kLadderRungs]
+  uint32_t* lad_list;       // [slots][4 kReduceActive] active nodes
   const uint32_t* ce;       // [nce][4]   backtrack skip chain of q in its
                             //            32-row window (bit per row), the
                             //            first row of that chain past the
@@ -269,6 +300,24 @@ struct DevState {
 static_assert(sizeof(AdoptSet) + sizeof(DevState) <= 4096, "k_adopt arguments");
 static_assert(sizeof(ChainSet) + sizeof(DevState) + 64 <= 4096, "ChainSet kernel arguments");
 
+// Reduced solve (pp_reduce.hip): one block of kReduceThreads per chain, at
+// most kReduceActive nodes near or above the price, trees of at most
+// kReduceMaxDepth levels below the roots (one barrier per level) and
+// kLadderSlots level-order slots (one thread per 64 of them).
+constexpr int kReduceThreads = 1024;
+constexpr int kReduceActive = 15 * kReduceThreads;
+constexpr int kReduceMaxDepth = 254;
+constexpr int kLadderSlots = 65536;  // level-order slots (nodes, padded levels)
+constexpr int kReduceRedBytes = 1024;  // block-wide scratch words
+constexpr int kLadderRungs = 16;       // prices k_ladder tries per chain
+size_t reduce_lds_min(int32_t n, int32_t nlv, int32_t levels, int32_t leaf0);
+size_t ladder_lds(int32_t nlv, int32_t levels, int32_t leaf0);
+// mode kModeRefine: updates whose upper bound cannot beat the incumbent are
+// resolved (as rejected) without a solve.  Chains it cannot solve keep
+// ChainState::solved = 0.  lds: dynamic LDS bytes per block.
+hipError_t launch_reduce(const ChainSet& set, const DevState& d, int mode, int lds,
+                         hipStream_t st);
+
 // Host-side launchers (pp_kernels.hip).  All enqueue on `st`.
 hipError_t launch_gather(const int64_t* src, int64_t* dst, int32_t rows,
                          int32_t n, const int32_t* order, hipStream_t st);
@@ -276,6 +325,8 @@ hipError_t launch_gather(const int64_t* src, int64_t* dst, int32_t rows,
 hipError_t launch_gather_inputs(const int64_t* lam, const int64_t* w, const int64_t* f,
                                 int64_t* dlam, int64_t* dw, int64_t* df, int32_t m,
                                 int32_t n, const int32_t* order, hipStream_t st);
+// profit keys of one chain slot in level order, from its profit row
+hipError_t launch_profit_keys(const DevState& d, int64_t slot, hipStream_t st);
 hipError_t launch_gather_u8(const uint8_t* src, uint8_t* dst, int32_t rows,
                             int32_t n, const int32_t* order, hipStream_t st);
 hipError_t launch_scatter_u8(const uint8_t* src, uint8_t* dst, int32_t rows,
@@ -322,8 +373,10 @@ hipError_t launch_mat_cost(const DevState& d, int32_t inc, int32_t prop,
 hipError_t launch_dp(const ChainSet& set, const DevState& d, uint32_t epoch,
                      uint32_t spin_limit, int store_bits, int32_t slots_lds,
                      int fmax, hipStream_t st);
+// defer: chains not solved by k_reduce are left undecided (not accepted,
+// their sums kept) for a sweep and a second call
 hipError_t launch_backtrack(const ChainSet& set, const DevState& d, int mode,
-                            hipStream_t st);
+                            hipStream_t st, int defer = 0);
 // Speculative refinement: the updates of consecutive positions of one
 // start run together in spare slots; per start, the first accepted one (in
 // spare slot `from`, or none: from = -1) is adopted into the start's slot,

@@ -328,6 +328,26 @@ __global__ void k_holder_build(ChainSet set, DevState d) {
 
 // ------------------------------------------------------------- gains ----
 
+// The key of a profit: the upper half of its double, rounded up (0: none).
+// The next key is above every double that shares the upper half and above
+// any integer that rounds to one.
+__device__ __forceinline__ uint32_t profit_key(int64_t p, int f64) {
+  const uint64_t b = f64 ? (uint64_t)p : (uint64_t)as_i((double)p);
+  return p == 0 ? 0u : (uint32_t)(b >> 32) + 1u;
+}
+
+// A profit to the chain's row, and its key in level order where the reduced
+// solve is in use.
+__device__ __forceinline__ void store_profit(const DevState& d, int64_t s, int64_t i, int64_t p) {
+  d.profit[s * d.n + i] = p;
+  if (d.key_lv) d.key_lv[s * d.nlv + d.lvslot[i]] = profit_key(p, d.f64);
+}
+
+__global__ void k_profit_keys(DevState d, int64_t s) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i < d.n) d.key_lv[s * d.nlv + d.lvslot[i]] = profit_key(d.profit[s * d.n + i], d.f64);
+}
+
 // p_h(b) = sum_m Lambda_m(b) [q_{m<-h}(b) - v_m^{(-h)}(b)]_+  (Eq. 7) for
 // every preorder position, written to the chain's profit row; also the
 // incumbent's value sum_{b in T_h} p_h(b) and G(T_-h) = sum Lambda v^{(-h)}.
@@ -352,6 +372,7 @@ __global__ void __launch_bounds__(256) k_gains(ChainSet set, DevState d, int gmo
                        ((d.cs[ps].dirty[h >> 5] >> (h & 31)) & 1u) == 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       d.cs[s].skip = clean ? 1 : 0;
+      d.cs[s].solved = 0;
       if (clean) {
         d.cs[s].skips += 1;
         d.cs[s].skipped_cells += n * set.kprime[ci];
@@ -380,7 +401,7 @@ __global__ void __launch_bounds__(256) k_gains(ChainSet set, DevState d, int gmo
       const double own = L * dpos(Wv - F);
       p = covered ? a : a + own;
     }
-    d.profit[s * n + i] = as_i(p);
+    store_profit(d, s, i, as_i(p));
     return;
   }
   if (gmode != kGainsMarginal) {
@@ -402,7 +423,7 @@ __global__ void __launch_bounds__(256) k_gains(ChainSet set, DevState d, int gmo
       const int64_t a = L * (Wv < F ? Wv : F);
       p = covered ? a : a + L * imax(Wv - F, 0);
     }
-    d.profit[s * n + i] = p;
+    store_profit(d, s, i, p);
     return;
   }
   if (d.f64) {
@@ -422,7 +443,7 @@ __global__ void __launch_bounds__(256) k_gains(ChainSet set, DevState d, int gmo
         p = p + term;
         wl = wl + L * as_f(d.w[(int64_t)r * n + i]);
       }
-      d.profit[s * n + i] = as_i(p);
+      store_profit(d, s, i, as_i(p));
       in_th = d.tgt[ps * mn + (int64_t)h * n + i] != 0;
     }
     const double sh = block_sum_f64(in_th ? p : 0.0);
@@ -442,7 +463,7 @@ __global__ void __launch_bounds__(256) k_gains(ChainSet set, DevState d, int gmo
       p += L * imax(saving(d, h, r, i) - vmh, 0);
       g += L * vmh;
     }
-    d.profit[s * n + i] = p;
+    store_profit(d, s, i, p);
     held = d.tgt[ps * mn + (int64_t)h * n + i] ? p : 0;
   }
   const int64_t sh = block_sum(held);
@@ -690,7 +711,8 @@ k_dp(ChainSet set, DevState d, uint32_t epoch, uint32_t spin_limit,
   int ci = 0;
   while (ci + 1 < set.count && set.base[ci + 1] <= blk) ++ci;
   const int64_t slot = set.slot[ci];
-  if (d.cs[slot].skip) return;  // the update is resolved without a sweep
+  // the update is resolved without a sweep, or solved by k_reduce
+  if (d.cs[slot].skip || d.cs[slot].solved) return;
   const int kp = set.kprime[ci];
   const int g = blk - set.base[ci];
   const int G = set.base[ci + 1] - set.base[ci];
@@ -1345,7 +1367,7 @@ __device__ __forceinline__ void walk_sw_c1(uint32_t& q, uint32_t& rem, uint32_t&
 // written as a bitmap when the walk leaves the super-window.
 template <int C>
 __global__ void __launch_bounds__(64) k_backtrack(ChainSet set, DevState d,
-                                                  int mode) {
+                                                  int mode, int defer) {
   constexpr int kWin = kDpBatch;        // rows per choice word
   constexpr int kSwWin = 16;            // windows per super-window
   constexpr int kSw = kWin * kSwWin;    // rows per super-window
@@ -1370,6 +1392,14 @@ __global__ void __launch_bounds__(64) k_backtrack(ChainSet set, DevState d,
     }
     return;
   }
+  const bool solved = st->solved != 0;
+  if (defer && !solved) {
+    if (lane == 0) {
+      st->accept = 0;
+      st->rejected = 1;
+    }
+    return;
+  }
   if (lane == 0) {  // worker h's DP ran: its inputs are current again
     const int h = set.worker[ci];
     st->dirty[h >> 5] &= ~(1u << (h & 31));
@@ -1388,21 +1418,16 @@ __global__ void __launch_bounds__(64) k_backtrack(ChainSet set, DevState d,
     // requesters of Lambda * w), each of the two sums of at most k' of them
     // adds k' u of its total, and denormal terms add at most 2^-1074 per
     // rounding.
-    const double dv = as_f(dpval), inc = as_f(st->inc), wsum = as_f(st->wsum);
-    bool early = false;
-    if (mode == kModeRefine) {
-      const double u = 0x1p-53;
-      const double e = 1.25 * (d.m + 8.0 + 2.0 * kp) * u * wsum + 2.0 * u * d.eps +
-                       (double)n * (d.m + 4.0) * 0x1p-1070;
-      early = dv + e < inc + d.eps;
-    }
+    const bool early = mode == kModeRefine &&
+                       early_reject_f64(as_f(dpval), as_f(st->inc), as_f(st->wsum), d.m, kp, n,
+                                        d.eps);
     if (lane == 0) {
       st->accept = 0;
       st->inc = 0;
       st->wsum = 0;
       st->rejected = early ? 1 : 0;
     }
-    if (early) return;
+    if (early || solved) return;
     const int nwords = d.npad / 32;
     uint32_t* selw = d.sel + slot * nwords;
     for (int q = lane; q < nwords; q += kWave) selw[q] = 0;
@@ -1427,6 +1452,7 @@ __global__ void __launch_bounds__(64) k_backtrack(ChainSet set, DevState d,
 #pragma unroll
       for (int q = 0; q < 8; ++q) st->dirty[q] |= q == (h >> 5) ? ~(1u << (h & 31)) : ~0u;
     }
+    if (solved) return;
     for (int q = lane; q < nwords; q += kWave) selw[q] = 0;
     if (kp <= 0) return;
   }
@@ -1981,6 +2007,12 @@ hipError_t launch_gather_inputs(const int64_t* lam, const int64_t* w, const int6
   return hipGetLastError();
 }
 
+hipError_t launch_profit_keys(const DevState& d, int64_t slot, hipStream_t st) {
+  if (!d.key_lv) return hipSuccess;
+  hipLaunchKernelGGL(k_profit_keys, grid1(d.n, 256, 1), dim3(256), 0, st, d, slot);
+  return hipGetLastError();
+}
+
 hipError_t launch_gather_u8(const uint8_t* src, uint8_t* dst, int32_t rows,
                             int32_t n, const int32_t* order, hipStream_t st) {
   hipLaunchKernelGGL(k_gather_u8, grid1(n, 256, rows), dim3(256), 0, st, src,
@@ -2172,11 +2204,11 @@ int dp_resident_blocks_query(int cells, int32_t slots_lds, int device) {
 }  // namespace
 
 hipError_t launch_backtrack(const ChainSet& set, const DevState& d, int mode,
-                            hipStream_t st) {
+                            hipStream_t st, int defer) {
   switch (d.cells) {
-    case 1: hipLaunchKernelGGL(k_backtrack<1>, dim3(set.count), dim3(kWave), 0, st, set, d, mode); break;
-    case 2: hipLaunchKernelGGL(k_backtrack<2>, dim3(set.count), dim3(kWave), 0, st, set, d, mode); break;
-    case 4: hipLaunchKernelGGL(k_backtrack<4>, dim3(set.count), dim3(kWave), 0, st, set, d, mode); break;
+    case 1: hipLaunchKernelGGL(k_backtrack<1>, dim3(set.count), dim3(kWave), 0, st, set, d, mode, defer); break;
+    case 2: hipLaunchKernelGGL(k_backtrack<2>, dim3(set.count), dim3(kWave), 0, st, set, d, mode, defer); break;
+    case 4: hipLaunchKernelGGL(k_backtrack<4>, dim3(set.count), dim3(kWave), 0, st, set, d, mode, defer); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -1,0 +1,941 @@
+// pp_reduce.hip -- reduced exact solve of one worker's rooted-tree knapsack.
+//
+// k_reduce solves Eq. 9 for a chain without sweeping all n rows.  For a price
+// lambda >= 0 let V(b) = p_b - lambda + sum over children c of max(V(c), 0),
+// and S the nodes whose V and whose ancestors' V are all positive.  S
+// maximises sum (p - lambda), so for every feasible set X
+//     value(X) <= UB = lambda k' + sum over roots of max(V, 0),
+// and X falls short of UB by at least
+//     -V(a) for any ancestor-or-self a with V(a) < 0 of a node X takes,
+//      V(a) for any ancestor-or-self a in S of a node of S that X leaves out.
+// With a feasible set of value LB in hand and gap = UB - LB, every optimal
+// set therefore leaves out each node below (or at) some V < -gap, and takes
+// each node of S whose whole ancestor path has V > gap.  What is left, the
+// core, is small (the gap is about the price of a fraction of one chunk: 64
+// to 128 core nodes at n = 50,000, k = 4096).  LB comes from solving a core
+// of guessed width D with the plain DP; the result stands if gap <= D, and
+// otherwise the core of width D = gap is solved, which proves itself.
+//
+// The returned set is the full DP's, ties included.  The full DP's walk
+// yields one particular optimal set X*, and every optimal set avoids the
+// nodes left out and holds the forced ones.  On the rows the walk visits the
+// reduced table holds the full table's values (X*'s suffix is feasible in
+// the reduced problem, which only has fewer sets), a take row's skip value
+// only shrinks and a skip row's take value only shrinks, so the reduced walk
+// branches the same way everywhere.  For real-valued costs the same argument
+// holds for the rounded values: rounding is monotone, so the full table's
+// entries are the maxima of the sets' rounded sums; forced rows are kept in
+// the reduced recurrence (D = p + D) so that every sum is rounded as there,
+// and the gap includes the bound (1 + 2^-53)^k' on rounded sums.
+//
+// V is computed on integers: the profits themselves if their sum is below
+// 2^47, else shifted right (integer costs) or scaled by a power of two and
+// truncated (real-valued costs); truncation loses less than one unit per
+// node, so UB is raised by k' units then.
+//
+// k_ladder first finds, for a ladder of prices t, a superset of S_t over the
+// whole tree, one block per chain and price; k_reduce (one block of 1024
+// threads per chain) takes the highest price whose set clearly exceeds k'.
+// For a price lambda >= t, S is inside S_t, and any node outside S_t has an
+// ancestor-or-self with V <= t - lambda, so it stays out as long as gap <
+// lambda - t.  A chain that does not fit (too many active nodes, too wide a
+// core) is left to the full sweep.
+//
+// Both kernels read the tree in level order (DevState::lvpos): internal
+// nodes level by level from the roots, then every leaf.  Child sums live in
+// LDS; leaves add theirs in one pass, internal nodes level by level with one
+// barrier each.  What bounds them is instruction issue and, for code that
+// runs once per launch, instruction fetch, so loops are kept rolled.
+
+#include <algorithm>
+
+#include "pp_internal.h"
+
+namespace pp {
+
+namespace {
+
+constexpr int kRThreads = kReduceThreads;
+constexpr int kRWaves = kRThreads / 64;
+// V words: V in the upper bits, the size of the subtree's part of S below
+constexpr int kSizeBits = 14;
+static_assert(kReduceActive < (1 << kSizeBits), "size field");
+constexpr int kValueBits = 47;  // bound on the sum of the integer profits
+constexpr int kBins = 2048;     // histogram bins, 32 per factor of two
+constexpr int kCopies = 8;      // counters per bin
+constexpr int kCoreMax = kRThreads;
+constexpr int kMaxSearch = 40;  // evaluations of one price search
+constexpr uint32_t kNone = 0xFFFFu;
+constexpr int kChunks = kReduceActive / kRThreads;
+
+struct Red {  // block-wide scratch words in LDS
+  double dsum[kRWaves];
+  int64_t isum[kRWaves];
+  uint32_t wsum[kRWaves];
+  uint32_t vh[64];
+  int32_t bt;
+  uint32_t depth_max, core, forced;
+  int64_t value;
+  double price[kLadderRungs];
+  int32_t count[kLadderRungs];
+  int32_t lev[2 * kChunks];  // first and last level of each 1024 active nodes
+};
+
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// Exclusive prefix over the block of one count per thread; *total: the sum.
+__device__ uint32_t block_scan(uint32_t c, uint32_t* wsum, uint32_t* total) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  uint32_t x = c;
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) wsum[wv] = x;
+  __syncthreads();
+  uint32_t base = 0, t = 0;
+  for (int k = 0; k < kRWaves; ++k) {
+    const uint32_t v = wsum[k];
+    base += k < wv ? v : 0u;
+    t += v;
+  }
+  __syncthreads();
+  *total = t;
+  return base + x - c;
+}
+
+__device__ int64_t block_total(int64_t v, int64_t* part) {
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+  __syncthreads();
+  int64_t t = 0;
+  for (int k = 0; k < kRWaves; ++k) t += part[k];
+  __syncthreads();
+  return t;
+}
+
+// ----------------------------------------------------------- ladder ----
+
+// Prices of the rungs: the profits of rank c k', for these c (times 1/16).
+// |S| at a price is between about 0.4 and 1 times the number of profits
+// above it on prefix trees (profits that the other workers' copies leave
+// under poor ancestors do not count), so the steps are small there.
+__device__ constexpr int kRungRank16[kLadderRungs] = {1,  4,  10, 13, 14, 16, 18, 20,
+                                                      23, 26, 30, 35, 41, 50, 70, 130};
+
+// S_t for a ladder of prices t, one block per (chain, rung).  Profits come as
+// the upper 32 bits of doubles, rounded up (profit keys).  Child sums are
+// 32-bit fixed-point upper bounds in units of t / 2^u, so the result holds
+// S_t: values are clipped at a height that leaves every ancestor positive
+// (the clip exceeds one price per level).  Integer sums: the same bits
+// whatever the order of the atomics.
+template <bool F64>
+__global__ void __launch_bounds__(kRThreads) k_ladder(ChainSet set, DevState d) {
+  extern __shared__ int64_t lds[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = uniform(tid >> 6);
+  const int ci = blockIdx.x / kLadderRungs, rung = blockIdx.x % kLadderRungs;
+  const int64_t slot = set.slot[ci];
+  if (d.cs[slot].skip) return;
+  const int kp = set.kprime[ci];
+  const int levels = d.levels, nlv = d.nlv, leaf0 = d.leaf0;
+  const int nlw = nlv / 32, n64 = nlv / 64;
+  Red* red = (Red*)lds;
+  int32_t* lst = (int32_t*)((char*)lds + kReduceRedBytes);  // level starts, then leaf0
+  uint32_t* bits = (uint32_t*)(lst + ((levels + 2) & ~1));
+  uint32_t* cs = bits + nlw;
+  // The histogram comes first, kCopies counters per bin: most profits fall
+  // into a few bins, and atomics of one wave on one counter take turns.
+  uint32_t* suf = cs;
+  const int copy = lane % kCopies;
+  const uint32_t* __restrict__ key = d.key_lv + slot * (int64_t)nlv;
+  const uint16_t* __restrict__ par = d.lvpar;
+  for (int q = tid; q <= levels; q += kRThreads) lst[q] = d.lvtab[q];
+  for (int b = tid; b < kBins * kCopies; b += kRThreads) suf[b] = 0;
+  int base = 1023 << 5;  // integer profits: from 1 up
+  __syncthreads();
+  // (padding slots have key 0: no profit)
+  if (F64) {  // the 64 octaves below the largest profit
+    uint32_t mx = 0;
+#pragma unroll 8
+    for (int i = tid; i < nlv; i += kRThreads) mx = max(mx, key[i]);
+    for (int o = 32; o > 0; o >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, o, 64));
+    if (lane == 0) red->wsum[wv] = mx;
+    __syncthreads();
+    for (int k = 0; k < kRWaves; ++k) mx = max(mx, red->wsum[k]);
+    base = (int)(mx >> 15) - (kBins - 1);
+    __syncthreads();
+  }
+#pragma unroll 8
+  for (int i = tid; i < nlv; i += kRThreads) {
+    const uint32_t x = key[i];
+    if (x) atomicAdd(suf + max((int)(x >> 15) - base, 0) * kCopies + copy, 1u);
+  }
+  __syncthreads();
+  // the rung's price: the largest edge with at least `want` profits above
+  const int64_t want = max((int64_t)1, (int64_t)kRungRank16[rung] * kp / 16);
+  {
+    constexpr int per = kBins / kRThreads;
+    uint32_t c = 0, h[per];
+#pragma unroll
+    for (int b = 0; b < per; ++b) {
+      h[b] = 0;
+#pragma unroll
+      for (int k = 0; k < kCopies; ++k) h[b] += suf[(tid * per + b) * kCopies + k];
+      c += h[b];
+    }
+    if (tid == 0) red->bt = 0;
+    uint32_t tot;
+    uint32_t run = block_scan(c, red->wsum, &tot);
+    run = tot - run;  // profits in this thread's bins and above
+#pragma unroll
+    for (int b = 0; b < per; ++b) {
+      const uint32_t above = run - h[b];
+      if ((int64_t)run >= want && (int64_t)above < want) red->bt = tid * per + b;
+      run = above;
+    }
+    __syncthreads();
+  }
+  const int bt = red->bt;
+  const double t = bt <= 0 ? 0.0
+                           : __builtin_bit_cast(double, (uint64_t)((uint32_t)(bt + base) << 15) << 32);
+  const int clip = d.lv_clip;
+  const int unit = t > 0.0 ? 1 << d.lv_bits : 0;
+  const double inv = t > 0.0 ? (double)unit / t : 0.0;
+  const double clipd = (double)(clip - 2);
+  // p - t in units, rounded up (price 0: only whether there is a profit)
+  auto up = [&](uint32_t x) -> int {
+    if (t == 0.0) return x ? clip : 0;
+    return (int)fmin(__builtin_bit_cast(double, (uint64_t)x << 32) * inv, clipd) + 2 - unit;
+  };
+  for (int q = tid; q < leaf0; q += kRThreads) cs[q] = 0;
+  __syncthreads();
+  auto put = [&](int i, uint64_t m) {  // the wave's 64 bits at slot i - lane
+    if ((lane & 31) == 0) bits[(i - lane) / 32 + (lane >> 5)] = (uint32_t)(m >> (lane & 32));
+  };
+  // up: the leaves at once, then the levels from the deepest
+#pragma unroll 4
+  for (int i = leaf0 + tid; i < nlv; i += kRThreads) {
+    const int v = up(key[i]);
+    const uint32_t pr = par[i];
+    put(i, __ballot(v > 0));
+    if (v > 0 && pr != kNone) atomicAdd(cs + pr, (uint32_t)min(v, clip));
+  }
+  {
+    uint32_t kn = 0, pn = kNone;
+    auto load = [&](int q) {
+      if (q >= 0 && lst[q] + tid < lst[q + 1]) {
+        kn = key[lst[q] + tid];
+        pn = par[lst[q] + tid];
+      }
+    };
+    load(levels - 1);
+    for (int q = levels - 1; q >= 0; --q) {
+      const int end = lst[q + 1];
+      __syncthreads();
+      for (int i = lst[q] + tid; i < end; i += kRThreads) {
+        const uint32_t x = kn, pr = pn;
+        if (i + kRThreads < end) {
+          kn = key[i + kRThreads];
+          pn = par[i + kRThreads];
+        }
+        const int v = up(x) + (int)cs[i];
+        put(i, __ballot(v > 0));
+        if (v > 0 && pr != kNone) atomicAdd(cs + pr, (uint32_t)min(v, clip));
+      }
+      load(q - 1);
+    }
+  }
+  // down: what hangs on positive ancestors
+  {
+    auto keep = [&](int i, uint32_t pr) {
+      const uint64_t own = (uint64_t)bits[(i - lane) / 32 + 1] << 32 | bits[(i - lane) / 32];
+      if (own == 0) return;
+      const bool in = ((own >> lane) & 1u) &&
+                      (pr == kNone || ((bits[pr >> 5] >> (pr & 31)) & 1u));
+      put(i, __ballot(in));
+    };
+    uint32_t pn = kNone;
+    for (int q = 1; q < levels; ++q) {
+      const int end = lst[q + 1];
+      if (lst[q] + tid < end) pn = par[lst[q] + tid];
+      __syncthreads();
+      for (int i = lst[q] + tid; i < end; i += kRThreads) {
+        const uint32_t pr = pn;
+        if (i + kRThreads < end) pn = par[i + kRThreads];
+        keep(i, pr);
+      }
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int i = leaf0 + tid; i < nlv; i += kRThreads) keep(i, par[i]);
+    __syncthreads();
+  }
+  uint32_t* out = d.lad_bits + (slot * kLadderRungs + rung) * (int64_t)nlw;
+  uint32_t* pre = d.lad_pre + (slot * kLadderRungs + rung) * (int64_t)n64;
+  for (int w = tid; w < nlw; w += kRThreads) out[w] = bits[w];
+  uint32_t tot;
+  const uint32_t c = tid < n64 ? __popc(bits[2 * tid]) + __popc(bits[2 * tid + 1]) : 0u;
+  const uint32_t run = block_scan(c, red->wsum, &tot);
+  if (tid < n64) pre[tid] = run;
+  if (tid == 0) {
+    d.lad_price[slot * kLadderRungs + rung] = t;
+    d.lad_count[slot * kLadderRungs + rung] = (int32_t)tot;
+  }
+}
+
+// ------------------------------------------------------------ solve ----
+
+// Row words of the core DP: bit 0 forced (real-valued costs), bit 1 leaf
+// (the skip operand is the previous row), bits 2..15 the slot the row is
+// stored to (0: none), bits 16..31 the slot of the skip operand (0: the row
+// past the end, all zero).
+constexpr uint32_t kRowForced = 1u, kRowLeaf = 2u;
+
+__device__ __forceinline__ double as_d(int64_t v) { return __builtin_bit_cast(double, v); }
+__device__ __forceinline__ int64_t as_l(double v) { return __builtin_bit_cast(int64_t, v); }
+
+__device__ __forceinline__ int64_t shr1(int64_t v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), 0x138, 0xf, 0xf, true);
+  return (int64_t)((uint64_t)(uint32_t)hi << 32 | (uint32_t)lo);
+}
+
+// The core DP of one wave, columns 0..64C-1 (lane l: columns lC .. lC+C-1),
+// rows last to first; *out: the last row's value at column col.  A row's word
+// and profit are read two rows ahead, its skip operand one row ahead (the
+// row just computed is never the next row's far operand: that one is a
+// leaf).  Choice masks of core row r (its rank among the core rows):
+// ch[r C + c].
+template <int C, bool F64>
+__device__ void core_dp(int rows, int core, const int64_t* rp, const uint32_t* rinfo,
+                        int64_t* slots, uint64_t* ch, int col, int64_t* out) {
+  const int lane = threadIdx.x & 63;
+  int64_t D[C], skn[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) D[c] = skn[c] = slots[c * 64 + lane] = 0;
+  uint32_t i0 = rows > 0 ? rinfo[rows - 1] : 0u, i1 = rows > 1 ? rinfo[rows - 2] : 0u;
+  int64_t p0 = rows > 0 ? rp[rows - 1] : 0, p1 = rows > 1 ? rp[rows - 2] : 0;
+  int cr = core;
+  for (int r = rows - 1; r >= 0; --r) {
+    const uint32_t in = (uint32_t)uniform((int)i0);
+    const int64_t p = p0;
+    i0 = i1;
+    p0 = p1;
+    if (r > 1) {
+      i1 = rinfo[r - 2];
+      p1 = rp[r - 2];
+    }
+    int64_t sk[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) sk[c] = skn[c];
+    const uint32_t ns = (uint32_t)uniform((int)i0) >> 16;
+#pragma unroll
+    for (int c = 0; c < C; ++c) skn[c] = slots[(ns * C + c) * 64 + lane];
+    if (F64 && (in & kRowForced)) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) D[c] = as_l(as_d(p) + as_d(D[c]));
+    } else {
+      --cr;
+      const int64_t left = shr1(D[C - 1]);
+      int64_t t[C];
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        const int64_t v = c == 0 ? left : D[c - 1];
+        t[c] = F64 ? as_l(as_d(p) + as_d(v)) : p + v;
+        if (in & kRowLeaf) sk[c] = D[c];
+      }
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        // non-negative doubles compare like their bit patterns
+        const bool take = t[c] > sk[c] && (c > 0 || lane > 0);
+        const uint64_t m = __ballot(take);
+        if (lane == 0) ch[cr * C + c] = m;
+        D[c] = take ? t[c] : sk[c];
+      }
+    }
+    const uint32_t st = (in >> 2) & 0x3FFFu;
+    if (st != 0) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) slots[(st * C + c) * 64 + lane] = D[c];
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+    if (lane == col / C && c == col % C) *out = D[c];
+}
+
+// The walk from (core row 0, column col): 64 core rows' masks and links are in
+// registers; the positions of the rows taken are marked in sel.
+template <int C>
+__device__ void core_walk(int core, const uint64_t* ch, const uint16_t* cnx,
+                          const uint32_t* cpos, int col, uint32_t* sel) {
+  const int lane = threadIdx.x & 63;
+  int r = 0, j = col;
+  for (int b = 0; b < core && j > 0; b += 64) {
+    if (r >= b + 64) continue;
+    const int mine = min(b + lane, core - 1);
+    uint64_t m[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) m[c] = ch[mine * C + c];
+    const int nx = cnx[mine];
+    uint64_t taken = 0;
+    while (r < min(b + 64, core) && j > 0) {
+      const int l = r - b;
+      uint64_t w = m[0];
+      if (C > 1) {
+#pragma unroll
+        for (int c = 1; c < C; ++c) w = (j & (C - 1)) == c ? m[c] : w;
+      }
+      const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)w, l);
+      const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(w >> 32), l);
+      const uint64_t row = (uint64_t)hi << 32 | lo;
+      if ((row >> (j / C)) & 1u) {
+        taken |= 1ull << l;
+        ++r;
+        --j;
+      } else {
+        r = __builtin_amdgcn_readlane(nx, l);
+      }
+    }
+    if ((taken >> lane) & 1u) {
+      const uint32_t q = cpos[b + lane];
+      atomicOr(sel + (q >> 5), 1u << (q & 31));
+    }
+  }
+}
+
+template <bool F64>
+__global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, int mode,
+                                                      int lds_bytes) {
+  extern __shared__ int64_t lds[];
+  const int tid = threadIdx.x;
+  const int ci = blockIdx.x;
+  const int64_t slot = set.slot[ci];
+  ChainState* st = d.cs + slot;
+  if (st->skip) return;
+  const int n = d.n, nw = (n + 31) / 32, n64 = d.nlv / 64;
+  const int kp = set.kprime[ci];
+  const int64_t* __restrict__ prof = d.profit + slot * (int64_t)n;
+  // the active nodes, leaves first, then the deepest level: position, parent's
+  // index | level << 16 (leaves: d.levels), integer profit
+  uint32_t* apos = d.lad_list + slot * (int64_t)(4 * kReduceActive);
+  uint32_t* amd = apos + kReduceActive;
+  int64_t* aq = (int64_t*)(amd + kReduceActive);
+
+  Red* red = (Red*)lds;
+  uint32_t* sel = (uint32_t*)((char*)lds + kReduceRedBytes);  // selection, n bits
+  int64_t* W = (int64_t*)(((size_t)(sel + nw) + 15) & ~(size_t)15);
+  const int wbytes = lds_bytes - (int)((char*)W - (char*)lds);
+  const int acap = min(kReduceActive, wbytes / 8 - 4);
+
+  if (tid == 0) st->solved = 0;
+  if (kp <= 0) return;
+  double* price = red->price;
+  int32_t* count = red->count;
+  if (tid < kLadderRungs) {
+    price[tid] = d.lad_price[slot * kLadderRungs + tid];
+    count[tid] = d.lad_count[slot * kLadderRungs + tid];
+  }
+  __syncthreads();
+  // the highest rung with clearly more than k' nodes, else price 0
+  const int need = kp + kp / 8 + 160;
+  int j = 0;
+  while (j < kLadderRungs - 1 && count[j] < need && price[j] > 0.0) ++j;
+  const int nwords = d.npad / 32;
+  uint32_t* selw = d.sel + slot * nwords;
+
+  for (;;) {  // again from a lower rung if the gap turns out to need it
+    const double t = price[j];
+    const int A = count[j];
+    if (A > acap || (A < need && t > 0.0)) return;
+    if (A == 0) {  // price 0, no profit: nothing is strictly better than skipping
+      for (int w = tid; w < nwords; w += kRThreads) selw[w] = 0;
+      if (tid == 0) {
+        st->dpval = 0;
+        st->solved = 1;
+      }
+      return;
+    }
+    const int chunks = (A + kRThreads - 1) / kRThreads;
+
+    // --------------------------------------------------- active nodes --
+    {
+      uint32_t* list = (uint32_t*)W;
+      uint64_t* lb = (uint64_t*)(list + kReduceActive);
+      uint32_t* lp = (uint32_t*)(lb + n64);
+      const uint64_t* rb =
+          (const uint64_t*)(d.lad_bits + (slot * kLadderRungs + j) * (int64_t)(2 * n64));
+      const uint32_t* rpre = d.lad_pre + (slot * kLadderRungs + j) * (int64_t)n64;
+      if (tid < n64) {
+        uint64_t m = rb[tid];
+        int x = A - 1 - (int)rpre[tid];
+        lb[tid] = m;
+        lp[tid] = (uint32_t)x;  // active index of the group's first node
+        while (m) {
+          list[x--] = (uint32_t)(64 * tid + __builtin_ctzll(m));
+          m &= m - 1;
+        }
+      }
+      __syncthreads();
+      double total = 0.0;
+#pragma unroll 2
+      for (int x = tid; x < A; x += kRThreads) {
+        const uint32_t s = list[x];
+        const uint32_t pd = d.lvpos[s], pr = d.lvpar[s];
+        const int64_t p = prof[pd & 0xFFFFFFu];
+        uint32_t ps = kNone;
+        if (pr != kNone)
+          ps = lp[pr >> 6] - __popcll(lb[pr >> 6] & ((1ull << (pr & 63)) - 1u));
+        apos[x] = pd & 0xFFFFFFu;
+        const int lv = min((int)(pd >> 24), d.levels);  // leaves: below every level
+        amd[x] = ps | (uint32_t)lv << 16;
+        aq[x] = p;
+        total += F64 ? as_d(p) : (double)p;
+        if ((x & (kRThreads - 1)) == 0) red->lev[2 * (x / kRThreads)] = lv;
+        if (x == A - 1 || (x & (kRThreads - 1)) == kRThreads - 1)
+          red->lev[2 * (x / kRThreads) + 1] = lv;
+      }
+      for (int o = 32; o > 0; o >>= 1) total += __shfl_down(total, o, 64);
+      if ((tid & 63) == 0) red->dsum[tid >> 6] = total;
+      __syncthreads();
+    }
+    double total = 0.0;
+    for (int k = 0; k < kRWaves; ++k) total += red->dsum[k];
+    if (!(total < 1.7976931348623157e308) || (!F64 && total >= 9.2e18)) return;
+    // integer profits: p >> shift; real-valued: trunc(p 2^scale)
+    const int lg = ilogb(total * (1.0 + 0x1p-20));
+    const int shift = max(0, lg + 1 - kValueBits);
+    const int scale = F64 ? kValueBits - 1 - lg : -shift;
+    const int64_t qerr = (F64 || shift > 0) ? kp : 0;  // units UB can be low by
+    auto quant = [&](int64_t p) -> int64_t {
+      return F64 ? (int64_t)ldexp(as_d(p), scale) : p >> shift;
+    };
+    // a price in these units, rounded up
+    auto price_q = [&](double v) -> int64_t {
+      return (int64_t)min(ceil(ldexp(v, scale)), 0x1p48);
+    };
+    const int64_t tq = price_q(t);
+    if (F64 || shift > 0)
+      for (int x = tid; x < A; x += kRThreads) aq[x] = quant(aq[x]);
+
+    // --------------------------------------------------- price search --
+    // f(l) = |S(l)| falls with l; find a small l with f(l) <= k'.  The rungs'
+    // counts bracket it (to be confirmed); regula falsi (Illinois) with a
+    // bisection every fourth step, until the rest of the bracket can add at
+    // most 2^-9 of the price to the gap.
+    int64_t* cw = W;  // child sums by active index, then two root words
+    int64_t lam = 0, rootsum = 0;
+    {
+      int jl = 0;  // the highest rung with more than k' nodes
+      while (jl < j && count[jl] <= kp) ++jl;
+      int64_t lo = price_q(price[jl]), hi;
+      double ylo = max(count[jl] - kp, 1), yhi = -(double)kp;
+      bool vhi = false;
+      int fhi = 0;
+      if (jl > 0) {
+        hi = max(price_q(price[jl - 1]), lo + 2);
+        yhi = min(count[jl - 1] - kp, -1);
+      } else {
+        hi = price[0] > 0.0 ? 2 * lo + 2 : price_q(total) + 2;
+      }
+      bool zero = t == 0.0 && jl == j;  // price 0 itself may be the one
+      bool last = false;
+      int side = 0;
+      uint32_t parity = 0;
+      for (int it = 0;; ++it) {
+        int64_t l;
+        if (last) {
+          l = hi;
+        } else if (zero) {
+          l = 0;
+        } else if (hi - lo <= 1) {
+          l = hi;
+        } else if ((it & 3) == 3) {
+          l = lo + (hi - lo) / 2;
+        } else {
+          l = lo + (int64_t)((double)(hi - lo) * (ylo / (ylo - yhi)));
+          l = min(max(l, lo + 1), hi - 1);
+        }
+        if (it >= kMaxSearch && !last) {
+          if (!vhi) return;
+          last = true;
+          l = hi;
+        }
+        // |S| and the sum over roots of max(V, 0) at price l
+        parity ^= 1u;
+        for (int x = tid; x < A; x += kRThreads) cw[x] = 0;
+        if (tid == 0) cw[acap + parity] = 0;
+        int64_t qa = tid < A ? aq[tid] : 0, qb = 0;
+        uint32_t ma = tid < A ? amd[tid] : 0xFFFF0000u, mb = 0xFFFF0000u;
+        __syncthreads();
+        int cur = uniform(red->lev[0]);
+        for (int u = 0; u < chunks; ++u) {
+          const int x = tid + kRThreads * u;
+          const int64_t q = qa;
+          const uint32_t md = ma;
+          mb = 0xFFFF0000u;
+          if (x + kRThreads < A) {
+            qb = aq[x + kRThreads];
+            mb = amd[x + kRThreads];
+          }
+          const int l0 = uniform(red->lev[2 * u]), l1 = uniform(red->lev[2 * u + 1]);
+          for (int dd = l0; dd >= l1; --dd) {
+            if (dd != cur) {  // the levels below are complete
+              __syncthreads();
+              cur = dd;
+            }
+            if ((int)(md >> 16) == dd) {
+              const int64_t w = (q - l) * (1 << kSizeBits) + 1 + cw[x];
+              const uint32_t ps = md & 0xFFFFu;
+              if ((w >> kSizeBits) > 0)
+                atomicAdd((unsigned long long*)&cw[ps == kNone ? acap + parity : ps],
+                          (unsigned long long)w);
+            }
+          }
+          qa = qb;
+          ma = mb;
+        }
+        __syncthreads();
+        const int64_t root = cw[acap + parity];
+        const int fsize = (int)((uint32_t)root & ((1u << kSizeBits) - 1));
+        rootsum = root >> kSizeBits;
+        lam = l;
+        if (last) break;
+        const int miss = fsize - kp;
+        if (miss <= 0) {
+          hi = l;
+          fhi = fsize;
+          vhi = true;
+          if (zero || miss == 0) break;
+          yhi = miss;
+          if (side < 0) ylo *= 0.5;
+          side = -1;
+        } else {
+          if (l == hi) {  // the rung above was no upper bound
+            hi = l + max(l / 4, (int64_t)1);
+            yhi = -(double)kp;
+            vhi = false;
+          }
+          lo = l;
+          ylo = miss;
+          if (side > 0) yhi *= 0.5;
+          side = 1;
+        }
+        zero = false;
+        if (vhi && (hi - lo <= 1 ||
+                    (double)(kp - fhi) * (double)(hi - lo) * 512.0 <= (double)hi)) {
+          if (lam == hi) break;
+          last = true;
+        }
+      }
+    }
+    const int64_t ub = lam * kp + rootsum + qerr;
+    if (mode == kModeRefine) {
+      // no set can be worth more than the incumbent: rejected as it stands
+      // (real-valued: only if it also passes k_backtrack's early test, with
+      // the upper bound in place of the value)
+      bool reject;
+      int64_t bound;
+      if (!F64) {
+        bound = ub <= (INT64_MAX >> shift) ? ub << shift : INT64_MAX;
+        reject = bound <= st->inc;
+      } else {
+        const double v = ldexp((double)ub, -scale) * (1.0 + (kp + 8.0) * 0x1p-52);
+        bound = as_l(v);
+        reject = early_reject_f64(v, as_d(st->inc), as_d(st->wsum), d.m, kp, n, d.eps);
+      }
+      if (reject) {
+        if (tid == 0) {
+          st->dpval = bound;
+          st->solved = 1;
+        }
+        return;
+      }
+    }
+
+    // ----------------------------------------------------------- core --
+    // Entry width of each node, from the roots down, in place of its child
+    // sum: > 0 in S, the least V on its ancestor path (in the core iff at
+    // most the width, else forced); < 0 outside, -1 - the largest -V on the
+    // path (in the core iff that is at most the width).
+    if (tid < 64) red->vh[tid] = 0;
+    {
+      int cur = uniform(red->lev[2 * chunks - 1]);
+      int64_t qa = 0;
+      uint32_t ma = 0;
+      const int xl = tid + kRThreads * (chunks - 1);
+      if (xl < A) {
+        qa = aq[xl];
+        ma = amd[xl];
+      }
+      for (int u = chunks - 1; u >= 0; --u) {
+        const int x = tid + kRThreads * u;
+        const int64_t q = qa;
+        const uint32_t md = x < A ? ma : 0xFFFF0000u;
+        if (u > 0) {
+          qa = aq[x - kRThreads];
+          ma = amd[x - kRThreads];
+        }
+        const int l0 = uniform(red->lev[2 * u]), l1 = uniform(red->lev[2 * u + 1]);
+        for (int dd = l1; dd <= l0; ++dd) {
+          if (dd != cur) {
+            __syncthreads();
+            cur = dd;
+          }
+          if ((int)(md >> 16) == dd) {
+            const int64_t V = ((q - lam) * (1 << kSizeBits) + 1 + cw[x]) >> kSizeBits;
+            const uint32_t ps = md & 0xFFFFu;
+            const int64_t ep = ps == kNone ? INT64_MAX : cw[ps];
+            int64_t e;
+            if (ep < 0) e = V > 0 ? ep : min(ep, V - 1);
+            else e = V > 0 ? min(ep, V) : V - 1;
+            cw[x] = e;
+          }
+        }
+      }
+      __syncthreads();
+    }
+    // nodes that are not active stay out while gap <= dmax
+    const int64_t dmax = t == 0.0 ? INT64_MAX : max(lam - tq - 1, (int64_t)0);
+    // numbers of nodes by entry width (powers of two), up to half a price (or a
+    // few of the units the profits lose)
+    const int64_t cutoff = max(lam >> 1, 4 * qerr + 1);
+    for (int x = tid; x < A; x += kRThreads) {
+      const int64_t e = cw[x], a = e < 0 ? -1 - e : e;
+      if (a < cutoff)
+        atomicAdd(&red->vh[a == 0 ? 0 : 64 - __builtin_clzll((unsigned long long)a)], 1u);
+    }
+    __syncthreads();
+    // the largest width 2^b - 1 below the cutoff with at most `limit` nodes
+    auto widest = [&](uint32_t limit) -> int64_t {
+      const int b = tid & 63;
+      uint32_t x = red->vh[b];
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o, 64);
+        if (b >= o) x += y;
+      }
+      const bool ok = b < 62 && x <= limit && (b == 0 || ((int64_t)1 << b) - 1 < cutoff);
+      const uint64_t m = __ballot(ok);  // a prefix of the bins
+      return m == 0 ? 0 : ((int64_t)1 << (63 - __builtin_clzll(m))) - 1;
+    };
+    int64_t width = min(dmax, widest(96));
+    if (lam == 0) width = 0;
+    // LDS after the child sums (the core is small: they stay for a second,
+    // wider one)
+    char* const X = (char*)(W + A);
+    const int xbytes = wbytes - 8 * A;
+    bool lower = false;
+    for (int attempt = 0; attempt < 4 && !lower; ++attempt) {
+      if (tid == 0) red->core = red->forced = red->depth_max = 0;
+      for (int w = tid; w < nw; w += kRThreads) sel[w] = 0;
+      int off = 0;
+      auto take = [&](int64_t bytes) {
+        char* p = X + off;
+        off = (int)min((int64_t)1 << 30, off + ((bytes + 15) & ~(int64_t)15));
+        return p;
+      };
+      uint32_t* cun = (uint32_t*)take(4 * kCoreMax);  // core nodes as found
+      if (off > xbytes) return;
+      __syncthreads();
+      // core nodes (any order); forced ones go to the selection, their value
+      // into the base
+      int64_t base = 0;
+      uint32_t forced_mine = 0;
+      for (int x = tid; x < A; x += kRThreads) {
+        const int64_t e = cw[x];
+        const bool core = e < 0 ? -1 - e <= width : e <= width;
+        if (core) {
+          const uint32_t c = atomicAdd(&red->core, 1u);
+          if (c < (uint32_t)kCoreMax) cun[c] = apos[x];
+        } else if (e > 0) {
+          const uint32_t q = apos[x];
+          atomicOr(sel + (q >> 5), 1u << (q & 31));
+          ++forced_mine;
+          if (!F64) base += shift == 0 ? aq[x] : prof[q];
+        }
+      }
+      for (int o = 32; o > 0; o >>= 1) forced_mine += __shfl_down(forced_mine, o, 64);
+      if ((tid & 63) == 0 && forced_mine) atomicAdd(&red->forced, forced_mine);
+      base = block_total(base, red->isum);
+      const int R = (int)red->core, forced = (int)red->forced;
+      const int K = min(kp - forced, R);  // forced nodes are in S: at most k'
+      if (R > kCoreMax || K < 0 || K > 255) return;
+      const int C = K < 64 ? 1 : K < 128 ? 2 : 4;
+      const int rows = F64 ? R + forced : R;
+      uint32_t* cpos = (uint32_t*)take(4 * R);
+      uint32_t* cend = (uint32_t*)take(4 * R);
+      uint16_t* cnx = (uint16_t*)take(2 * R);
+      uint16_t* cdep = (uint16_t*)take(2 * R);
+      uint64_t* ch = (uint64_t*)take(8 * R * C);
+      int64_t* rp = (int64_t*)take(8ll * rows);
+      uint32_t* rinfo = (uint32_t*)take(4ll * rows);
+      // real-valued: the rows' positions as a bitmap, and its prefix
+      uint32_t* ib = F64 ? (uint32_t*)take(4 * nw) : sel;
+      uint32_t* ip = F64 ? (uint32_t*)take(4 * nw) : sel;
+      if (off > xbytes) return;
+      // each core node: rank, next core row, and core depth (the core rows
+      // before it whose subtree holds it)
+      uint32_t q = 0, qe = 0, rk = 0, nx = 0, dep = 0;
+      if (tid < R) {
+        q = cun[tid];
+        qe = (uint32_t)d.nextpos[q];
+        cend[tid] = qe;
+      }
+      if (F64)
+        for (int w = tid; w < nw; w += kRThreads) ib[w] = sel[w];
+      for (int r = tid; r < rows; r += kRThreads) rinfo[r] = 0;
+      __syncthreads();
+      if (tid < R) {
+#pragma unroll 4
+        for (int a = 0; a < R; ++a) {
+          const uint32_t qa = cun[a], ea = cend[a];
+          rk += qa < q;
+          nx += qa < qe;
+          dep += qa < q && ea > q;
+        }
+        cpos[rk] = q;
+        cnx[rk] = (uint16_t)nx;
+        cdep[rk] = (uint16_t)dep;
+        atomicMax(&red->depth_max, dep);
+        if (F64) atomicOr(ib + (q >> 5), 1u << (q & 31));
+      }
+      __syncthreads();
+      if (F64) {
+        const int per = (nw + kRThreads - 1) / kRThreads;
+        const int w0 = tid * per, w1 = min(w0 + per, nw);
+        uint32_t c = 0, tot;
+        for (int w = w0; w < w1; ++w) c += __popc(ib[w]);
+        uint32_t run = block_scan(c, red->wsum, &tot);
+        for (int w = w0; w < w1; ++w) {
+          ip[w] = run;
+          run += __popc(ib[w]);
+        }
+        __syncthreads();
+      }
+      auto row_of = [&](uint32_t at) -> int {  // rows before position `at`
+        return at >= (uint32_t)n
+                   ? rows
+                   : (int)(ip[at >> 5] + __popc(ib[at >> 5] & ((1u << (at & 31)) - 1u)));
+      };
+      int64_t* slots = (int64_t*)take(((int64_t)red->depth_max + 2) * C * 512);
+      if (off > xbytes) return;
+      // Row words.  A row is stored to the slot of its core depth if some
+      // earlier core row that is no leaf skips to it: between such a row and
+      // its readers every other stored row lies below the reader, so it is
+      // deeper.  Forced rows have no core ancestor (depth 0).
+      if (tid < R) {
+        const int it = F64 ? row_of(q) : (int)rk;
+        const int nit = F64 ? row_of(qe) : (int)nx;
+        rp[it] = prof[q];
+        uint32_t info = 0;
+        if (nit == it + 1) {
+          info = kRowLeaf;
+        } else if (nit < rows) {
+          // the target row (the first at or past the subtree's end) is a
+          // core row iff it is the first core row there
+          uint32_t sd = 1;
+          if ((int)nx < R && (!F64 || row_of(cpos[nx]) == nit)) sd = cdep[nx] + 1u;
+          info = sd << 16;
+          atomicOr(&rinfo[nit], sd << 2);
+        }
+        atomicOr(&rinfo[it], info);
+      }
+      if (F64) {
+        for (int x = tid; x < A; x += kRThreads)
+          if (cw[x] > width) {
+            const uint32_t at = apos[x];
+            const int it = row_of(at);
+            rp[it] = prof[at];
+            atomicOr(&rinfo[it], kRowForced);
+          }
+      }
+      __syncthreads();
+      if (tid < 64) {
+        if (C == 1) core_dp<1, F64>(rows, R, rp, rinfo, slots, ch, K, &red->value);
+        else if (C == 2) core_dp<2, F64>(rows, R, rp, rinfo, slots, ch, K, &red->value);
+        else core_dp<4, F64>(rows, R, rp, rinfo, slots, ch, K, &red->value);
+      }
+      __syncthreads();
+      const int64_t value = F64 ? red->value : base + red->value;
+      int64_t gap;
+      if (F64) {
+        // the value's integer units, low by what k' roundings can add
+        const double v = as_d(value);
+        if (!(v < 1.7976931348623157e308)) return;
+        gap = ub - (int64_t)ldexp(v - v * ((kp + 8.0) * 0x1p-52), scale) + 1;
+      } else {
+        gap = ub - (value >> shift);
+      }
+      if (gap <= width) {
+        if (tid < 64) {
+          if (C == 1) core_walk<1>(R, ch, cnx, cpos, K, sel);
+          else if (C == 2) core_walk<2>(R, ch, cnx, cpos, K, sel);
+          else core_walk<4>(R, ch, cnx, cpos, K, sel);
+        }
+        __syncthreads();
+        for (int w = tid; w < nwords; w += kRThreads) selw[w] = w < nw ? sel[w] : 0u;
+        if (tid == 0) {
+          st->dpval = value;
+          st->solved = 1;
+        }
+        return;
+      }
+      // wider: the gap itself if its core is small enough, else (the gap is
+      // this core's poor value) as wide as the next limit allows
+      int64_t next = widest(attempt == 0 ? 320u : 1000u);
+      if (next <= width) next = widest(1000u);
+      const int64_t want = gap <= next || attempt >= 2 ? gap : next;
+      if (width >= dmax || (want <= width && dmax < gap)) lower = true;
+      else if (want <= width) return;
+      else width = min(want, dmax);
+    }
+    if (!lower) return;
+    int jn = j + 1;
+    while (jn < kLadderRungs && price[jn] > 0.0 && count[jn] < A + A / 2) ++jn;
+    if (jn >= kLadderRungs) return;
+    j = jn;
+    __syncthreads();
+  }
+}
+
+}  // namespace
+
+// Dynamic LDS the two kernels need at least on a tree of n nodes, nlv
+// level-order slots, `levels` levels and leaf0 slots of internal nodes.
+size_t ladder_lds(int32_t nlv, int32_t levels, int32_t leaf0) {
+  return kReduceRedBytes + 4 * ((size_t)levels + 2) + (size_t)nlv / 8 +
+         4 * (size_t)std::max<int32_t>(kBins * kCopies, leaf0) + 16;
+}
+
+size_t reduce_lds_min(int32_t n, int32_t nlv, int32_t levels, int32_t leaf0) {
+  const size_t nw = ((size_t)n + 31) / 32;
+  const size_t solve = kReduceRedBytes + 4 * nw + 16 + 4 * (size_t)kReduceActive +
+                       12 * (size_t)nlv / 64 + 64;
+  return std::max(solve, ladder_lds(nlv, levels, leaf0));
+}
+
+hipError_t launch_reduce(const ChainSet& set, const DevState& d, int mode, int lds,
+                         hipStream_t st) {
+  static_assert(sizeof(Red) <= kReduceRedBytes, "scratch words");
+  static_assert(kLadderSlots <= 64 * kRThreads, "one thread per 64 slots");
+  if (set.count == 0) return hipSuccess;
+  if (!d.key_lv || !d.lvpos || !d.lvpar || !d.lvtab || !d.lad_bits || !d.lad_pre ||
+      !d.lad_price || !d.lad_count || !d.lad_list ||
+      reduce_lds_min(d.n, d.nlv, d.levels, d.leaf0) > (size_t)lds)
+    return hipErrorInvalidValue;
+  const size_t lad = ladder_lds(d.nlv, d.levels, d.leaf0);
+  const dim3 grid((unsigned)(set.count * kLadderRungs));
+  if (d.f64) {
+    hipLaunchKernelGGL(k_ladder<true>, grid, dim3(kRThreads), lad, st, set, d);
+    hipLaunchKernelGGL(k_reduce<true>, dim3(set.count), dim3(kRThreads), lds, st, set, d, mode,
+                       lds);
+  } else {
+    hipLaunchKernelGGL(k_ladder<false>, grid, dim3(kRThreads), lad, st, set, d);
+    hipLaunchKernelGGL(k_reduce<false>, dim3(set.count), dim3(kRThreads), lds, st, set, d, mode,
+                       lds);
+  }
+  return hipGetLastError();
+}
+
+}  // namespace pp

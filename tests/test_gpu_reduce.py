@@ -1,0 +1,110 @@
+"""The reduced solve (k_reduce) against the CPU oracle, forced on for every
+tree size: the same set and value as the full dynamic program, ties included,
+whether the reduction proves its core or leaves the chain to the sweep."""
+
+import numpy as np
+import pytest
+
+from paper_2608_01655_amd import binding as B
+from paper_2608_01655_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _forced(monkeypatch, request):
+    print(f"\n[case] {request.node.name}", flush=True)
+    monkeypatch.setenv("PP_REDUCE_MIN_N", "1")
+    yield
+
+
+def _gw(n, rng):
+    return W._relabel_preorder(W.galton_watson_tree(n, 2.2, 16, rng))[0]
+
+
+def _trees(n, rng):
+    depth = min(n, 200)
+    yield "forest", W.random_forest(n, rng, p_root=0.02)
+    yield "flat", np.full(n, -1, np.int32)
+    yield "star", np.array([-1] + [0] * (n - 1), np.int32)
+    yield "paths", np.array([v - 1 if v % depth else -1 for v in range(n)], np.int32)
+    yield "gw", _gw(n, rng)
+
+
+def _profits(parent, rng):
+    n = parent.shape[0]
+    yield "ties", rng.integers(0, 4, size=n)
+    yield "equal", np.full(n, 7)
+    yield "sparse", rng.integers(1, 10 ** 6, size=n) * (rng.random(n) < 0.1)
+    yield "spread", rng.integers(0, 2 ** 40, size=n)
+    yield "zipf", 10 ** 12 // (rng.permutation(n) + 1)
+    # the sum needs more than the 47 bits of the reduced profits
+    yield "wide", rng.integers(0, (2 ** 62) // n, size=n)
+
+
+@pytest.mark.parametrize("n", [1, 2, 31, 32, 33, 64, 65, 255, 1023, 1024, 1025, 2111])
+def test_rooted_dp_reduced(oracle_mod, n):
+    rng = np.random.default_rng(n)
+    for tname, parent in _trees(n, rng):
+        for pname, p in _profits(parent, rng):
+            p = np.ascontiguousarray(p, np.int64)
+            for k in sorted({1, 2, 63, 64, 65, n // 20 + 1, n // 3 + 1, n}):
+                sel, val = B.pp_rooted_dp(parent, p, k)
+                osel, oval = oracle_mod.rooted_dp(parent, p, k)
+                assert val == oval, (tname, pname, k)
+                np.testing.assert_array_equal(sel, osel, err_msg=f"{tname} {pname} {k}")
+            pf = p * rng.uniform(0.5, 1.5, size=n) * 10.0 ** float(rng.integers(-300, 250))
+            for k in sorted({1, 64, n // 20 + 1, n}):
+                sel, val = B.pp_rooted_dp_f64(parent, pf, k)
+                osel, oval = oracle_mod.rooted_dp_f64(parent, pf, k)
+                assert val == oval, (tname, pname, k, "f64")
+                np.testing.assert_array_equal(sel, osel, err_msg=f"{tname} {pname} {k} f64")
+
+
+@pytest.mark.parametrize("n,k", [(12_345, 700), (20_011, 1_531), (50_000, 4_096), (50_000, 8_192),
+                                 (50_000, 128), (60_000, 3_000), (66_000, 500)])
+@pytest.mark.parametrize("tree", ["gw", "forest"])
+def test_rooted_dp_reduced_sizes(oracle_mod, n, k, tree):
+    """Up to the limits of the level order (65,536 slots) and of the node lists."""
+    rng = np.random.default_rng(n + k)
+    parent = _gw(n, rng) if tree == "gw" else W.random_forest(n, rng, p_root=0.001)
+    for p in (10 ** 13 // (rng.permutation(n) + 1), rng.integers(0, 300, size=n)):
+        p = p.astype(np.int64)
+        sel, val = B.pp_rooted_dp(parent, p, k)
+        osel, oval = oracle_mod.rooted_dp(parent, p, k)
+        assert val == oval
+        np.testing.assert_array_equal(sel, osel)
+    pf = p * rng.uniform(0.9, 1.1, size=n)
+    sel, val = B.pp_rooted_dp_f64(parent, pf, k)
+    osel, oval = oracle_mod.rooted_dp_f64(parent, pf, k)
+    assert val == oval
+    np.testing.assert_array_equal(sel, osel)
+
+
+def _same(g, o):
+    assert g.objective == o.objective
+    np.testing.assert_array_equal(g.target, o.target)
+    for key in ("start_objective", "start_sweeps", "start_accepts", "standalone", "orders"):
+        np.testing.assert_array_equal(getattr(g, key), getattr(o, key))
+    assert (g.best_start, g.updates, g.dp_cells) == (o.best_start, o.updates, o.dp_cells)
+
+
+@pytest.mark.parametrize("seed", range(24))
+def test_plan_reduced(oracle_mod, seed):
+    """Whole plans, integer and real-valued, pairwise and requester-side
+    costs with the comparators, small budgets to budgets beyond n."""
+    rng = np.random.default_rng(7000 + seed)
+    m, n = int(rng.integers(1, 7)), int(rng.integers(1, 500))
+    inst = W.random_instance(n, m, rng, kmax=int(rng.choice([3, 40, n + 2])),
+                             source_dependent=bool(seed % 3),
+                             value_range=int(rng.choice([4, 100, 10 ** 6])))
+    kw = dict(n_starts=int(rng.integers(0, 5)), max_rounds=int(rng.integers(0, 3)),
+              order_seed=seed, flags=B.PP_F_SAFEGUARDS if seed % 2 else 0)
+    _same(B.pp_plan(inst.parent, inst.demand, inst.recompute_cost, inst.fetch_cost, inst.cap,
+                    **kw),
+          oracle_mod.plan(inst.parent, inst.demand, inst.recompute_cost, inst.fetch_cost,
+                          inst.cap, **kw))
+    lam, w, f = W.real_valued(inst, seed, jitter=0.5)
+    eps = float(rng.choice([0.0, 1e-9])) * float(np.sum(lam * w))
+    _same(B.pp_plan_f64(inst.parent, lam, w, f, inst.cap, epsilon=eps, **kw),
+          oracle_mod.plan_f64(inst.parent, lam, w, f, inst.cap, epsilon=eps, **kw))
