@@ -345,7 +345,7 @@ __device__ __forceinline__ void store_profit(const DevState& d, int64_t s, int64
 
 __global__ void k_profit_keys(DevState d, int64_t s) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < d.n) d.key_lv[s * d.nlv + d.lvslot[i]] = profit_key(d.profit[s * d.n + i], d.f64);
+  if (i < d.n) store_profit(d, s, i, d.profit[s * d.n + i]);
 }
 
 // p_h(b) = sum_m Lambda_m(b) [q_{m<-h}(b) - v_m^{(-h)}(b)]_+  (Eq. 7) for

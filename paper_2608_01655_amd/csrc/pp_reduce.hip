@@ -63,6 +63,7 @@ static_assert(kReduceActive < (1 << kSizeBits), "size field");
 constexpr int kValueBits = 47;  // bound on the sum of the integer profits
 constexpr int kBins = 2048;     // histogram bins, 32 per factor of two
 constexpr int kCopies = 8;      // counters per bin
+constexpr int kPlane = kBins + 32 / kCopies;
 constexpr int kCoreMax = kRThreads;
 constexpr int kMaxSearch = 40;  // evaluations of one price search
 constexpr uint32_t kNone = 0xFFFFu;
@@ -74,7 +75,8 @@ struct Red {  // block-wide scratch words in LDS
   uint32_t wsum[kRWaves];
   uint32_t vh[64];
   int32_t bt;
-  uint32_t depth_max, core, forced;
+  uint32_t core, forced;
+  uint32_t used[kCoreMax / 32];  // core depths of the rows that are skipped to
   int64_t value;
   double price[kLadderRungs];
   int32_t count[kLadderRungs];
@@ -82,6 +84,13 @@ struct Red {  // block-wide scratch words in LDS
 };
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// Barrier where only LDS is exchanged: global loads stay in flight across it.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 
 // Exclusive prefix over the block of one count per thread; *total: the sum.
 __device__ uint32_t block_scan(uint32_t c, uint32_t* wsum, uint32_t* total) {
@@ -92,14 +101,15 @@ __device__ uint32_t block_scan(uint32_t c, uint32_t* wsum, uint32_t* total) {
     if (lane >= o) x += y;
   }
   if (lane == 63) wsum[wv] = x;
-  __syncthreads();
+  lds_barrier();
   uint32_t base = 0, t = 0;
+#pragma unroll
   for (int k = 0; k < kRWaves; ++k) {
     const uint32_t v = wsum[k];
     base += k < wv ? v : 0u;
     t += v;
   }
-  __syncthreads();
+  lds_barrier();
   *total = t;
   return base + x - c;
 }
@@ -107,10 +117,11 @@ __device__ uint32_t block_scan(uint32_t c, uint32_t* wsum, uint32_t* total) {
 __device__ int64_t block_total(int64_t v, int64_t* part) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
-  __syncthreads();
+  lds_barrier();
   int64_t t = 0;
+#pragma unroll
   for (int k = 0; k < kRWaves; ++k) t += part[k];
-  __syncthreads();
+  lds_barrier();
   return t;
 }
 
@@ -120,8 +131,16 @@ __device__ int64_t block_total(int64_t v, int64_t* part) {
 // |S| at a price is between about 0.4 and 1 times the number of profits
 // above it on prefix trees (profits that the other workers' copies leave
 // under poor ancestors do not count), so the steps are small there.
-__device__ constexpr int kRungRank16[kLadderRungs] = {1,  4,  10, 13, 14, 16, 18, 20,
-                                                      23, 26, 30, 35, 41, 50, 70, 130};
+// Launches of more than 16 chains take half as many steps, so that the blocks
+// fit the chip at once.  The last ones are for gaps that are a large part of a
+// price (small k').
+__device__ constexpr int kRank16[kLadderRungs] = {4,  10, 12, 14, 16, 18, 20,  23,
+                                                  26, 30, 35, 41, 50, 64, 100, 400};
+__device__ constexpr int kRank8[kLadderRungs / 2] = {8, 13, 17, 22, 30, 42, 64, 150};
+
+__device__ __forceinline__ int rung_rank16(int rung, int rungs) {
+  return rungs == kLadderRungs ? kRank16[rung] : kRank8[rung];
+}
 
 // S_t for a ladder of prices t, one block per (chain, rung).  Profits come as
 // the upper 32 bits of doubles, rounded up (profit keys).  Child sums are
@@ -130,11 +149,11 @@ __device__ constexpr int kRungRank16[kLadderRungs] = {1,  4,  10, 13, 14, 16, 18
 // (the clip exceeds one price per level).  Integer sums: the same bits
 // whatever the order of the atomics.
 template <bool F64>
-__global__ void __launch_bounds__(kRThreads) k_ladder(ChainSet set, DevState d) {
+__global__ void __launch_bounds__(kRThreads) k_ladder(ChainSet set, DevState d, int rungs) {
   extern __shared__ int64_t lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = uniform(tid >> 6);
-  const int ci = blockIdx.x / kLadderRungs, rung = blockIdx.x % kLadderRungs;
+  const int ci = blockIdx.x / rungs, rung = blockIdx.x % rungs;
   const int64_t slot = set.slot[ci];
   if (d.cs[slot].skip) return;
   const int kp = set.kprime[ci];
@@ -142,16 +161,17 @@ __global__ void __launch_bounds__(kRThreads) k_ladder(ChainSet set, DevState d) 
   const int nlw = nlv / 32, n64 = nlv / 64;
   Red* red = (Red*)lds;
   int32_t* lst = (int32_t*)((char*)lds + kReduceRedBytes);  // level starts, then leaf0
-  uint32_t* bits = (uint32_t*)(lst + ((levels + 2) & ~1));
+  uint32_t* bits = (uint32_t*)(lst + ((levels + 2) & ~1));  // (8-byte aligned)
   uint32_t* cs = bits + nlw;
-  // The histogram comes first, kCopies counters per bin: most profits fall
-  // into a few bins, and atomics of one wave on one counter take turns.
+  // The histogram comes first, kCopies counters per bin (in planes a few
+  // banks apart): most profits fall into a few bins, and atomics of one wave
+  // on one counter take turns.
   uint32_t* suf = cs;
-  const int copy = lane % kCopies;
+  uint32_t* const sufc = suf + (lane % kCopies) * kPlane;
   const uint32_t* __restrict__ key = d.key_lv + slot * (int64_t)nlv;
   const uint16_t* __restrict__ par = d.lvpar;
   for (int q = tid; q <= levels; q += kRThreads) lst[q] = d.lvtab[q];
-  for (int b = tid; b < kBins * kCopies; b += kRThreads) suf[b] = 0;
+  for (int b = tid; b < kPlane * kCopies; b += kRThreads) suf[b] = 0;
   int base = 1023 << 5;  // integer profits: from 1 up
   __syncthreads();
   // (padding slots have key 0: no profit)
@@ -166,14 +186,17 @@ __global__ void __launch_bounds__(kRThreads) k_ladder(ChainSet set, DevState d) 
     base = (int)(mx >> 15) - (kBins - 1);
     __syncthreads();
   }
+  // Ranks of many hundreds are estimated from every fourth profit: the rungs
+  // need not be exact.
+  const int every = kp >= 1024 ? 4 : 1;
 #pragma unroll 8
-  for (int i = tid; i < nlv; i += kRThreads) {
+  for (int i = tid * every + (tid & (every - 1)); i < nlv; i += kRThreads * every) {
     const uint32_t x = key[i];
-    if (x) atomicAdd(suf + max((int)(x >> 15) - base, 0) * kCopies + copy, 1u);
+    if (x) atomicAdd(sufc + max((int)(x >> 15) - base, 0), 1u);
   }
-  __syncthreads();
+  lds_barrier();
   // the rung's price: the largest edge with at least `want` profits above
-  const int64_t want = max((int64_t)1, (int64_t)kRungRank16[rung] * kp / 16);
+  const int64_t want = max((int64_t)1, (int64_t)rung_rank16(rung, rungs) * kp / (16 * every));
   {
     constexpr int per = kBins / kRThreads;
     uint32_t c = 0, h[per];
@@ -181,7 +204,7 @@ __global__ void __launch_bounds__(kRThreads) k_ladder(ChainSet set, DevState d) 
     for (int b = 0; b < per; ++b) {
       h[b] = 0;
 #pragma unroll
-      for (int k = 0; k < kCopies; ++k) h[b] += suf[(tid * per + b) * kCopies + k];
+      for (int k = 0; k < kCopies; ++k) h[b] += suf[k * kPlane + tid * per + b];
       c += h[b];
     }
     if (tid == 0) red->bt = 0;
@@ -210,74 +233,79 @@ __global__ void __launch_bounds__(kRThreads) k_ladder(ChainSet set, DevState d) 
   };
   for (int q = tid; q < leaf0; q += kRThreads) cs[q] = 0;
   __syncthreads();
+  uint64_t* const bits64 = (uint64_t*)bits;
   auto put = [&](int i, uint64_t m) {  // the wave's 64 bits at slot i - lane
-    if ((lane & 31) == 0) bits[(i - lane) / 32 + (lane >> 5)] = (uint32_t)(m >> (lane & 32));
+    if (lane == 0) bits64[i >> 6] = m;
   };
   // up: the leaves at once, then the levels from the deepest
-#pragma unroll 4
+#pragma unroll 8
   for (int i = leaf0 + tid; i < nlv; i += kRThreads) {
     const int v = up(key[i]);
     const uint32_t pr = par[i];
     put(i, __ballot(v > 0));
     if (v > 0 && pr != kNone) atomicAdd(cs + pr, (uint32_t)min(v, clip));
   }
+  // (a thread's first node of the two levels above is loaded ahead)
   {
-    uint32_t kn = 0, pn = kNone;
-    auto load = [&](int q) {
-      if (q >= 0 && lst[q] + tid < lst[q + 1]) {
-        kn = key[lst[q] + tid];
-        pn = par[lst[q] + tid];
-      }
+    uint32_t k0 = 0, p0 = kNone, k1 = 0, p1 = kNone;
+    auto load = [&](int q, uint32_t& k, uint32_t& p) {
+      const int i = q >= 0 ? min(lst[q] + tid, nlv - 1) : 0;
+      k = key[i];
+      p = par[i];
     };
-    load(levels - 1);
+    load(levels - 1, k0, p0);
+    load(levels - 2, k1, p1);
     for (int q = levels - 1; q >= 0; --q) {
       const int end = lst[q + 1];
-      __syncthreads();
+      uint32_t x = k0, pr = p0;
+      k0 = k1;
+      p0 = p1;
+      load(q - 2, k1, p1);
+      lds_barrier();
       for (int i = lst[q] + tid; i < end; i += kRThreads) {
-        const uint32_t x = kn, pr = pn;
-        if (i + kRThreads < end) {
-          kn = key[i + kRThreads];
-          pn = par[i + kRThreads];
-        }
+        // (past the level's end: some later slot, unused)
+        const uint32_t xn = key[min(i + kRThreads, nlv - 1)];
+        const uint32_t pn = par[min(i + kRThreads, nlv - 1)];
         const int v = up(x) + (int)cs[i];
         put(i, __ballot(v > 0));
         if (v > 0 && pr != kNone) atomicAdd(cs + pr, (uint32_t)min(v, clip));
+        x = xn;
+        pr = pn;
       }
-      load(q - 1);
     }
   }
   // down: what hangs on positive ancestors
   {
     auto keep = [&](int i, uint32_t pr) {
-      const uint64_t own = (uint64_t)bits[(i - lane) / 32 + 1] << 32 | bits[(i - lane) / 32];
-      if (own == 0) return;
-      const bool in = ((own >> lane) & 1u) &&
-                      (pr == kNone || ((bits[pr >> 5] >> (pr & 31)) & 1u));
-      put(i, __ballot(in));
+      const uint64_t own = bits64[i >> 6];
+      const uint32_t pw = bits[pr >> 5];  // (roots: some word in LDS)
+      const uint64_t m = __ballot(pr == kNone || ((pw >> (pr & 31)) & 1u));
+      put(i, own & m);
     };
-    uint32_t pn = kNone;
+    auto load = [&](int q) { return (uint32_t)par[q < levels ? min(lst[q] + tid, nlv - 1) : 0]; };
+    uint32_t p0 = load(1), p1 = load(2);
     for (int q = 1; q < levels; ++q) {
       const int end = lst[q + 1];
-      if (lst[q] + tid < end) pn = par[lst[q] + tid];
-      __syncthreads();
+      uint32_t pr = p0;
+      p0 = p1;
+      p1 = load(q + 2);
+      lds_barrier();
       for (int i = lst[q] + tid; i < end; i += kRThreads) {
-        const uint32_t pr = pn;
-        if (i + kRThreads < end) pn = par[i + kRThreads];
+        const uint32_t pn = par[min(i + kRThreads, nlv - 1)];
         keep(i, pr);
+        pr = pn;
       }
     }
-    __syncthreads();
-#pragma unroll 4
+    lds_barrier();
+#pragma unroll 8
     for (int i = leaf0 + tid; i < nlv; i += kRThreads) keep(i, par[i]);
-    __syncthreads();
+    lds_barrier();
   }
   uint32_t* out = d.lad_bits + (slot * kLadderRungs + rung) * (int64_t)nlw;
-  uint32_t* pre = d.lad_pre + (slot * kLadderRungs + rung) * (int64_t)n64;
   for (int w = tid; w < nlw; w += kRThreads) out[w] = bits[w];
   uint32_t tot;
-  const uint32_t c = tid < n64 ? __popc(bits[2 * tid]) + __popc(bits[2 * tid + 1]) : 0u;
-  const uint32_t run = block_scan(c, red->wsum, &tot);
-  if (tid < n64) pre[tid] = run;
+  const uint32_t run = block_scan(tid < n64 ? __popcll(bits64[tid]) : 0, red->wsum, &tot);
+  if (tid < n64) d.lad_pre[(slot * kLadderRungs + rung) * (int64_t)n64 + tid] = run;
   if (tid == 0) {
     d.lad_price[slot * kLadderRungs + rung] = t;
     d.lad_count[slot * kLadderRungs + rung] = (int32_t)tot;
@@ -407,7 +435,7 @@ __device__ void core_walk(int core, const uint64_t* ch, const uint16_t* cnx,
 
 template <bool F64>
 __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, int mode,
-                                                      int lds_bytes) {
+                                                      int lds_bytes, int rungs) {
   extern __shared__ int64_t lds[];
   const int tid = threadIdx.x;
   const int ci = blockIdx.x;
@@ -418,7 +446,8 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
   const int kp = set.kprime[ci];
   const int64_t* __restrict__ prof = d.profit + slot * (int64_t)n;
   // the active nodes, leaves first, then the deepest level: position, parent's
-  // index | level << 16 (leaves: d.levels), integer profit
+  // index | level << 16 (leaves: d.levels), integer profit (an entry is
+  // written and read by one thread)
   uint32_t* apos = d.lad_list + slot * (int64_t)(4 * kReduceActive);
   uint32_t* amd = apos + kReduceActive;
   int64_t* aq = (int64_t*)(amd + kReduceActive);
@@ -433,15 +462,15 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
   if (kp <= 0) return;
   double* price = red->price;
   int32_t* count = red->count;
-  if (tid < kLadderRungs) {
+  if (tid < rungs) {
     price[tid] = d.lad_price[slot * kLadderRungs + tid];
     count[tid] = d.lad_count[slot * kLadderRungs + tid];
   }
   __syncthreads();
   // the highest rung with clearly more than k' nodes, else price 0
-  const int need = kp + kp / 8 + 160;
+  const int need = kp + kp / 16 + 160;
   int j = 0;
-  while (j < kLadderRungs - 1 && count[j] < need && price[j] > 0.0) ++j;
+  while (j < rungs - 1 && count[j] < need && price[j] > 0.0) ++j;
   const int nwords = d.npad / 32;
   uint32_t* selw = d.sel + slot * nwords;
 
@@ -464,20 +493,17 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
       uint32_t* list = (uint32_t*)W;
       uint64_t* lb = (uint64_t*)(list + kReduceActive);
       uint32_t* lp = (uint32_t*)(lb + n64);
-      const uint64_t* rb =
-          (const uint64_t*)(d.lad_bits + (slot * kLadderRungs + j) * (int64_t)(2 * n64));
-      const uint32_t* rpre = d.lad_pre + (slot * kLadderRungs + j) * (int64_t)n64;
       if (tid < n64) {
-        uint64_t m = rb[tid];
-        int x = A - 1 - (int)rpre[tid];
+        const int64_t o = (slot * kLadderRungs + j) * (int64_t)n64 + tid;
+        const uint64_t m = ((const uint64_t*)d.lad_bits)[o];
+        int x = A - 1 - (int)d.lad_pre[o];
         lb[tid] = m;
         lp[tid] = (uint32_t)x;  // active index of the group's first node
-        while (m) {
-          list[x--] = (uint32_t)(64 * tid + __builtin_ctzll(m));
-          m &= m - 1;
-        }
+        // (a thread per 64 slots: a wave-wide compaction per group took twice
+        // as long, 800 groups each paying its LDS latency)
+        for (uint64_t r = m; r; r &= r - 1) list[x--] = (uint32_t)(64 * tid + __builtin_ctzll(r));
       }
-      __syncthreads();
+      lds_barrier();
       double total = 0.0;
 #pragma unroll 2
       for (int x = tid; x < A; x += kRThreads) {
@@ -487,8 +513,8 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
         uint32_t ps = kNone;
         if (pr != kNone)
           ps = lp[pr >> 6] - __popcll(lb[pr >> 6] & ((1ull << (pr & 63)) - 1u));
-        apos[x] = pd & 0xFFFFFFu;
         const int lv = min((int)(pd >> 24), d.levels);  // leaves: below every level
+        apos[x] = pd & 0xFFFFFFu;
         amd[x] = ps | (uint32_t)lv << 16;
         aq[x] = p;
         total += F64 ? as_d(p) : (double)p;
@@ -568,7 +594,7 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
         if (tid == 0) cw[acap + parity] = 0;
         int64_t qa = tid < A ? aq[tid] : 0, qb = 0;
         uint32_t ma = tid < A ? amd[tid] : 0xFFFF0000u, mb = 0xFFFF0000u;
-        __syncthreads();
+        lds_barrier();
         int cur = uniform(red->lev[0]);
         for (int u = 0; u < chunks; ++u) {
           const int x = tid + kRThreads * u;
@@ -582,7 +608,7 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
           const int l0 = uniform(red->lev[2 * u]), l1 = uniform(red->lev[2 * u + 1]);
           for (int dd = l0; dd >= l1; --dd) {
             if (dd != cur) {  // the levels below are complete
-              __syncthreads();
+              lds_barrier();
               cur = dd;
             }
             if ((int)(md >> 16) == dd) {
@@ -596,7 +622,7 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
           qa = qb;
           ma = mb;
         }
-        __syncthreads();
+        lds_barrier();
         const int64_t root = cw[acap + parity];
         const int fsize = (int)((uint32_t)root & ((1u << kSizeBits) - 1));
         rootsum = root >> kSizeBits;
@@ -680,7 +706,7 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
         const int l0 = uniform(red->lev[2 * u]), l1 = uniform(red->lev[2 * u + 1]);
         for (int dd = l1; dd <= l0; ++dd) {
           if (dd != cur) {
-            __syncthreads();
+            lds_barrier();
             cur = dd;
           }
           if ((int)(md >> 16) == dd) {
@@ -694,7 +720,7 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
           }
         }
       }
-      __syncthreads();
+      lds_barrier();
     }
     // nodes that are not active stay out while gap <= dmax
     const int64_t dmax = t == 0.0 ? INT64_MAX : max(lam - tq - 1, (int64_t)0);
@@ -719,7 +745,7 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
       const uint64_t m = __ballot(ok);  // a prefix of the bins
       return m == 0 ? 0 : ((int64_t)1 << (63 - __builtin_clzll(m))) - 1;
     };
-    int64_t width = min(dmax, widest(96));
+    int64_t width = min(dmax, widest(64));
     if (lam == 0) width = 0;
     // LDS after the child sums (the core is small: they stay for a second,
     // wider one)
@@ -727,7 +753,8 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
     const int xbytes = wbytes - 8 * A;
     bool lower = false;
     for (int attempt = 0; attempt < 4 && !lower; ++attempt) {
-      if (tid == 0) red->core = red->forced = red->depth_max = 0;
+      if (tid == 0) red->core = red->forced = 0;
+      if (tid < kCoreMax / 32) red->used[tid] = 0;
       for (int w = tid; w < nw; w += kRThreads) sel[w] = 0;
       int off = 0;
       auto take = [&](int64_t bytes) {
@@ -797,7 +824,6 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
         cpos[rk] = q;
         cnx[rk] = (uint16_t)nx;
         cdep[rk] = (uint16_t)dep;
-        atomicMax(&red->depth_max, dep);
         if (F64) atomicOr(ib + (q >> 5), 1u << (q & 31));
       }
       __syncthreads();
@@ -818,24 +844,38 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
                    ? rows
                    : (int)(ip[at >> 5] + __popc(ib[at >> 5] & ((1u << (at & 31)) - 1u)));
       };
-      int64_t* slots = (int64_t*)take(((int64_t)red->depth_max + 2) * C * 512);
-      if (off > xbytes) return;
-      // Row words.  A row is stored to the slot of its core depth if some
-      // earlier core row that is no leaf skips to it: between such a row and
-      // its readers every other stored row lies below the reader, so it is
-      // deeper.  Forced rows have no core ancestor (depth 0).
+      // Row words.  A row is stored if some earlier core row that is no leaf
+      // skips to it, in the slot of its core depth: between such a row and its
+      // readers every other stored row lies below the reader, so it is deeper.
+      // Forced rows have no core ancestor (depth 0).  Slots are numbered by
+      // the depths that are in use.
+      int it = 0, nit = 0;
+      uint32_t td = kNone;  // depth of the row this one skips to
       if (tid < R) {
-        const int it = F64 ? row_of(q) : (int)rk;
-        const int nit = F64 ? row_of(qe) : (int)nx;
+        it = F64 ? row_of(q) : (int)rk;
+        nit = F64 ? row_of(qe) : (int)nx;
         rp[it] = prof[q];
-        uint32_t info = 0;
-        if (nit == it + 1) {
-          info = kRowLeaf;
-        } else if (nit < rows) {
-          // the target row (the first at or past the subtree's end) is a
-          // core row iff it is the first core row there
-          uint32_t sd = 1;
-          if ((int)nx < R && (!F64 || row_of(cpos[nx]) == nit)) sd = cdep[nx] + 1u;
+        if (nit != it + 1 && nit < rows) {
+          // the target (the first row at or past the subtree's end) is a core
+          // row iff it is the first core row there
+          td = (int)nx < R && (!F64 || row_of(cpos[nx]) == nit) ? cdep[nx] : 0u;
+          atomicOr(&red->used[td >> 5], 1u << (td & 31));
+        }
+      }
+      lds_barrier();
+      int nslots = 1;  // the zero row
+      uint32_t sd = 0;
+      for (int w = 0; w < kCoreMax / 32; ++w) {
+        const uint32_t m = red->used[w];
+        if (w < (int)(td >> 5)) sd += __popc(m);
+        nslots += __popc(m);
+      }
+      int64_t* slots = (int64_t*)take((int64_t)nslots * C * 512);
+      if (off > xbytes) return;
+      if (tid < R) {
+        uint32_t info = nit == it + 1 ? kRowLeaf : 0u;
+        if (td != kNone) {
+          sd += __popc(red->used[td >> 5] & ((1u << (td & 31)) - 1u)) + 1u;
           info = sd << 16;
           atomicOr(&rinfo[nit], sd << 2);
         }
@@ -881,19 +921,17 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
         }
         return;
       }
-      // wider: the gap itself if its core is small enough, else (the gap is
-      // this core's poor value) as wide as the next limit allows
-      int64_t next = widest(attempt == 0 ? 320u : 1000u);
-      if (next <= width) next = widest(1000u);
-      const int64_t want = gap <= next || attempt >= 2 ? gap : next;
-      if (width >= dmax || (want <= width && dmax < gap)) lower = true;
-      else if (want <= width) return;
+      // wider: the gap itself, except that a first core's gap may only show
+      // how poor its value is: then to at most 320 nodes
+      const int64_t next = widest(320);
+      const int64_t want = attempt == 0 && gap > next && next > width ? next : gap;
+      if (width >= dmax) lower = true;
       else width = min(want, dmax);
     }
     if (!lower) return;
     int jn = j + 1;
-    while (jn < kLadderRungs && price[jn] > 0.0 && count[jn] < A + A / 2) ++jn;
-    if (jn >= kLadderRungs) return;
+    while (jn < rungs && price[jn] > 0.0 && count[jn] < A + A / 2) ++jn;
+    if (jn >= rungs) return;
     j = jn;
     __syncthreads();
   }
@@ -905,7 +943,7 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
 // level-order slots, `levels` levels and leaf0 slots of internal nodes.
 size_t ladder_lds(int32_t nlv, int32_t levels, int32_t leaf0) {
   return kReduceRedBytes + 4 * ((size_t)levels + 2) + (size_t)nlv / 8 +
-         4 * (size_t)std::max<int32_t>(kBins * kCopies, leaf0) + 16;
+         4 * (size_t)std::max<int32_t>(kPlane * kCopies, leaf0) + 16;
 }
 
 size_t reduce_lds_min(int32_t n, int32_t nlv, int32_t levels, int32_t leaf0) {
@@ -925,15 +963,16 @@ hipError_t launch_reduce(const ChainSet& set, const DevState& d, int mode, int l
       reduce_lds_min(d.n, d.nlv, d.levels, d.leaf0) > (size_t)lds)
     return hipErrorInvalidValue;
   const size_t lad = ladder_lds(d.nlv, d.levels, d.leaf0);
-  const dim3 grid((unsigned)(set.count * kLadderRungs));
+  const int rungs = set.count <= 16 ? kLadderRungs : kLadderRungs / 2;
+  const dim3 grid((unsigned)(set.count * rungs));
   if (d.f64) {
-    hipLaunchKernelGGL(k_ladder<true>, grid, dim3(kRThreads), lad, st, set, d);
+    hipLaunchKernelGGL(k_ladder<true>, grid, dim3(kRThreads), lad, st, set, d, rungs);
     hipLaunchKernelGGL(k_reduce<true>, dim3(set.count), dim3(kRThreads), lds, st, set, d, mode,
-                       lds);
+                       lds, rungs);
   } else {
-    hipLaunchKernelGGL(k_ladder<false>, grid, dim3(kRThreads), lad, st, set, d);
+    hipLaunchKernelGGL(k_ladder<false>, grid, dim3(kRThreads), lad, st, set, d, rungs);
     hipLaunchKernelGGL(k_reduce<false>, dim3(set.count), dim3(kRThreads), lds, st, set, d, mode,
-                       lds);
+                       lds, rungs);
   }
   return hipGetLastError();
 }
