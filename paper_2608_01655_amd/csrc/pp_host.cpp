@@ -739,14 +739,14 @@ int npad_of(int32_t n) { return (n + 63) / 64 * 64; }
 
 // Allocate per-slot buffers for `slots` chains of up to `kmax` cells.
 int ensure_slots(pp_ctx* c, DevState& d, int32_t slots, int32_t kmax,
-                 int cells) {
+                 int cells, int64_t rows = 0) {
   const size_t n = (size_t)d.n, m = (size_t)d.m, npad = (size_t)d.npad;
   const int32_t stages = std::max(1, (kmax + 64 * cells - 1) / (64 * cells));
   PP_TRY(c->tgt.ensure(slots * m * n));
   PP_TRY(c->v1.ensure(slots * m * n * 8));
   PP_TRY(c->v2.ensure(slots * m * n * 8));
   PP_TRY(c->h1.ensure(slots * m * n));
-  PP_TRY(c->profit.ensure(slots * n * 8));
+  PP_TRY(c->profit.ensure((slots + rows) * n * 8));
   PP_TRY(c->sel.ensure(slots * (npad / 8)));
   PP_TRY(c->bits.ensure((size_t)slots * stages * cells * npad * 8));
   // ring words carry a launch tag; fresh memory is zeroed so that no stale
@@ -804,6 +804,7 @@ ChainSet chain_set(const std::vector<int32_t>& slots,
     s.src[k - lo] = slots[k];
     s.worker[k - lo] = workers[k];
     s.kprime[k - lo] = kprime[k];
+    s.row[k - lo] = slots[k];
   }
   return s;
 }
@@ -860,6 +861,7 @@ struct Engine {
         s.src[s.count] = in.src[k];
         s.worker[s.count] = in.worker[k];
         s.kprime[s.count] = in.kprime[k];
+        s.row[s.count] = in.row[k];
         s.base[s.count] = blocks;
         blocks += g;
         ++s.count;
@@ -884,7 +886,7 @@ struct Engine {
     if (set.count == 0) return PP_OK;
     PP_HIP(launch_take_standalone(set, d, sel0, st));
     if (d.f64) PP_HIP(launch_gexact(set, d, kModeGreedy, st));  // exact G, marks
-    PP_HIP(launch_commit(set, d, kModeGreedy, st));
+    PP_HIP(launch_commit(set, d, 0, st));
     return PP_OK;
   }
 
@@ -914,7 +916,7 @@ struct Engine {
     PP_HIP(launch_gains(set, d, st, kGainsMarginal, mode == kModeRefine ? 1 : 0));
     PP_TRY(solve(set, mode));
     if (d.f64) PP_HIP(launch_gexact(set, d, mode, st));  // exact G and the decision
-    PP_HIP(launch_commit(set, d, mode, st));
+    PP_HIP(launch_commit(set, d, 0, st));
     return PP_OK;
   }
 };
@@ -963,6 +965,8 @@ int choose_cells(int32_t total_stage_cells_c1, int dev, int32_t slots_lds) {
 // whose tables fit.  Forcing the sweep's lane width or its spin limit (test
 // hooks) asks for the sweep itself.
 constexpr int32_t kReduceMinN = 1024;
+// device memory a batch's profit rows may take (12 bytes per chunk)
+constexpr int64_t kRowBytes = (int64_t)4 << 30;
 int reduce_lds_for(const TreeLayout& t, int dev) {
   if (std::getenv("PP_DP_CELLS") || std::getenv("PP_SPIN_LIMIT")) return 0;
   if (t.lvtab.empty() || t.n < env_int("PP_REDUCE_MIN_N", kReduceMinN)) return 0;
@@ -976,7 +980,8 @@ int reduce_lds_for(const TreeLayout& t, int dev) {
 }
 
 // The reduced solve's tables and per-slot scratch for `slots` chain slots.
-int ensure_reduce(pp_ctx* c, const TreeLayout& t, DevState& d, int32_t slots, hipStream_t st) {
+int ensure_reduce(pp_ctx* c, const TreeLayout& t, DevState& d, int32_t slots, hipStream_t st,
+                  int64_t rows = 0) {
   const size_t n = (size_t)t.n, nlv = t.lvpos.size(), levels = t.lvtab.size() - 1;
   const size_t a = (n * 4 + 255) & ~(size_t)255, b = a + ((nlv * 4 + 255) & ~(size_t)255),
                e = b + ((nlv * 2 + 255) & ~(size_t)255);
@@ -988,9 +993,9 @@ int ensure_reduce(pp_ctx* c, const TreeLayout& t, DevState& d, int32_t slots, hi
   std::memcpy(h.data() + e, t.lvtab.data(), (levels + 1) * 4);
   PP_TRY(c->lvl.ensure(h.size()));
   PP_TRY(stage_h2d(c, c->lvl.p, h.data(), h.size(), st));
-  PP_TRY(c->key_lv.ensure(slots * nlv * 4));
+  PP_TRY(c->key_lv.ensure((slots + rows) * nlv * 4));
   // the padding slots between levels are never written and hold no profit
-  PP_HIP(hipMemsetAsync(c->key_lv.p, 0, slots * nlv * 4, st));
+  PP_HIP(hipMemsetAsync(c->key_lv.p, 0, (slots + rows) * nlv * 4, st));
   PP_TRY(c->lad_pre.ensure(slots * (size_t)kLadderRungs * (nlv / 16)));
   PP_TRY(c->lad_bits.ensure(slots * (size_t)kLadderRungs * (nlv / 8)));
   PP_TRY(c->lad_stat.ensure(slots * (size_t)kLadderRungs * 12));
@@ -1101,7 +1106,7 @@ int run_safeguards(Engine& e, int32_t m, const std::vector<int32_t>& kp,
     PP_HIP(launch_gains(set, d, st, kGainsLocalDedup));
     PP_TRY(e.solve(set, kModeGreedy));
     if (d.f64) PP_HIP(launch_gexact(set, d, kModeGreedy, st));  // adopts T'_h
-    PP_HIP(launch_commit(set, d, kModeGreedy, st));
+    PP_HIP(launch_commit(set, d, 0, st));
   }
   {
     std::vector<int32_t> z(3, 0);
@@ -1175,6 +1180,13 @@ int refine_starts(Engine& e, const std::vector<int32_t>& starts, int32_t spare_b
       mark_ran(h);
     }
   };
+  // the profits of every (start, worker) at once, then only where an adopted
+  // replacement changes them
+  const bool rows = d.row0 > 0;
+  if (rows) {
+    d.row_s0 = starts[0];
+    PP_HIP(launch_rows(d, starts[0], A, e.st));
+  }
   std::vector<St> st(A);
   {
     std::vector<ChainState> cs0(A);
@@ -1297,8 +1309,10 @@ int refine_starts(Engine& e, const std::vector<int32_t>& starts, int32_t spare_b
       set.src[k] = st[items[k].q].s;
       set.worker[k] = items[k].worker;
       set.kprime[k] = kp[items[k].worker];
+      set.row[k] = rows ? d.row0 + items[k].q * m + items[k].worker : items[k].slot;
     }
-    PP_HIP(launch_gains(set, d, e.st, kGainsMarginal, 1));
+    if (rows) PP_HIP(launch_prep(set, d, e.st));
+    else PP_HIP(launch_gains(set, d, e.st, kGainsMarginal, 1));
     PP_TRY(e.reduce(set, kModeRefine));
     if (!e.reduce_lds) PP_TRY(e.dp(set, 1));
     PP_HIP(launch_backtrack(set, d, kModeRefine, e.st, e.reduce_lds ? 1 : 0));
@@ -1332,6 +1346,7 @@ int refine_starts(Engine& e, const std::vector<int32_t>& starts, int32_t spare_b
           rest.src[q] = set.src[k];
           rest.worker[q] = set.worker[k];
           rest.kprime[q] = set.kprime[k];
+          rest.row[q] = set.row[k];
         }
       if (rest.count > 0) {
         PP_TRY(e.dp(rest, 1));
@@ -1402,7 +1417,7 @@ int refine_starts(Engine& e, const std::vector<int32_t>& starts, int32_t spare_b
     }
     PP_HIP(launch_adopt(ad, d, e.st));
     if (!csl.empty())
-      PP_HIP(launch_commit(chain_set(csl, cwk, ckp, 0, csl.size()), d, kModeRefine, e.st));
+      PP_HIP(launch_commit(chain_set(csl, cwk, ckp, 0, csl.size()), d, rows ? 1 : 0, e.st));
   }
 }
 
@@ -1533,7 +1548,13 @@ int run_plan_once(pp_ctx* c, const TreeLayout& t, int32_t m, const int32_t* cap,
   e.reduce_lds = reduce_lds_for(t, c->device);
   res.lane_cells = cells;
   res.fmax = (e.fmax || f64) ? 1 : 0;
-  PP_TRY(ensure_slots(c, d, slots, kmax, cells));
+  // profit rows of every (start, worker) of a refinement batch, unless they
+  // take more than kRowBytes or nothing is refined
+  int64_t rows = (int64_t)std::min(S, kMaxChains) * m;
+  if (!e.reduce_lds || (o.flags & PP_F_NO_REFINE) || rows * n * 12 > kRowBytes || slots < 1)
+    rows = 0;
+  PP_TRY(ensure_slots(c, d, slots, kmax, cells, rows));
+  d.row0 = rows > 0 ? slots : 0;
   if (f64) {
     d.f64 = 1;
     d.eps = eps;
@@ -1542,7 +1563,7 @@ int run_plan_once(pp_ctx* c, const TreeLayout& t, int32_t m, const int32_t* cap,
   PP_TRY(upload_meta(c, t, cells, st));
   d.meta = c->meta.as<uint32_t>();  // upload_meta may have (re)allocated it
   PP_TRY(upload_spills(c, t, d, slots, st));
-  if (e.reduce_lds) PP_TRY(ensure_reduce(c, t, d, slots, st));
+  if (e.reduce_lds) PP_TRY(ensure_reduce(c, t, d, slots, st, rows));
 
   // --- standalone scores: each worker against the empty placement
   res.standalone.assign(m, 0);

@@ -207,6 +207,8 @@ struct ChainSet {
                                // update computed in a spare slot)
   int32_t worker[kMaxChains];  // worker h being updated
   int32_t kprime[kMaxChains];  // min(k_h, n)
+  int32_t row[kMaxChains];     // profit row of the update (its slot, or the
+                               // row of its start and worker, see row0)
   int32_t base[kMaxChains + 1];  // DP: first block of each chain's stages
 };
 
@@ -238,7 +240,7 @@ struct DevState {
   int32_t levels, nlv, leaf0;
   int32_t lv_bits, lv_clip; // k_ladder's fixed point: bits below one price,
                             // height at which values are clipped
-  uint32_t* key_lv;         // [slots][nlv]  upper halves of the profits as
+  uint32_t* key_lv;         // [rows][nlv]   upper halves of the profits as
                             //            doubles, rounded up
   uint32_t* lad_bits;       // [slots][kLadderRungs][nlv / 32] S_t per rung
   uint32_t* lad_pre;        // [slots][kLadderRungs][nlv / 64] its prefix
@@ -258,7 +260,12 @@ struct DevState {
   int64_t* v1;              // [slots][m][n] best holder saving
   int64_t* v2;              // [slots][m][n] best saving among other holders
   uint8_t* h1;              // [slots][m][n] holder giving v1
-  int64_t* profit;          // [slots][n]    marginal profits p_h, preorder
+  int64_t* profit;          // [rows][n]     marginal profits p_h, preorder:
+                            //   one row per slot, then (refinement, row0 >
+                            //   0) row0 + (s - row_s0) m + h for worker h
+                            //   of the start in slot s, kept current by
+                            //   k_commit
+  int32_t row0, row_s0;
   uint32_t* sel;            // [slots][npad/32] backtracked selection bitmap:
                             //   position q is bit q%32 of word q/32
   uint64_t* bits;           // [slots][stages][cells][npad] DP choice bits:
@@ -387,8 +394,13 @@ hipError_t launch_adopt(const AdoptSet& set, const DevState& d, hipStream_t st);
 // worker (row `worker` of sel0, [m][npad/32]) as its walk would have.
 hipError_t launch_take_standalone(const ChainSet& set, const DevState& d,
                                  const uint32_t* sel0, hipStream_t st);
-hipError_t launch_commit(const ChainSet& set, const DevState& d, int mode,
+// refresh: also the profit rows of the chains' starts at changed chunks
+hipError_t launch_commit(const ChainSet& set, const DevState& d, int refresh,
                          hipStream_t st);
+// profit rows of the `count` starts in slots s0 ...; a refinement update's
+// incumbent value and marks from its row (in place of launch_gains)
+hipError_t launch_rows(const DevState& d, int32_t s0, int32_t count, hipStream_t st);
+hipError_t launch_prep(const ChainSet& set, const DevState& d, hipStream_t st);
 hipError_t launch_objective(const ChainSet& set, const DevState& d,
                             hipStream_t st);
 

@@ -770,7 +770,7 @@ k_dp(ChainSet set, DevState d, uint32_t epoch, uint32_t spin_limit,
     // ---------------------------------------------------------- I/O wave
     const int64_t stride = (int64_t)d.npad;  // steps per stage row of the ring
     const int64_t cstride = 2 * stride;      // choice words per (stage, cell)
-    const int64_t* __restrict__ prof = d.profit + slot * n;
+    const int64_t* __restrict__ prof = d.profit + (int64_t)set.row[ci] * n;
     const uint4* __restrict__ meta = (const uint4*)d.meta;  // [nsteps], padded
     uint32_t* bits = (uint32_t*)d.bits + (slot * d.stages + g) * (int64_t)C * cstride;
     uint64_t* ring_out = d.ring + (slot * d.stages + g) * stride * 2;
@@ -1594,40 +1594,55 @@ __global__ void __launch_bounds__(64) k_backtrack(ChainSet set, DevState d,
 // -------------------------------------------------------------- commit --
 
 // Adopt T'_h where accepted: write the new membership and refresh the top-2
-// holder state of every chunk whose membership changed.  A block holds
-// kCommitThreads / M chunks times M requesters (requester-major, so each
-// requester's loads are contiguous); each thread updates one requester's
-// top-2, and the new membership is written after a barrier.  Only worker
-// h's membership changes, so the new state follows from the old one and
-// h's saving q_h: when h joins, q_h is inserted (top-2 values of the
-// multiset, lowest holder id among the maxima); when h leaves and was
-// neither the best holder nor tied with the second value (q_h < v2), the
-// state is unchanged.  Otherwise (h leaves as h1, or with q_h == v2) the
-// thread rebuilds the top-2 over all holders, O(M).
+// holder state of every chunk whose membership changed.  A block looks at
+// kCommitTile chunks, lists the changed ones and spreads (changed chunk,
+// requester) pairs over its threads, requester-major, so that each
+// requester's loads are near each other.  Only worker h's membership
+// changes, so the new state follows from the old one and h's saving q_h:
+// when h joins, q_h is inserted (top-2 values of the multiset, lowest holder
+// id among the maxima); when h leaves and was neither the best holder nor
+// tied with the second value (q_h < v2), the state is unchanged.  Otherwise
+// (h leaves as h1, or with q_h == v2) the thread rebuilds the top-2 over all
+// holders, O(M).
+// refresh: the profits of every worker of the start at the changed chunks
+// follow (DevState::row0), each in full, so that they are the bits k_gains
+// would compute.
 constexpr int kCommitThreads = 256;
+constexpr int kCommitTile = 64;  // one choice per lane of the first wave
 
 __global__ void __launch_bounds__(kCommitThreads) k_commit(ChainSet set, DevState d,
-                                                            int mode) {
+                                                            int refresh) {
   const int ci = blockIdx.y;
   const int64_t s = set.slot[ci];
   if (!d.cs[s].accept) return;
   const int h = set.worker[ci];
   const int m = d.m;
   const int64_t n = d.n;
-  const int cpb = kCommitThreads / m;  // chunks per block (m <= 255)
-  const int r = threadIdx.x / cpb;
-  const int64_t i = (int64_t)blockIdx.x * cpb + threadIdx.x % cpb;
+  const int tid = threadIdx.x;
   const int64_t mn = (int64_t)m * n;
   const uint8_t* t = d.tgt + s * mn;
   uint8_t* th = d.tgt + s * mn + (int64_t)h * n;
-  bool changed = false;
-  uint8_t nv = 0;
-  if (r < m && i < n) {
-    nv = (uint8_t)((d.sel[s * (d.npad / 32) + i / 32] >> (i % 32)) & 1u);
-    changed = nv != th[i];
+  __shared__ uint32_t s_chunk[kCommitTile];  // chunk, bit 31: joins
+  __shared__ int s_count;
+  if (tid < kWave) {
+    const int64_t i = (int64_t)blockIdx.x * kCommitTile + tid;
+    bool changed = false;
+    uint32_t nv = 0;
+    if (i < n) {
+      nv = (d.sel[s * (d.npad / 32) + i / 32] >> (i % 32)) & 1u;
+      changed = nv != th[i];
+    }
+    const uint64_t c = __ballot(changed);
+    if (changed) s_chunk[__popcll(c & ((1ull << tid) - 1u))] = (uint32_t)i | nv << 31;
+    if (tid == 0) s_count = __popcll(c);
   }
-  if (!__syncthreads_or(changed)) return;
-  if (changed) {
+  __syncthreads();
+  const int count = s_count;
+  if (count == 0) return;
+  for (int x = tid; x < count * m; x += kCommitThreads) {
+    const int r = x / count;
+    const uint32_t e = s_chunk[x - r * count];
+    const int64_t i = e & 0x7FFFFFFFu;
     const int64_t o = s * mn + (int64_t)r * n + i;
     const int64_t wr = d.w[(int64_t)r * n + i];
     auto q_of = [&](int l) -> int64_t {
@@ -1641,7 +1656,7 @@ __global__ void __launch_bounds__(kCommitThreads) k_commit(ChainSet set, DevStat
     // savings are non-negative (doubles: finite, +0 for none), so their
     // bit patterns compare like the values
     bool rebuild = false;
-    if (nv) {
+    if (e >> 31) {
       if (hb == kNoHolder) {
         b1 = qh;
         b2 = 0;
@@ -1680,8 +1695,125 @@ __global__ void __launch_bounds__(kCommitThreads) k_commit(ChainSet set, DevStat
     d.v2[o] = b2;
     d.h1[o] = (uint8_t)hb;
   }
-  __syncthreads();  // every requester has read the old membership row
-  if (changed && r == 0) th[i] = nv;
+  if (tid < count) th[s_chunk[tid] & 0x7FFFFFFFu] = (uint8_t)(s_chunk[tid] >> 31);
+  if (!refresh) return;
+  __syncthreads();  // the new holder state is in place
+  for (int x = tid; x < count * m; x += kCommitThreads) {
+    const int l = x / count;
+    const int64_t i = s_chunk[x - l * count] & 0x7FFFFFFFu;
+    int64_t p = 0;
+    double pf = 0.0;
+#pragma unroll 4
+    for (int r = 0; r < m; ++r) {
+      const int64_t o = s * mn + (int64_t)r * n + i;
+      const int64_t vmh = (d.h1[o] == l) ? d.v2[o] : d.v1[o];
+      const int64_t L = d.lam[(int64_t)r * n + i];
+      const int64_t q = saving(d, l, r, i);
+      if (d.f64)
+        pf = pf + as_f(L) * dpos(as_f(q) - as_f(vmh));
+      else
+        p += L * imax(q - vmh, 0);
+    }
+    store_profit(d, d.row0 + (s - d.row_s0) * m + l, i, d.f64 ? as_i(pf) : p);
+  }
+}
+
+// Profits of every worker of `count` starts from slot s0 on, into their rows
+// (DevState::row0); real-valued costs: also the scale sum Lambda * w, in the
+// starts' gwo.  One thread per chunk keeps the sums of kRowWorkers workers
+// in registers (blockIdx.y: which of them), so the holder state is read once
+// for all of them; each worker's terms are added in increasing requester,
+// as in k_gains.  Blocks of one tile of chunks, over the starts, are eight
+// apart: they land on one XCD, whose L2 then serves the fetch costs.
+constexpr int kRowWorkers = 16;
+
+__global__ void __launch_bounds__(256) k_rows(DevState d, int64_t s0, int count, int tiles) {
+  const int xcd = blockIdx.x % 8, at = blockIdx.x / 8;
+  const int64_t s = s0 + at % count;
+  const int tile = at / count * 8 + xcd;
+  if (tile >= tiles) return;
+  const int l0 = blockIdx.y * kRowWorkers;
+  const int m = d.m, lc = min(kRowWorkers, m - l0);
+  const int64_t n = d.n, mn = (int64_t)m * n;
+  const int64_t i = (int64_t)tile * 256 + threadIdx.x;
+  int64_t p[kRowWorkers];
+  double pf[kRowWorkers], wl = 0.0;
+#pragma unroll
+  for (int k = 0; k < kRowWorkers; ++k) {
+    p[k] = 0;
+    pf[k] = 0.0;
+  }
+  if (i < n) {
+    for (int r = 0; r < m; ++r) {
+      const int64_t o = s * mn + (int64_t)r * n + i;
+      const int64_t v1 = d.v1[o], v2 = d.v2[o];
+      const int hb = d.h1[o];
+      const int64_t L = d.lam[(int64_t)r * n + i], wr = d.w[(int64_t)r * n + i];
+      const int64_t* f = d.f + ((int64_t)l0 * m + r) * n + i;
+      if (d.f64) {
+        wl = wl + as_f(L) * as_f(wr);
+#pragma unroll
+        for (int k = 0; k < kRowWorkers; ++k)
+          if (k < lc) {
+            const int l = l0 + k;
+            const double q = l == r ? as_f(wr) : dpos(as_f(wr) - as_f(f[(int64_t)k * m * n]));
+            pf[k] = pf[k] + as_f(L) * dpos(q - as_f(hb == l ? v2 : v1));
+          }
+      } else {
+#pragma unroll
+        for (int k = 0; k < kRowWorkers; ++k)
+          if (k < lc) {
+            const int l = l0 + k;
+            const int64_t q = l == r ? wr : imax(wr - f[(int64_t)k * m * n], 0);
+            p[k] += L * imax(q - (hb == l ? v2 : v1), 0);
+          }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kRowWorkers; ++k)
+      if (k < lc)
+        store_profit(d, d.row0 + (s - d.row_s0) * m + l0 + k, i, d.f64 ? as_i(pf[k]) : p[k]);
+  }
+  if (d.f64 && l0 == 0) {
+    const double sw = block_sum_f64(wl);
+    if (threadIdx.x == 0 && sw != 0.0) atomicAdd((double*)&d.cs[s].gwo, sw);
+  }
+}
+
+// A refinement update whose profits are in its row: the incumbent's value
+// sum over T_h of p_h and the update's marks, as k_gains leaves them.
+constexpr int kPrepTile = 2048;
+
+__global__ void __launch_bounds__(256) k_prep(ChainSet set, DevState d) {
+  const int ci = blockIdx.y;
+  ChainState* st = d.cs + set.slot[ci];
+  const int64_t ps = set.src[ci], n = d.n;
+  const uint8_t* th = d.tgt + (ps * d.m + set.worker[ci]) * n;
+  const int64_t* p = d.profit + (int64_t)set.row[ci] * n;
+  const int64_t i0 = (int64_t)blockIdx.x * kPrepTile + threadIdx.x;
+  int64_t acc = 0;
+  double accf = 0.0;
+#pragma unroll
+  for (int k = 0; k < kPrepTile / 256; ++k) {
+    const int64_t i = i0 + k * 256;
+    if (i < n && th[i]) {
+      if (d.f64) accf += as_f(p[i]);
+      else acc += p[i];
+    }
+  }
+  if (d.f64) {
+    const double v = block_sum_f64(accf);
+    if (threadIdx.x == 0 && v != 0.0) atomicAdd((double*)&st->inc, v);
+  } else {
+    const int64_t v = block_sum(acc);
+    if (threadIdx.x == 0 && v)
+      atomicAdd((unsigned long long*)&st->inc, (unsigned long long)v);
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->skip = 0;
+    st->solved = 0;
+    if (d.f64) st->wsum = d.cs[ps].gwo;
+  }
 }
 
 // Speculative refinement, after the decisions (one block per start): the
@@ -2227,10 +2359,24 @@ hipError_t launch_take_standalone(const ChainSet& set, const DevState& d,
   return hipGetLastError();
 }
 
-hipError_t launch_commit(const ChainSet& set, const DevState& d, int mode,
+hipError_t launch_commit(const ChainSet& set, const DevState& d, int refresh,
                          hipStream_t st) {
-  hipLaunchKernelGGL(k_commit, grid1(d.n, kCommitThreads / d.m, set.count),
-                     dim3(kCommitThreads), 0, st, set, d, mode);
+  hipLaunchKernelGGL(k_commit, grid1(d.n, kCommitTile, set.count), dim3(kCommitThreads), 0, st,
+                     set, d, refresh);
+  return hipGetLastError();
+}
+
+hipError_t launch_rows(const DevState& d, int32_t s0, int32_t count, hipStream_t st) {
+  const int tiles = (d.n + 255) / 256;
+  hipLaunchKernelGGL(k_rows,
+                     dim3((unsigned)((tiles + 7) / 8 * 8 * count),
+                          (unsigned)((d.m + kRowWorkers - 1) / kRowWorkers)),
+                     dim3(256), 0, st, d, (int64_t)s0, count, tiles);
+  return hipGetLastError();
+}
+
+hipError_t launch_prep(const ChainSet& set, const DevState& d, hipStream_t st) {
+  hipLaunchKernelGGL(k_prep, grid1(d.n, kPrepTile, set.count), dim3(256), 0, st, set, d);
   return hipGetLastError();
 }
 

@@ -168,7 +168,7 @@ __global__ void __launch_bounds__(kRThreads) k_ladder(ChainSet set, DevState d, 
   // on one counter take turns.
   uint32_t* suf = cs;
   uint32_t* const sufc = suf + (lane % kCopies) * kPlane;
-  const uint32_t* __restrict__ key = d.key_lv + slot * (int64_t)nlv;
+  const uint32_t* __restrict__ key = d.key_lv + (int64_t)set.row[ci] * nlv;
   const uint16_t* __restrict__ par = d.lvpar;
   for (int q = tid; q <= levels; q += kRThreads) lst[q] = d.lvtab[q];
   for (int b = tid; b < kPlane * kCopies; b += kRThreads) suf[b] = 0;
@@ -444,7 +444,7 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
   if (st->skip) return;
   const int n = d.n, nw = (n + 31) / 32, n64 = d.nlv / 64;
   const int kp = set.kprime[ci];
-  const int64_t* __restrict__ prof = d.profit + slot * (int64_t)n;
+  const int64_t* __restrict__ prof = d.profit + (int64_t)set.row[ci] * n;
   // the active nodes, leaves first, then the deepest level: position, parent's
   // index | level << 16 (leaves: d.levels), integer profit (an entry is
   // written and read by one thread)
