@@ -315,7 +315,7 @@ constexpr int kReduceThreads = 1024;
 constexpr int kReduceActive = 15 * kReduceThreads;
 constexpr int kReduceMaxDepth = 254;
 constexpr int kLadderSlots = 65536;  // level-order slots (nodes, padded levels)
-constexpr int kReduceRedBytes = 1536;  // block-wide scratch words
+constexpr int kReduceRedBytes = 2048;  // block-wide scratch words
 constexpr int kLadderRungs = 16;       // prices k_ladder tries per chain
 size_t reduce_lds_min(int32_t n, int32_t nlv, int32_t levels, int32_t leaf0);
 size_t ladder_lds(int32_t nlv, int32_t levels, int32_t leaf0);

@@ -69,11 +69,22 @@ constexpr int kMaxSearch = 40;  // evaluations of one price search
 constexpr uint32_t kNone = 0xFFFFu;
 constexpr int kChunks = kReduceActive / kRThreads;
 
+// Bins of the entry widths: exact below 4, then four per factor of two.
+constexpr int kWidthBins = 256;
+__device__ __forceinline__ int width_bin(int64_t a) {
+  if (a < 4) return (int)a;
+  const int e = 63 - __builtin_clzll((unsigned long long)a);
+  return 4 * (e - 1) + (int)((a >> (e - 2)) & 3);
+}
+__device__ __forceinline__ int64_t width_edge(int b) {  // least value in bin b
+  return b < 4 ? b : (int64_t)(4 + (b & 3)) << (b / 4 - 1);
+}
+
 struct Red {  // block-wide scratch words in LDS
   double dsum[kRWaves];
   int64_t isum[kRWaves];
   uint32_t wsum[kRWaves];
-  uint32_t vh[64];
+  uint32_t vh[kWidthBins];
   int32_t bt;
   uint32_t core, forced;
   uint32_t used[kCoreMax / 32];  // core depths of the rows that are skipped to
@@ -547,9 +558,13 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
 
     // --------------------------------------------------- price search --
     // f(l) = |S(l)| falls with l; find a small l with f(l) <= k'.  The rungs'
-    // counts bracket it (to be confirmed); regula falsi (Illinois) with a
-    // bisection every fourth step, until the rest of the bracket can add at
-    // most 2^-9 of the price to the gap.
+    // counts bracket it (to be confirmed); regula falsi (Illinois), which is
+    // quick where f falls in small steps.  UB(l) = l k' + rootsum is convex
+    // and piecewise linear with slope k' - f(l), so where both ends are known
+    // every other price is where their tangents meet: exact where one subtree
+    // of many nodes joins at once, which a search on f alone would bisect.
+    // The tangents also show when UB can fall by at most 2^-9 of the price
+    // below the end hi: then hi will do.
     int64_t* cw = W;  // child sums by active index, then two root words
     int64_t lam = 0, rootsum = 0;
     {
@@ -558,7 +573,7 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
       int64_t lo = price_q(price[jl]), hi;
       double ylo = max(count[jl] - kp, 1), yhi = -(double)kp;
       bool vhi = false;
-      int fhi = 0;
+      int fhi = 0, flo = 0;
       if (jl > 0) {
         hi = max(price_q(price[jl - 1]), lo + 2);
         yhi = min(count[jl - 1] - kp, -1);
@@ -567,7 +582,9 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
       }
       bool zero = t == 0.0 && jl == j;  // price 0 itself may be the one
       bool last = false;
+      bool vlo = false;
       int side = 0;
+      int64_t Llo = 0, Lhi = 0;
       uint32_t parity = 0;
       for (int it = 0;; ++it) {
         int64_t l;
@@ -577,8 +594,11 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
           l = 0;
         } else if (hi - lo <= 1) {
           l = hi;
-        } else if ((it & 3) == 3) {
-          l = lo + (hi - lo) / 2;
+        } else if (vlo && vhi && (it & 1)) {
+          const int64_t w = hi - lo;
+          const double x = ceil((double)(Lhi - Llo - (int64_t)(kp - fhi) * w) /
+                                (double)(fhi - flo));
+          l = lo + min(max((int64_t)x, (int64_t)1), w - 1);
         } else {
           l = lo + (int64_t)((double)(hi - lo) * (ylo / (ylo - yhi)));
           l = min(max(l, lo + 1), hi - 1);
@@ -632,6 +652,7 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
         if (miss <= 0) {
           hi = l;
           fhi = fsize;
+          Lhi = l * kp + rootsum;
           vhi = true;
           if (zero || miss == 0) break;
           yhi = miss;
@@ -644,15 +665,26 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
             vhi = false;
           }
           lo = l;
+          flo = fsize;
+          Llo = l * kp + rootsum;
+          vlo = true;
           ylo = miss;
           if (side > 0) yhi *= 0.5;
           side = 1;
         }
         zero = false;
-        if (vhi && (hi - lo <= 1 ||
-                    (double)(kp - fhi) * (double)(hi - lo) * 512.0 <= (double)hi)) {
-          if (lam == hi) break;
-          last = true;
+        if (vhi) {
+          // how far below hi the tangents meet (the bracket, if only hi is
+          // known)
+          int64_t w = hi - lo;
+          if (vlo && w > 1)
+            w -= min((int64_t)ceil((double)(Lhi - Llo - (int64_t)(kp - fhi) * w) /
+                                   (double)(fhi - flo)),
+                     w);
+          if (hi - lo <= 1 || (double)(kp - fhi) * (double)w * 512.0 <= (double)hi) {
+            if (lam == hi) break;
+            last = true;
+          }
         }
       }
     }
@@ -685,7 +717,7 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
     // sum: > 0 in S, the least V on its ancestor path (in the core iff at
     // most the width, else forced); < 0 outside, -1 - the largest -V on the
     // path (in the core iff that is at most the width).
-    if (tid < 64) red->vh[tid] = 0;
+    if (tid < kWidthBins) red->vh[tid] = 0;
     {
       int cur = uniform(red->lev[2 * chunks - 1]);
       int64_t qa = 0;
@@ -724,26 +756,38 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
     }
     // nodes that are not active stay out while gap <= dmax
     const int64_t dmax = t == 0.0 ? INT64_MAX : max(lam - tq - 1, (int64_t)0);
-    // numbers of nodes by entry width (powers of two), up to half a price (or a
+    // numbers of nodes by entry width (four bins a factor of two), up to half a price (or a
     // few of the units the profits lose)
     const int64_t cutoff = max(lam >> 1, 4 * qerr + 1);
     for (int x = tid; x < A; x += kRThreads) {
       const int64_t e = cw[x], a = e < 0 ? -1 - e : e;
-      if (a < cutoff)
-        atomicAdd(&red->vh[a == 0 ? 0 : 64 - __builtin_clzll((unsigned long long)a)], 1u);
+      if (a < cutoff) atomicAdd(&red->vh[width_bin(a)], 1u);
     }
     __syncthreads();
-    // the largest width 2^b - 1 below the cutoff with at most `limit` nodes
+    // the largest width at a bin's end, below the cutoff, with at most `limit`
+    // nodes
     auto widest = [&](uint32_t limit) -> int64_t {
-      const int b = tid & 63;
-      uint32_t x = red->vh[b];
+      const int b = 4 * (tid & 63);
+      uint32_t c[4], x = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x += c[e] = red->vh[b + e];
+      uint32_t y = x;
       for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o, 64);
-        if (b >= o) x += y;
+        const uint32_t z = __shfl_up(y, o, 64);
+        if ((tid & 63) >= o) y += z;
       }
-      const bool ok = b < 62 && x <= limit && (b == 0 || ((int64_t)1 << b) - 1 < cutoff);
-      const uint64_t m = __ballot(ok);  // a prefix of the bins
-      return m == 0 ? 0 : ((int64_t)1 << (63 - __builtin_clzll(m))) - 1;
+      y -= x;
+      int top = -1;  // a prefix of the bins fits
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        y += c[e];
+        if (y <= limit && b + e < kWidthBins - 8 && width_edge(b + e + 1) - 1 < cutoff)
+          top = b + e;
+      }
+      const uint64_t m = __ballot(top >= 0);
+      if (m == 0) return 0;
+      const int w = __builtin_amdgcn_readlane(top, 63 - __builtin_clzll(m));
+      return width_edge(w + 1) - 1;
     };
     int64_t width = min(dmax, widest(64));
     if (lam == 0) width = 0;
@@ -769,17 +813,18 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
       // into the base
       int64_t base = 0;
       uint32_t forced_mine = 0;
+#pragma unroll 4
       for (int x = tid; x < A; x += kRThreads) {
-        const int64_t e = cw[x];
+        const int64_t e = cw[x], p = aq[x];
+        const uint32_t q = apos[x];
         const bool core = e < 0 ? -1 - e <= width : e <= width;
         if (core) {
           const uint32_t c = atomicAdd(&red->core, 1u);
-          if (c < (uint32_t)kCoreMax) cun[c] = apos[x];
+          if (c < (uint32_t)kCoreMax) cun[c] = q;
         } else if (e > 0) {
-          const uint32_t q = apos[x];
           atomicOr(sel + (q >> 5), 1u << (q & 31));
           ++forced_mine;
-          if (!F64) base += shift == 0 ? aq[x] : prof[q];
+          if (!F64) base += shift == 0 ? p : prof[q];
         }
       }
       for (int o = 32; o > 0; o >>= 1) forced_mine += __shfl_down(forced_mine, o, 64);
