@@ -890,23 +890,60 @@ struct Engine {
     return PP_OK;
   }
 
-  // The reduced solve of every chain (k_reduce); what it leaves unsolved is
-  // the sweep's.
-  int reduce(const ChainSet& set, int mode) {
-    if (!reduce_lds) return PP_OK;
+  // The reduced solve of every chain (k_reduce), with its decision.
+  int reduce(const ChainSet& set, int mode, int prep = 0) {
     PP_TRY(timer_mark(c, timer, true, st));
-    PP_HIP(launch_reduce(set, d, mode, reduce_lds, st));
+    PP_HIP(launch_reduce(set, d, mode, prep, reduce_lds, st));
     return timer_mark(c, timer, false, st);
   }
 
-  // The DP of every chain of `set` (its profits are in place) and the walk:
-  // the reduced solve, then the sweep and the walk, which pass the chains
-  // it has solved over.
-  int solve(const ChainSet& set, int mode) {
-    PP_TRY(reduce(set, mode));
-    PP_TRY(dp(set, 1));
-    PP_HIP(launch_backtrack(set, d, mode, st));
+  // The sweep, walk and decision of the chains of `set` that the reduced
+  // solve left unsolved (cs[k]: chain k's state after it); *swept: how many.
+  int sweep_rest(const ChainSet& set, const ChainState* const* cs, int mode, int* swept,
+                 ChainSet* rest_out = nullptr) {
+    ChainSet rest;
+    std::memset(&rest, 0, sizeof rest);
+    for (int32_t k = 0; k < set.count; ++k)
+      if (!cs[k]->skip && !cs[k]->solved) {
+        const int32_t q = rest.count++;
+        rest.slot[q] = set.slot[k];
+        rest.src[q] = set.src[k];
+        rest.worker[q] = set.worker[k];
+        rest.kprime[q] = set.kprime[k];
+        rest.row[q] = set.row[k];
+      }
+    *swept = rest.count;
+    if (rest.count > 0) {
+      PP_TRY(dp(rest, 1));
+      PP_HIP(launch_backtrack(rest, d, mode, st));
+    }
+    if (rest_out) *rest_out = rest;
     return PP_OK;
+  }
+
+  // The DP of every chain of `set` (its profits are in place) and the walk.
+  int solve(const ChainSet& set, int mode) {
+    if (!reduce_lds) {
+      PP_TRY(dp(set, 1));
+      PP_HIP(launch_backtrack(set, d, mode, st));
+      return PP_OK;
+    }
+    PP_TRY(reduce(set, mode));
+    int32_t lo = INT32_MAX, hi = -1;
+    for (int32_t k = 0; k < set.count; ++k) {
+      lo = std::min(lo, set.slot[k]);
+      hi = std::max(hi, set.slot[k]);
+    }
+    if (hi < lo) return PP_OK;
+    const size_t span = (size_t)(hi - lo + 1);
+    PP_TRY(ensure_cs_pin(c, span));
+    PP_HIP(hipMemcpyAsync(c->cs_pin, d.cs + lo, sizeof(ChainState) * span,
+                          hipMemcpyDeviceToHost, st));
+    PP_TRY(poll_stream(st));
+    const ChainState* cs[kMaxChains];
+    for (int32_t k = 0; k < set.count; ++k) cs[k] = c->cs_pin + (set.slot[k] - lo);
+    int swept = 0;
+    return sweep_rest(set, cs, mode, &swept);
   }
 
   // One worker update (gains, DP, accept + backtrack, commit) for every
@@ -1311,11 +1348,13 @@ int refine_starts(Engine& e, const std::vector<int32_t>& starts, int32_t spare_b
       set.kprime[k] = kp[items[k].worker];
       set.row[k] = rows ? d.row0 + items[k].q * m + items[k].worker : items[k].slot;
     }
-    if (rows) PP_HIP(launch_prep(set, d, e.st));
-    else PP_HIP(launch_gains(set, d, e.st, kGainsMarginal, 1));
-    PP_TRY(e.reduce(set, kModeRefine));
-    if (!e.reduce_lds) PP_TRY(e.dp(set, 1));
-    PP_HIP(launch_backtrack(set, d, kModeRefine, e.st, e.reduce_lds ? 1 : 0));
+    if (!rows) PP_HIP(launch_gains(set, d, e.st, kGainsMarginal, 1));
+    if (e.reduce_lds) {
+      PP_TRY(e.reduce(set, kModeRefine, rows ? 1 : 0));
+    } else {
+      PP_TRY(e.dp(set, 1));
+      PP_HIP(launch_backtrack(set, d, kModeRefine, e.st));
+    }
     if (d.f64) PP_HIP(launch_gexact(set, d, kModeRefine, e.st));
     // the launch's results, to pinned memory in one copy: the starts' slots
     // (consecutive) through the last spare slot used (the slots between
@@ -1336,21 +1375,12 @@ int refine_starts(Engine& e, const std::vector<int32_t>& starts, int32_t spare_b
     };
     PP_TRY(read_states());
     if (e.reduce_lds) {
-      // updates the reduced solve left: swept now
+      const ChainState* at[kMaxChains];
+      for (int32_t k = 0; k < set.count; ++k) at[k] = &cs[k];
+      int swept = 0;
       ChainSet rest;
-      std::memset(&rest, 0, sizeof rest);
-      for (int32_t k = 0; k < set.count; ++k)
-        if (!cs[k].skip && !cs[k].solved) {
-          const int32_t q = rest.count++;
-          rest.slot[q] = set.slot[k];
-          rest.src[q] = set.src[k];
-          rest.worker[q] = set.worker[k];
-          rest.kprime[q] = set.kprime[k];
-          rest.row[q] = set.row[k];
-        }
-      if (rest.count > 0) {
-        PP_TRY(e.dp(rest, 1));
-        PP_HIP(launch_backtrack(rest, d, kModeRefine, e.st));
+      PP_TRY(e.sweep_rest(set, at, kModeRefine, &swept, &rest));
+      if (swept > 0) {
         if (d.f64) PP_HIP(launch_gexact(rest, d, kModeRefine, e.st));
         PP_TRY(read_states());
       }

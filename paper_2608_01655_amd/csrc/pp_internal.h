@@ -182,8 +182,8 @@ struct ChainState {
   int32_t skips;           // updates resolved that way
   int64_t skipped_cells;   // their n * k' DP cells
   uint32_t dirty[8];       // one bit per worker (m <= 255)
-  // the current update's DP was solved by k_reduce: dpval and the selection
-  // are final, the sweep and the walk pass the chain over
+  // the current update's DP was solved by k_reduce: dpval, the selection and
+  // the decision are final
   int32_t solved;
   int32_t pad;
 };
@@ -316,13 +316,19 @@ constexpr int kReduceActive = 15 * kReduceThreads;
 constexpr int kReduceMaxDepth = 254;
 constexpr int kLadderSlots = 65536;  // level-order slots (nodes, padded levels)
 constexpr int kReduceRedBytes = 2048;  // block-wide scratch words
-constexpr int kLadderRungs = 16;       // prices k_ladder tries per chain
+// prices k_ladder tries per chain, with at most 16 chains and with more (and
+// one more block per chain: 256 blocks at 16 and at 32 chains)
+constexpr int kLadderRungs = 15;
+constexpr int kLadderShort = 7;
 size_t reduce_lds_min(int32_t n, int32_t nlv, int32_t levels, int32_t leaf0);
 size_t ladder_lds(int32_t nlv, int32_t levels, int32_t leaf0);
 // mode kModeRefine: updates whose upper bound cannot beat the incumbent are
-// resolved (as rejected) without a solve.  Chains it cannot solve keep
-// ChainState::solved = 0.  lds: dynamic LDS bytes per block.
-hipError_t launch_reduce(const ChainSet& set, const DevState& d, int mode, int lds,
+// resolved (as rejected) without a solve.  A solved chain is decided and
+// marked as by launch_backtrack; one it cannot solve is left undecided (not
+// accepted, ChainState::solved = 0, its sums kept) for a sweep and a walk.
+// prep: refinement with profit rows: also the incumbent's value, in place of
+// launch_gains.  lds: dynamic LDS bytes per block.
+hipError_t launch_reduce(const ChainSet& set, const DevState& d, int mode, int prep, int lds,
                          hipStream_t st);
 
 // Host-side launchers (pp_kernels.hip).  All enqueue on `st`.
@@ -380,10 +386,8 @@ hipError_t launch_mat_cost(const DevState& d, int32_t inc, int32_t prop,
 hipError_t launch_dp(const ChainSet& set, const DevState& d, uint32_t epoch,
                      uint32_t spin_limit, int store_bits, int32_t slots_lds,
                      int fmax, hipStream_t st);
-// defer: chains not solved by k_reduce are left undecided (not accepted,
-// their sums kept) for a sweep and a second call
 hipError_t launch_backtrack(const ChainSet& set, const DevState& d, int mode,
-                            hipStream_t st, int defer = 0);
+                            hipStream_t st);
 // Speculative refinement: the updates of consecutive positions of one
 // start run together in spare slots; per start, the first accepted one (in
 // spare slot `from`, or none: from = -1) is adopted into the start's slot,
@@ -397,10 +401,8 @@ hipError_t launch_take_standalone(const ChainSet& set, const DevState& d,
 // refresh: also the profit rows of the chains' starts at changed chunks
 hipError_t launch_commit(const ChainSet& set, const DevState& d, int refresh,
                          hipStream_t st);
-// profit rows of the `count` starts in slots s0 ...; a refinement update's
-// incumbent value and marks from its row (in place of launch_gains)
+// profit rows of the `count` starts in slots s0 ...
 hipError_t launch_rows(const DevState& d, int32_t s0, int32_t count, hipStream_t st);
-hipError_t launch_prep(const ChainSet& set, const DevState& d, hipStream_t st);
 hipError_t launch_objective(const ChainSet& set, const DevState& d,
                             hipStream_t st);
 

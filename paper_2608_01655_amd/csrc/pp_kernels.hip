@@ -711,8 +711,7 @@ k_dp(ChainSet set, DevState d, uint32_t epoch, uint32_t spin_limit,
   int ci = 0;
   while (ci + 1 < set.count && set.base[ci + 1] <= blk) ++ci;
   const int64_t slot = set.slot[ci];
-  // the update is resolved without a sweep, or solved by k_reduce
-  if (d.cs[slot].skip || d.cs[slot].solved) return;
+  if (d.cs[slot].skip) return;  // the update is resolved without a sweep
   const int kp = set.kprime[ci];
   const int g = blk - set.base[ci];
   const int G = set.base[ci + 1] - set.base[ci];
@@ -1367,7 +1366,7 @@ __device__ __forceinline__ void walk_sw_c1(uint32_t& q, uint32_t& rem, uint32_t&
 // written as a bitmap when the walk leaves the super-window.
 template <int C>
 __global__ void __launch_bounds__(64) k_backtrack(ChainSet set, DevState d,
-                                                  int mode, int defer) {
+                                                  int mode) {
   constexpr int kWin = kDpBatch;        // rows per choice word
   constexpr int kSwWin = 16;            // windows per super-window
   constexpr int kSw = kWin * kSwWin;    // rows per super-window
@@ -1389,14 +1388,6 @@ __global__ void __launch_bounds__(64) k_backtrack(ChainSet set, DevState d,
     if (lane == 0) {
       st->accept = 0;
       st->inc = 0;
-    }
-    return;
-  }
-  const bool solved = st->solved != 0;
-  if (defer && !solved) {
-    if (lane == 0) {
-      st->accept = 0;
-      st->rejected = 1;
     }
     return;
   }
@@ -1427,7 +1418,7 @@ __global__ void __launch_bounds__(64) k_backtrack(ChainSet set, DevState d,
       st->wsum = 0;
       st->rejected = early ? 1 : 0;
     }
-    if (early || solved) return;
+    if (early) return;
     const int nwords = d.npad / 32;
     uint32_t* selw = d.sel + slot * nwords;
     for (int q = lane; q < nwords; q += kWave) selw[q] = 0;
@@ -1452,7 +1443,6 @@ __global__ void __launch_bounds__(64) k_backtrack(ChainSet set, DevState d,
 #pragma unroll
       for (int q = 0; q < 8; ++q) st->dirty[q] |= q == (h >> 5) ? ~(1u << (h & 31)) : ~0u;
     }
-    if (solved) return;
     for (int q = lane; q < nwords; q += kWave) selw[q] = 0;
     if (kp <= 0) return;
   }
@@ -1777,42 +1767,6 @@ __global__ void __launch_bounds__(256) k_rows(DevState d, int64_t s0, int count,
   if (d.f64 && l0 == 0) {
     const double sw = block_sum_f64(wl);
     if (threadIdx.x == 0 && sw != 0.0) atomicAdd((double*)&d.cs[s].gwo, sw);
-  }
-}
-
-// A refinement update whose profits are in its row: the incumbent's value
-// sum over T_h of p_h and the update's marks, as k_gains leaves them.
-constexpr int kPrepTile = 2048;
-
-__global__ void __launch_bounds__(256) k_prep(ChainSet set, DevState d) {
-  const int ci = blockIdx.y;
-  ChainState* st = d.cs + set.slot[ci];
-  const int64_t ps = set.src[ci], n = d.n;
-  const uint8_t* th = d.tgt + (ps * d.m + set.worker[ci]) * n;
-  const int64_t* p = d.profit + (int64_t)set.row[ci] * n;
-  const int64_t i0 = (int64_t)blockIdx.x * kPrepTile + threadIdx.x;
-  int64_t acc = 0;
-  double accf = 0.0;
-#pragma unroll
-  for (int k = 0; k < kPrepTile / 256; ++k) {
-    const int64_t i = i0 + k * 256;
-    if (i < n && th[i]) {
-      if (d.f64) accf += as_f(p[i]);
-      else acc += p[i];
-    }
-  }
-  if (d.f64) {
-    const double v = block_sum_f64(accf);
-    if (threadIdx.x == 0 && v != 0.0) atomicAdd((double*)&st->inc, v);
-  } else {
-    const int64_t v = block_sum(acc);
-    if (threadIdx.x == 0 && v)
-      atomicAdd((unsigned long long*)&st->inc, (unsigned long long)v);
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    st->skip = 0;
-    st->solved = 0;
-    if (d.f64) st->wsum = d.cs[ps].gwo;
   }
 }
 
@@ -2336,11 +2290,11 @@ int dp_resident_blocks_query(int cells, int32_t slots_lds, int device) {
 }  // namespace
 
 hipError_t launch_backtrack(const ChainSet& set, const DevState& d, int mode,
-                            hipStream_t st, int defer) {
+                            hipStream_t st) {
   switch (d.cells) {
-    case 1: hipLaunchKernelGGL(k_backtrack<1>, dim3(set.count), dim3(kWave), 0, st, set, d, mode, defer); break;
-    case 2: hipLaunchKernelGGL(k_backtrack<2>, dim3(set.count), dim3(kWave), 0, st, set, d, mode, defer); break;
-    case 4: hipLaunchKernelGGL(k_backtrack<4>, dim3(set.count), dim3(kWave), 0, st, set, d, mode, defer); break;
+    case 1: hipLaunchKernelGGL(k_backtrack<1>, dim3(set.count), dim3(kWave), 0, st, set, d, mode); break;
+    case 2: hipLaunchKernelGGL(k_backtrack<2>, dim3(set.count), dim3(kWave), 0, st, set, d, mode); break;
+    case 4: hipLaunchKernelGGL(k_backtrack<4>, dim3(set.count), dim3(kWave), 0, st, set, d, mode); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -2372,11 +2326,6 @@ hipError_t launch_rows(const DevState& d, int32_t s0, int32_t count, hipStream_t
                      dim3((unsigned)((tiles + 7) / 8 * 8 * count),
                           (unsigned)((d.m + kRowWorkers - 1) / kRowWorkers)),
                      dim3(256), 0, st, d, (int64_t)s0, count, tiles);
-  return hipGetLastError();
-}
-
-hipError_t launch_prep(const ChainSet& set, const DevState& d, hipStream_t st) {
-  hipLaunchKernelGGL(k_prep, grid1(d.n, kPrepTile, set.count), dim3(256), 0, st, set, d);
   return hipGetLastError();
 }
 

@@ -145,12 +145,12 @@ __device__ int64_t block_total(int64_t v, int64_t* part) {
 // Launches of more than 16 chains take half as many steps, so that the blocks
 // fit the chip at once.  The last ones are for gaps that are a large part of a
 // price (small k').
-__device__ constexpr int kRank16[kLadderRungs] = {4,  10, 12, 14, 16, 18, 20,  23,
-                                                  26, 30, 35, 41, 50, 64, 100, 400};
-__device__ constexpr int kRank8[kLadderRungs / 2] = {8, 13, 17, 22, 30, 42, 64, 150};
+__device__ constexpr int kRankLong[kLadderRungs] = {4,  11, 13, 15, 17, 19,  22, 25,
+                                                    29, 34, 41, 50, 64, 100, 400};
+__device__ constexpr int kRankShort[kLadderShort] = {9, 14, 18, 24, 34, 56, 150};
 
 __device__ __forceinline__ int rung_rank16(int rung, int rungs) {
-  return rungs == kLadderRungs ? kRank16[rung] : kRank8[rung];
+  return rungs == kLadderRungs ? kRankLong[rung] : kRankShort[rung];
 }
 
 // S_t for a ladder of prices t, one block per (chain, rung).  Profits come as
@@ -159,14 +159,49 @@ __device__ __forceinline__ int rung_rank16(int rung, int rungs) {
 // S_t: values are clipped at a height that leaves every ancestor positive
 // (the clip exceeds one price per level).  Integer sums: the same bits
 // whatever the order of the atomics.
+// With `prep` set, one more block per chain sums the incumbent's value
+// sum over T_h of p_h of a refinement update (what k_gains leaves in inc;
+// real-valued costs: also the scale wsum, from the start's gwo).
 template <bool F64>
-__global__ void __launch_bounds__(kRThreads) k_ladder(ChainSet set, DevState d, int rungs) {
+__global__ void __launch_bounds__(kRThreads) k_ladder(ChainSet set, DevState d, int rungs,
+                                                      int prep) {
   extern __shared__ int64_t lds[];
   const int tid = threadIdx.x, lane = tid & 63;
+  if (prep && (int)blockIdx.x >= set.count * rungs) {
+    const int ci = blockIdx.x - set.count * rungs;
+    ChainState* st = d.cs + set.slot[ci];
+    const int64_t ps = set.src[ci], n = d.n;
+    const uint8_t* th = d.tgt + (ps * d.m + set.worker[ci]) * n;
+    const int64_t* p = d.profit + (int64_t)set.row[ci] * n;
+    Red* red = (Red*)lds;
+    int64_t acc = 0;
+    double accf = 0.0;
+#pragma unroll 8
+    for (int64_t i = tid; i < n; i += kRThreads)
+      if (th[i]) {
+        if (F64) accf += __builtin_bit_cast(double, p[i]);
+        else acc += p[i];
+      }
+    if (F64) {
+      for (int o = 32; o > 0; o >>= 1) accf += __shfl_down(accf, o, 64);
+      if (lane == 0) red->dsum[tid >> 6] = accf;
+      __syncthreads();
+      if (tid == 0) {
+        double v = 0.0;
+        for (int k = 0; k < kRWaves; ++k) v += red->dsum[k];
+        st->inc = __builtin_bit_cast(int64_t, v);
+        st->wsum = d.cs[ps].gwo;
+      }
+    } else {
+      acc = block_total(acc, red->isum);
+      if (tid == 0) st->inc = acc;
+    }
+    return;
+  }
   const int wv = uniform(tid >> 6);
   const int ci = blockIdx.x / rungs, rung = blockIdx.x % rungs;
   const int64_t slot = set.slot[ci];
-  if (d.cs[slot].skip) return;
+  if (!prep && d.cs[slot].skip) return;
   const int kp = set.kprime[ci];
   const int levels = d.levels, nlv = d.nlv, leaf0 = d.leaf0;
   const int nlw = nlv / 32, n64 = nlv / 64;
@@ -444,6 +479,30 @@ __device__ void core_walk(int core, const uint64_t* ch, const uint16_t* cnx,
   }
 }
 
+// A solved update: its value, and the decision and marks k_backtrack makes
+// after a sweep (real-valued costs: the early rejection; the decision itself
+// is k_gexact_final's).
+template <bool F64>
+__device__ void finish_update(ChainState* st, const DevState& d, int h, int kp, int mode,
+                              int64_t dpval) {
+  st->dpval = dpval;
+  st->solved = 1;
+  st->dirty[h >> 5] &= ~(1u << (h & 31));
+  if (F64) {
+    st->rejected = mode == kModeRefine &&
+                           early_reject_f64(as_d(dpval), as_d(st->inc), as_d(st->wsum), d.m, kp,
+                                            d.n, d.eps)
+                       ? 1
+                       : 0;
+    st->wsum = 0;
+  } else if (mode == kModeGreedy || dpval > st->inc) {
+    st->accept = 1;
+    if (mode == kModeRefine) st->accepts += 1;
+    for (int q = 0; q < 8; ++q) st->dirty[q] |= q == (h >> 5) ? ~(1u << (h & 31)) : ~0u;
+  }
+  st->inc = 0;
+}
+
 template <bool F64>
 __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, int mode,
                                                       int lds_bytes, int rungs) {
@@ -452,7 +511,16 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
   const int ci = blockIdx.x;
   const int64_t slot = set.slot[ci];
   ChainState* st = d.cs + slot;
-  if (st->skip) return;
+  if (st->skip) {
+    if (tid == 0) {
+      st->accept = 0;
+      st->inc = 0;
+    }
+    return;
+  }
+  const int h = set.worker[ci];
+  // (read ahead of the first barrier: finish_update clears them)
+  const int64_t inc = st->inc, wsum = st->wsum;
   const int n = d.n, nw = (n + 31) / 32, n64 = d.nlv / 64;
   const int kp = set.kprime[ci];
   const int64_t* __restrict__ prof = d.profit + (int64_t)set.row[ci] * n;
@@ -469,7 +537,11 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
   const int wbytes = lds_bytes - (int)((char*)W - (char*)lds);
   const int acap = min(kReduceActive, wbytes / 8 - 4);
 
-  if (tid == 0) st->solved = 0;
+  if (tid == 0) {  // undecided, until solved here or swept
+    st->solved = 0;
+    st->accept = 0;
+    st->rejected = 1;
+  }
   if (kp <= 0) return;
   double* price = red->price;
   int32_t* count = red->count;
@@ -491,10 +563,7 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
     if (A > acap || (A < need && t > 0.0)) return;
     if (A == 0) {  // price 0, no profit: nothing is strictly better than skipping
       for (int w = tid; w < nwords; w += kRThreads) selw[w] = 0;
-      if (tid == 0) {
-        st->dpval = 0;
-        st->solved = 1;
-      }
+      if (tid == 0) finish_update<F64>(st, d, h, kp, mode, 0);
       return;
     }
     const int chunks = (A + kRThreads - 1) / kRThreads;
@@ -691,23 +760,20 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
     const int64_t ub = lam * kp + rootsum + qerr;
     if (mode == kModeRefine) {
       // no set can be worth more than the incumbent: rejected as it stands
-      // (real-valued: only if it also passes k_backtrack's early test, with
-      // the upper bound in place of the value)
+      // (real-valued: only if the early test holds with the upper bound in
+      // place of the value)
       bool reject;
       int64_t bound;
       if (!F64) {
         bound = ub <= (INT64_MAX >> shift) ? ub << shift : INT64_MAX;
-        reject = bound <= st->inc;
+        reject = bound <= inc;
       } else {
         const double v = ldexp((double)ub, -scale) * (1.0 + (kp + 8.0) * 0x1p-52);
         bound = as_l(v);
-        reject = early_reject_f64(v, as_d(st->inc), as_d(st->wsum), d.m, kp, n, d.eps);
+        reject = early_reject_f64(v, as_d(inc), as_d(wsum), d.m, kp, n, d.eps);
       }
       if (reject) {
-        if (tid == 0) {
-          st->dpval = bound;
-          st->solved = 1;
-        }
+        if (tid == 0) finish_update<F64>(st, d, h, kp, mode, bound);
         return;
       }
     }
@@ -960,10 +1026,7 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
         }
         __syncthreads();
         for (int w = tid; w < nwords; w += kRThreads) selw[w] = w < nw ? sel[w] : 0u;
-        if (tid == 0) {
-          st->dpval = value;
-          st->solved = 1;
-        }
+        if (tid == 0) finish_update<F64>(st, d, h, kp, mode, value);
         return;
       }
       // wider: the gap itself, except that a first core's gap may only show
@@ -998,7 +1061,7 @@ size_t reduce_lds_min(int32_t n, int32_t nlv, int32_t levels, int32_t leaf0) {
   return std::max(solve, ladder_lds(nlv, levels, leaf0));
 }
 
-hipError_t launch_reduce(const ChainSet& set, const DevState& d, int mode, int lds,
+hipError_t launch_reduce(const ChainSet& set, const DevState& d, int mode, int prep, int lds,
                          hipStream_t st) {
   static_assert(sizeof(Red) <= kReduceRedBytes, "scratch words");
   static_assert(kLadderSlots <= 64 * kRThreads, "one thread per 64 slots");
@@ -1008,14 +1071,14 @@ hipError_t launch_reduce(const ChainSet& set, const DevState& d, int mode, int l
       reduce_lds_min(d.n, d.nlv, d.levels, d.leaf0) > (size_t)lds)
     return hipErrorInvalidValue;
   const size_t lad = ladder_lds(d.nlv, d.levels, d.leaf0);
-  const int rungs = set.count <= 16 ? kLadderRungs : kLadderRungs / 2;
-  const dim3 grid((unsigned)(set.count * rungs));
+  const int rungs = set.count <= 16 ? kLadderRungs : kLadderShort;
+  const dim3 grid((unsigned)(set.count * (rungs + (prep ? 1 : 0))));
   if (d.f64) {
-    hipLaunchKernelGGL(k_ladder<true>, grid, dim3(kRThreads), lad, st, set, d, rungs);
+    hipLaunchKernelGGL(k_ladder<true>, grid, dim3(kRThreads), lad, st, set, d, rungs, prep);
     hipLaunchKernelGGL(k_reduce<true>, dim3(set.count), dim3(kRThreads), lds, st, set, d, mode,
                        lds, rungs);
   } else {
-    hipLaunchKernelGGL(k_ladder<false>, grid, dim3(kRThreads), lad, st, set, d, rungs);
+    hipLaunchKernelGGL(k_ladder<false>, grid, dim3(kRThreads), lad, st, set, d, rungs, prep);
     hipLaunchKernelGGL(k_reduce<false>, dim3(set.count), dim3(kRThreads), lds, st, set, d, mode,
                        lds, rungs);
   }
