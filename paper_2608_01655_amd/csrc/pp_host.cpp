@@ -105,7 +105,7 @@ struct TreeLayout {
   std::vector<int32_t> lvslot, lvtab;
   std::vector<uint32_t> lvpos;
   std::vector<uint16_t> lvpar;
-  int32_t lv_bits = 0, lv_clip = 0;
+  int32_t lv_bits = 0, lv_clip = 0, max_depth = 0;
   // the backtrack's skip chains inside 32-row windows [32w, 32w + 32), as
   // ce[4q] = chain mask, ce[4q + 1] = exit row, ce[4q + 2] = the exit row's
   // own chain mask, ce[4q + 3] = 0: the mask has bit r set for every row
@@ -137,7 +137,14 @@ int layout_sweep_spilled(TreeLayout& t, int32_t pad, int32_t nsteps);
 void layout_levels(TreeLayout& t, const int32_t* parent, const std::vector<int32_t>& posof,
                    const std::vector<int32_t>& head);
 
-int build_tree(int32_t n, const int32_t* parent, TreeLayout& t) {
+int layout_sweep_tables(TreeLayout& t);
+
+// kmax >= 0: a call whose updates the reduced solve may settle, with
+// capacities up to kmax: the sweep's tables are left for when one needs it
+// (layout_sweep_tables), on trees where neither they nor the sweep's launch
+// can be refused -- at most 64 levels, so at most 64 + 16 LDS rows, three
+// stage blocks per compute unit and 64 columns each.
+int build_tree(int32_t n, const int32_t* parent, TreeLayout& t, int32_t kmax = -1) {
   for (int32_t v = 0; v < n; ++v) {
     const int32_t p = parent[v];
     if (p < -1 || p >= n || p == v)
@@ -180,6 +187,14 @@ int build_tree(int32_t n, const int32_t* parent, TreeLayout& t) {
     if (t.order[q] != q) t.identity = false;
   }
   layout_levels(t, parent, posof, head);
+  if (kmax >= 0 && kmax <= 32768 && !t.lvtab.empty() && t.max_depth <= 64) return PP_OK;
+  return layout_sweep_tables(t);
+}
+
+// The backtrack's skip chains and the sweep's step schedule.
+int layout_sweep_tables(TreeLayout& t) {
+  if (!t.ce.empty()) return PP_OK;
+  const int32_t n = t.n;
   const size_t ce_rows = ((size_t)n + kCeBlock - 1) / kCeBlock * kCeBlock + kCeBlock;
   t.ce.assign(4 * ce_rows, 0);
   for (size_t q = n; q < ce_rows; ++q) t.ce[4 * q + 1] = kCeEnd;
@@ -219,6 +234,7 @@ void layout_levels(TreeLayout& t, const int32_t* parent, const std::vector<int32
     maxd = std::max(maxd, dep);
     maxdeg = std::max<int64_t>(maxdeg, head[v + 1] - head[v]);
   }
+  t.max_depth = maxd;
   const int64_t clip = ((int64_t)1 << 31) / (maxdeg + 2) - 4;
   int bits = 0;
   while (bits < 20 && ((int64_t)(maxd + 4) << (bits + 1)) < clip) ++bits;
@@ -616,16 +632,16 @@ struct pp_ctx {
   // problem, preorder layout
   DevBuf lam, w, f, meta;
   // tree tables in one allocation (one upload): next positions, preorder
-  // (position -> caller id), the backtrack's skip-chain table and, in
-  // `lvl`, the reduced solve's level order
+  // (position -> caller id); the backtrack's skip-chain table in `ce`, the
+  // reduced solve's level order in `lvl`
   DevBuf tree;
   int32_t* nextpos = nullptr;
   int32_t* order = nullptr;
-  uint32_t* ce = nullptr;
   // uploads for host-pointer entry points (caller order)
   DevBuf up_lam, up_w, up_f, up_u8;
   // per-slot state
   DevBuf tgt, v1, v2, h1, profit, sel, bits, ring, cs;
+  DevBuf ce;
   DevBuf lvl, key_lv, lad_bits, lad_pre, lad_stat, lad_list;  // the reduced solve
   DevBuf sel0;  // standalone selections, [m][npad/32] (greedy position 0)
   DevBuf partial, flag, gx, gxp;
@@ -658,7 +674,7 @@ struct pp_ctx {
     for (DevBuf* b : {&lam, &w, &f, &tree, &meta, &up_lam, &up_w,
                       &up_f, &up_u8, &tgt, &v1, &v2, &h1, &profit, &sel, &sel0, &bits,
                       &ring, &cs, &partial, &flag, &gx, &gxp, &sp_lists, &spill,
-                      &lvl, &key_lv, &lad_bits, &lad_pre, &lad_stat, &lad_list})
+                      &ce, &lvl, &key_lv, &lad_bits, &lad_pre, &lad_stat, &lad_list})
       b->release();
     for (hipEvent_t e : events) (void)hipEventDestroy(e);
     if (own) (void)hipStreamDestroy(own);
@@ -737,21 +753,15 @@ int poll_stream(hipStream_t st) {
 
 int npad_of(int32_t n) { return (n + 63) / 64 * 64; }
 
-// Allocate per-slot buffers for `slots` chains of up to `kmax` cells.
-int ensure_slots(pp_ctx* c, DevState& d, int32_t slots, int32_t kmax,
-                 int cells, int64_t rows = 0) {
+// Allocate per-slot buffers for `slots` chains (and `rows` more profit rows).
+int ensure_slots(pp_ctx* c, DevState& d, int32_t slots, int64_t rows = 0) {
   const size_t n = (size_t)d.n, m = (size_t)d.m, npad = (size_t)d.npad;
-  const int32_t stages = std::max(1, (kmax + 64 * cells - 1) / (64 * cells));
   PP_TRY(c->tgt.ensure(slots * m * n));
   PP_TRY(c->v1.ensure(slots * m * n * 8));
   PP_TRY(c->v2.ensure(slots * m * n * 8));
   PP_TRY(c->h1.ensure(slots * m * n));
   PP_TRY(c->profit.ensure((slots + rows) * n * 8));
   PP_TRY(c->sel.ensure(slots * (npad / 8)));
-  PP_TRY(c->bits.ensure((size_t)slots * stages * cells * npad * 8));
-  // ring words carry a launch tag; fresh memory is zeroed so that no stale
-  // word can ever carry a live tag (tags start at 1)
-  PP_TRY(c->ring.ensure((size_t)slots * stages * npad * 16, true));
   PP_TRY(c->cs.ensure(slots * sizeof(ChainState)));
   d.tgt = c->tgt.as<uint8_t>();
   d.v1 = c->v1.as<int64_t>();
@@ -759,12 +769,32 @@ int ensure_slots(pp_ctx* c, DevState& d, int32_t slots, int32_t kmax,
   d.h1 = c->h1.as<uint8_t>();
   d.profit = c->profit.as<int64_t>();
   d.sel = c->sel.as<uint32_t>();
+  d.cs = c->cs.as<ChainState>();
+  return PP_OK;
+}
+
+int upload_meta(pp_ctx* c, const TreeLayout& t, int cells, hipStream_t st);
+
+// The sweep's tables and buffers for `slots` chains of up to `kmax` cells at
+// `cells` cells per lane.
+int ensure_sweep(pp_ctx* c, const TreeLayout& t, DevState& d, int32_t slots, int32_t kmax,
+                 int cells, hipStream_t st) {
+  const size_t npad = (size_t)d.npad;
+  const int32_t stages = std::max(1, (kmax + 64 * cells - 1) / (64 * cells));
+  PP_TRY(c->bits.ensure((size_t)slots * stages * cells * npad * 8));
+  // ring words carry a launch tag; fresh memory is zeroed so that no stale
+  // word can ever carry a live tag (tags start at 1)
+  PP_TRY(c->ring.ensure((size_t)slots * stages * npad * 16, true));
   d.bits = c->bits.as<uint64_t>();
   d.ring = c->ring.as<uint64_t>();
-  d.cs = c->cs.as<ChainState>();
   d.stages = stages;
   d.cells = cells;
-  return PP_OK;
+  PP_TRY(c->ce.ensure(t.ce.size() * 4));
+  PP_TRY(stage_h2d(c, c->ce.p, t.ce.data(), t.ce.size() * 4, st));
+  d.ce = c->ce.as<uint32_t>();
+  PP_TRY(upload_meta(c, t, cells, st));
+  d.meta = c->meta.as<uint32_t>();  // upload_meta may have (re)allocated it
+  return upload_spills(c, t, d, slots, st);
 }
 
 // Real-valued costs: exact objective values per slot and the per-block
@@ -832,20 +862,48 @@ int timer_mark(pp_ctx* c, Timer& t, bool start, hipStream_t st) {
   return PP_OK;
 }
 
+int choose_cells(int32_t total_stage_cells_c1, int dev, int32_t slots_lds);
+
 struct Engine {
   pp_ctx* c;
   DevState d;
-  int32_t slots_lds;
-  int resident;       // DP blocks resident at once
+  TreeLayout* tree = nullptr;
+  int32_t sweep_slots = 0;  // chain slots, widest capacity and, at one cell
+  int32_t kmax = 0;         // per lane, stages of the widest launch
+  int32_t stage64 = 0;
+  int attempt = 0;
+  int32_t slots_lds = 0;
+  int resident = 0;   // DP blocks resident at once (0: no sweep set up)
   uint32_t spin_limit;
   int fmax = 0;  // every DP value < 2^62: max via v_max_f64
   int reduce_lds = 0;  // LDS of a reduced solve's block, 0: sweep every update
   hipStream_t st;
   Timer timer;
 
+  // The sweep's tables, widths and buffers, set up when a chain needs it.
+  int set_up_sweep() {
+    if (resident > 0) return PP_OK;
+    PP_TRY(layout_sweep_tables(*tree));
+    slots_lds = tree->slots;
+    const int cells = choose_cells(stage64, c->device, slots_lds);
+    int r = dp_resident_blocks(cells, slots_lds, c->device);
+    if (attempt > 0 && r > 0) {
+      // fewer stage blocks per launch, but every chain's stages in one
+      const int32_t chain = (kmax + 64 * cells - 1) / (64 * cells);
+      r = std::max(chain, r >> attempt);
+    }
+    if (r <= 0)
+      return fail(PP_E_UNSUPPORTED, "DP sweep cannot be resident (LDS stack of " +
+                                        std::to_string(slots_lds) + " rows)");
+    PP_TRY(ensure_sweep(c, *tree, d, sweep_slots, kmax, cells, st));
+    resident = r;
+    return PP_OK;
+  }
+
   // One DP sweep over the chains of `set` (kprime >= 1 each), split into
   // launches whose stages all fit on the device at once.
   int dp(const ChainSet& in, int store_bits) {
+    PP_TRY(set_up_sweep());
     if (!d.meta || !d.profit || !d.bits || !d.ring || !d.cs)
       return fail(PP_E_DEVICE, "internal: DP sweep buffers are not set");
     const int cellsw = 64 * d.cells;
@@ -1290,7 +1348,7 @@ int refine_starts(Engine& e, const std::vector<int32_t>& starts, int32_t spare_b
     // speculative updates: at most `budget` updates in all (one spare slot
     // each; budget - 1 spare slots exist) and, beyond the starts' own
     // updates, at most `block_budget` DP stage blocks in the launch
-    const int32_t cellsw = 64 * d.cells;
+    const int32_t cellsw = 64 * std::max(d.cells, 1);
     auto blocks_of = [&](int32_t h) { return (kp[h] + cellsw - 1) / cellsw; };
     int32_t blocks = 0;
     for (const Item& it : items) blocks += blocks_of(it.worker);
@@ -1451,13 +1509,13 @@ int refine_starts(Engine& e, const std::vector<int32_t>& starts, int32_t spare_b
   }
 }
 
-int run_plan_once(pp_ctx* c, const TreeLayout& t, int32_t m, const int32_t* cap,
+int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
                   const pp_options& o, bool fmax_ok, hipStream_t st, PlanResult& res,
                   int32_t extra_slots, bool f64, double eps, int attempt);
 
 // Algorithm 1 on the context's inputs, run again (identical results: the
 // plan is deterministic) if a DP sweep stalled.
-int run_plan(pp_ctx* c, const TreeLayout& t, int32_t m, const int32_t* cap,
+int run_plan(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
              const pp_options& o, bool fmax_ok, hipStream_t st,
              PlanResult& res, int32_t extra_slots = 0, bool f64 = false,
              double eps = 0.0) {
@@ -1486,7 +1544,7 @@ uint32_t spin_limit_for(int attempt) {
 // Algorithm 1 on device-resident, preorder-laid-out inputs in `c`.
 // Real-valued costs (f64): every value is the bit pattern of a non-negative
 // double, so the comparisons below (orders, best start) hold unchanged.
-int run_plan_once(pp_ctx* c, const TreeLayout& t, int32_t m, const int32_t* cap,
+int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
                   const pp_options& o, bool fmax_ok, hipStream_t st, PlanResult& res,
                   int32_t extra_slots, bool f64, double eps, int attempt) {
   const int32_t n = t.n;
@@ -1515,6 +1573,8 @@ int run_plan_once(pp_ctx* c, const TreeLayout& t, int32_t m, const int32_t* cap,
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) ==
             hipSuccess && cus > 0)
       spec_blocks = 3 * cus;
+    // (reduced solves have no stages: as many updates as a launch holds)
+    if (reduce_lds_for(t, c->device)) spec_blocks = INT32_MAX;
     spec_blocks = env_int("PP_SPEC_BLOCKS", spec_blocks);
   }
   // speculative refinement: up to kSpecChains updates per launch (each
@@ -1525,7 +1585,8 @@ int run_plan_once(pp_ctx* c, const TreeLayout& t, int32_t m, const int32_t* cap,
   // same time with more chains
   const int32_t wide_stages = std::max(1, (kmax + 63) / 64);
   const int32_t spec_default =
-      2 * kSpecChains * wide_stages <= spec_blocks ? 2 * kSpecChains : kSpecChains;
+      spec_blocks < INT32_MAX && 2 * kSpecChains * wide_stages <= spec_blocks ? 2 * kSpecChains
+                                                                              : kSpecChains;
   const int32_t spec_chains =  // updates per refinement launch
       env_int("PP_NO_SPEC", 0) ? 1
                                : std::max(1, std::min(kMaxChains, env_int("PP_SPEC_CHAINS",
@@ -1536,7 +1597,10 @@ int run_plan_once(pp_ctx* c, const TreeLayout& t, int32_t m, const int32_t* cap,
   Engine e;
   e.c = c;
   e.st = st;
-  e.slots_lds = t.slots;
+  e.tree = &t;
+  e.kmax = kmax;
+  e.attempt = attempt;
+  e.sweep_slots = slots;
   e.spin_limit = spin_limit_for(attempt);
   e.timer.on = (o.flags & PP_F_TIME_KERNELS) != 0;
   DevState& d = e.d;
@@ -1548,7 +1612,6 @@ int run_plan_once(pp_ctx* c, const TreeLayout& t, int32_t m, const int32_t* cap,
   d.w = c->w.as<int64_t>();
   d.f = c->f.as<int64_t>();
   d.nextpos = c->nextpos;
-  d.ce = c->ce;
   // widest single launch: every start's update at once
   int64_t stage64 = 0;
   {
@@ -1557,43 +1620,31 @@ int run_plan_once(pp_ctx* c, const TreeLayout& t, int32_t m, const int32_t* cap,
     for (int32_t k = 0; k < std::min<int32_t>(S, kMaxChains); ++k)
       stage64 += (ks[k % m] + 63) / 64;
   }
-  const int cells = choose_cells((int32_t)std::min<int64_t>(stage64, INT32_MAX),
-                                 c->device, e.slots_lds);
+  e.stage64 = (int32_t)std::min<int64_t>(stage64, INT32_MAX);
   {
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) ==
             hipSuccess && cus > 0)
       d.role_max_blocks = 4 * cus;
   }
-  e.resident = dp_resident_blocks(cells, e.slots_lds, c->device);
-  if (attempt > 0 && e.resident > 0) {
-    // fewer stage blocks per launch, but every chain's stages in one
-    const int32_t chain = (kmax + 64 * cells - 1) / (64 * cells);
-    e.resident = std::max(chain, e.resident >> attempt);
-  }
-  if (e.resident <= 0)
-    return fail(PP_E_UNSUPPORTED, "DP sweep cannot be resident (LDS stack of " +
-                                      std::to_string(e.slots_lds) + " rows)");
   e.fmax = fmax_ok && env_int("PP_DP_NO_FMAX", 0) == 0;
   e.reduce_lds = reduce_lds_for(t, c->device);
-  res.lane_cells = cells;
   res.fmax = (e.fmax || f64) ? 1 : 0;
   // profit rows of every (start, worker) of a refinement batch, unless they
   // take more than kRowBytes or nothing is refined
   int64_t rows = (int64_t)std::min(S, kMaxChains) * m;
   if (!e.reduce_lds || (o.flags & PP_F_NO_REFINE) || rows * n * 12 > kRowBytes || slots < 1)
     rows = 0;
-  PP_TRY(ensure_slots(c, d, slots, kmax, cells, rows));
+  PP_TRY(ensure_slots(c, d, slots, rows));
   d.row0 = rows > 0 ? slots : 0;
   if (f64) {
     d.f64 = 1;
     d.eps = eps;
     PP_TRY(ensure_exact(c, d, slots));
   }
-  PP_TRY(upload_meta(c, t, cells, st));
-  d.meta = c->meta.as<uint32_t>();  // upload_meta may have (re)allocated it
-  PP_TRY(upload_spills(c, t, d, slots, st));
   if (e.reduce_lds) PP_TRY(ensure_reduce(c, t, d, slots, st, rows));
+  // trees whose tables are laid out already (see build_tree)
+  if (!e.reduce_lds || !t.ce.empty()) PP_TRY(e.set_up_sweep());
 
   // --- standalone scores: each worker against the empty placement
   res.standalone.assign(m, 0);
@@ -1678,7 +1729,7 @@ int run_plan_once(pp_ctx* c, const TreeLayout& t, int32_t m, const int32_t* cap,
       PP_TRY(e.update(position_set(active, a), kModeGreedy));
     if (!(o.flags & PP_F_NO_REFINE))
       PP_TRY(refine_starts(e, active, spare_base, spec_chains,
-                           std::min(spec_blocks, e.resident), m, kp,
+                           e.reduce_lds ? spec_blocks : std::min(spec_blocks, e.resident), m, kp,
                            o.max_rounds, res));
     std::vector<int32_t> sl, wk, kk;
     for (int32_t s = lo; s < hi; ++s) {
@@ -1699,6 +1750,7 @@ int run_plan_once(pp_ctx* c, const TreeLayout& t, int32_t m, const int32_t* cap,
       res.skipped_cells += fin[s - lo].skipped_cells;
     }
   }
+  res.lane_cells = d.cells;
   res.best = 0;
   if (f64) {
     // real-valued costs: starts compare exact objective values
@@ -1790,6 +1842,10 @@ int check_values_f64(int32_t n, int32_t m, const double* lam, const double* w,
   return PP_OK;
 }
 
+int32_t max_cap(int32_t m, const int32_t* cap) {
+  return *std::max_element(cap, cap + m);
+}
+
 int check_f64_options(double eps) {
   if (!finite_nonneg(eps)) return fail(PP_E_ARG, "epsilon must be finite and >= 0");
   return PP_OK;
@@ -1839,16 +1895,14 @@ pp_ctx* thread_ctx(int& rc) {
 // Upload the tree layout and (already gathered or identity) inputs.
 int upload_tree(pp_ctx* c, const TreeLayout& t, hipStream_t st) {
   const size_t n = (size_t)t.n;
-  const size_t a = (n * 4 + 255) & ~(size_t)255, ceb = t.ce.size() * 4;
+  const size_t a = (n * 4 + 255) & ~(size_t)255;
   std::vector<uint8_t>& h = c->tree_host;
-  h.assign(2 * a + ceb, 0);
+  h.assign(2 * a, 0);
   std::memcpy(h.data(), t.nextpos.data(), n * 4);
   std::memcpy(h.data() + a, t.order.data(), n * 4);
-  std::memcpy(h.data() + 2 * a, t.ce.data(), ceb);
   PP_TRY(c->tree.ensure(h.size()));
   c->nextpos = c->tree.as<int32_t>();
   c->order = (int32_t*)(c->tree.as<uint8_t>() + a);
-  c->ce = (uint32_t*)(c->tree.as<uint8_t>() + 2 * a);
   return stage_h2d(c, c->tree.p, h.data(), h.size(), st);
 }
 
@@ -2267,7 +2321,7 @@ int pp_plan_device(pp_ctx* ctx, int32_t n, int32_t m, const int32_t* parent,
                            ctx->partial.as<uint64_t>(), &nb, st));
     PP_HIP(hipMemcpyAsync(ctx->val_pin, ctx->partial.p, 16 * (size_t)nb,
                           hipMemcpyDeviceToHost, st));
-    const int trc = build_tree(n, parent, t);
+    const int trc = build_tree(n, parent, t, max_cap(m, cap));
     if (trc != PP_OK) {
       PP_TRY(poll_stream(st));
       return trc;
@@ -2311,7 +2365,7 @@ int pp_plan(int32_t n, int32_t m, const int32_t* parent, const int64_t* demand,
     unsigned __int128 tot = 0;
     PP_TRY(check_values(n, m, demand, recompute_cost, fetch_cost, &tot));
     TreeLayout t;
-    PP_TRY(build_tree(n, parent, t));
+    PP_TRY(build_tree(n, parent, t, o.flags & PP_F_VALIDATE_ONLY ? -1 : max_cap(m, cap)));
     if (o.flags & PP_F_VALIDATE_ONLY) return PP_OK;
     int rc = PP_OK;
     pp_ctx* c = thread_ctx(rc);
@@ -2354,7 +2408,7 @@ int pp_plan_f64_device(pp_ctx* ctx, int32_t n, int32_t m, const int32_t* parent,
                                ctx->partial.as<uint64_t>(), &nb, st));
     PP_HIP(hipMemcpyAsync(ctx->val_pin, ctx->partial.p, 8 * (size_t)nb,
                           hipMemcpyDeviceToHost, st));
-    const int trc = build_tree(n, parent, t);
+    const int trc = build_tree(n, parent, t, max_cap(m, cap));
     if (trc != PP_OK) {
       PP_TRY(poll_stream(st));
       return trc;
@@ -2393,7 +2447,7 @@ int pp_plan_f64(int32_t n, int32_t m, const int32_t* parent, const double* deman
       if (cap[h] < 0) return fail(PP_E_RANGE, "negative capacity");
     PP_TRY(check_values_f64(n, m, demand, recompute_cost, fetch_cost));
     TreeLayout t;
-    PP_TRY(build_tree(n, parent, t));
+    PP_TRY(build_tree(n, parent, t, o.flags & PP_F_VALIDATE_ONLY ? -1 : max_cap(m, cap)));
     if (o.flags & PP_F_VALIDATE_ONLY) return PP_OK;
     int rc = PP_OK;
     pp_ctx* c = thread_ctx(rc);
@@ -2430,7 +2484,7 @@ int pp_replan(int32_t n, int32_t m, const int32_t* parent, const int64_t* demand
     unsigned __int128 tot = 0;
     PP_TRY(check_values(n, m, demand, recompute_cost, fetch_cost, &tot));
     TreeLayout t;
-    PP_TRY(build_tree(n, parent, t));
+    PP_TRY(build_tree(n, parent, t, o.flags & PP_F_VALIDATE_ONLY ? -1 : max_cap(m, cap)));
     if (o.flags & PP_F_VALIDATE_ONLY) return PP_OK;
     int rc = PP_OK;
     pp_ctx* c = thread_ctx(rc);
@@ -2483,7 +2537,7 @@ static int rooted_dp_impl(int32_t n, const int32_t* parent, const void* profit_v
         return fail(PP_E_OVERFLOW, "sum of profits exceeds INT64_MAX");
     }
     TreeLayout t;
-    PP_TRY(build_tree(n, parent, t));
+    PP_TRY(build_tree(n, parent, t, k));
     const int32_t kp = std::min(k, n);
     if (kp == 0) {
       std::memset(selected, 0, n);
@@ -2500,14 +2554,8 @@ static int rooted_dp_impl(int32_t n, const int32_t* parent, const void* profit_v
     d.m = 1;
     d.npad = npad_of(n);
     d.nextpos = c->nextpos;
-    d.ce = c->ce;
     d.f64 = f64 ? 1 : 0;
-    const int32_t slots_lds = t.slots;
-    const int cells = choose_cells((kp + 63) / 64, c->device, slots_lds);
-    PP_TRY(ensure_slots(c, d, 1, kp, cells));
-    PP_TRY(upload_meta(c, t, cells, st));
-    d.meta = c->meta.as<uint32_t>();  // upload_meta may have (re)allocated it
-    PP_TRY(upload_spills(c, t, d, 1, st));
+    PP_TRY(ensure_slots(c, d, 1));
     const int reduce_lds = reduce_lds_for(t, c->device);
     if (reduce_lds) PP_TRY(ensure_reduce(c, t, d, 1, st));
     PP_TRY(c->up_lam.ensure((size_t)n * 8));
@@ -2521,11 +2569,13 @@ static int rooted_dp_impl(int32_t n, const int32_t* parent, const void* profit_v
     e.c = c;
     e.d = d;
     e.st = st;
-    e.slots_lds = slots_lds;
-    e.resident = dp_resident_blocks(cells, slots_lds, c->device);
+    e.tree = &t;
+    e.kmax = kp;
+    e.sweep_slots = 1;
+    e.stage64 = (kp + 63) / 64;
     e.fmax = tot < kFmaxBound && env_int("PP_DP_NO_FMAX", 0) == 0;
     e.reduce_lds = reduce_lds;
-    if (e.resident <= 0) return fail(PP_E_UNSUPPORTED, "DP sweep cannot be resident");
+    if (!reduce_lds || !t.ce.empty()) PP_TRY(e.set_up_sweep());
     std::vector<uint32_t> pre(d.npad / 32);
     ChainState out{};
     for (int attempt = 0;; ++attempt) {  // again, with a longer wait, if it stalled
@@ -2566,7 +2616,7 @@ int pp_replan_f64(int32_t n, int32_t m, const int32_t* parent, const double* dem
       if (incumbent[x] > 1) return fail(PP_E_ARG, "incumbent entries must be 0 or 1");
     PP_TRY(check_values_f64(n, m, demand, recompute_cost, fetch_cost));
     TreeLayout t;
-    PP_TRY(build_tree(n, parent, t));
+    PP_TRY(build_tree(n, parent, t, o.flags & PP_F_VALIDATE_ONLY ? -1 : max_cap(m, cap)));
     if (o.flags & PP_F_VALIDATE_ONLY) return PP_OK;
     int rc = PP_OK;
     pp_ctx* c = thread_ctx(rc);
@@ -2633,7 +2683,7 @@ static int marginal_or_objective(int32_t n, int32_t m, const int64_t* demand,
   d.lam = c->lam.as<int64_t>();
   d.w = c->w.as<int64_t>();
   d.f = c->f.as<int64_t>();
-  PP_TRY(ensure_slots(c, d, 1, 1, 1));
+  PP_TRY(ensure_slots(c, d, 1));
   std::vector<int32_t> sl{0}, wk{h}, kk{0};
   ChainSet set = chain_set(sl, wk, kk, 0, 1);
   PP_HIP(launch_init_slots(set, d, 0, st));
