@@ -802,7 +802,7 @@ int ensure_sweep(pp_ctx* c, const TreeLayout& t, DevState& d, int32_t slots, int
 int ensure_exact(pp_ctx* c, DevState& d, int32_t slots) {
   d.gx_blocks = gexact_blocks(d.n, d.m);
   PP_TRY(c->gx.ensure((size_t)slots * 2 * kExLimbs * 4));
-  PP_TRY(c->gxp.ensure((size_t)kMaxChains * d.gx_blocks * kExLimbs * 8));
+  PP_TRY(c->gxp.ensure((size_t)kMaxChains * d.gx_blocks * 2 * kExLimbs * 8));
   d.gx = c->gx.as<uint32_t>();
   d.gxp = c->gxp.as<uint64_t>();
   return PP_OK;

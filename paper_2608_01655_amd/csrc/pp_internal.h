@@ -294,7 +294,7 @@ struct DevState {
   double eps;               // refinement tolerance (real-valued costs)
   // Exact objective values (real-valued costs): gx[slot][0] = G of the
   // slot's placement, gx[slot][1] = G with the slot's last update adopted;
-  // gxp = lazy per-block partial sums, [chain][gx_blocks][kExLimbs].
+  // gxp = per-block partial sums, [chain][gx_blocks][2][kExLimbs].
   uint32_t* gx;
   uint64_t* gxp;
   int32_t gx_blocks;

@@ -1947,58 +1947,108 @@ __global__ void __launch_bounds__(256) k_objective(ChainSet set, DevState d) {
 
 // Real-valued costs: G (Eq. 6) as the exact sum of its rounded terms, so
 // that every comparison of objectives is independent of summation order.
-// replace = 0: the slot's own placement, terms Lambda_r(b) * v1_r(b).
-// replace = 1: the update's placement, worker h's set replaced by the
-// backtracked selection T'_h: terms Lambda_r(b) * max(v_r^{(-h)}(b),
-// [b in T'_h] q_{r<-h}(b)), v^{(-h)} from the source slot's top-2 holder
-// state (the same values the oracle's maximum over holders gives).
-// Per-block lazy partial sums go to d.gxp.
-__global__ void __launch_bounds__(256) k_gexact(ChainSet set, DevState d, int replace) {
-  const int ci = blockIdx.y;
-  const int64_t s = set.slot[ci];
-  if (replace && (d.cs[s].skip || d.cs[s].rejected)) return;  // already rejected
-  __shared__ unsigned long long acc[kExLimbs];
-  for (int q = threadIdx.x; q < kExLimbs; q += blockDim.x) acc[q] = 0;
+// k_gexact: the slot's own placement, terms Lambda_r(b) * v1_r(b).
+// k_gexact_change: what an update adds and takes away: where worker h's set
+// changes, the terms Lambda_r(b) * max(v_r^{(-h)}(b), [b in T'_h]
+// q_{r<-h}(b)) with the backtracked selection T'_h, and the terms
+// Lambda_r(b) * v1_r(b) they replace, v from the source slot's top-2 holder
+// state (the same values the oracle's maximum over holders gives); every
+// other term is in both sums.
+// Per-block partial sums, carried (each limb below 2^32), go to d.gxp:
+// kExLimbs words a block, for k_gexact_change those added, then those taken.
+// Bound by the latency of a few dependent loads per changed chunk and the
+// block's 72-limb carry: an update changes tens to hundreds of chunks, so
+// summing all m n terms again was almost all of it (n = 50,000, m = 16, up to
+// 16 chains: 43 us, now 8.5; with k_gexact_final 60, now 18).
+__device__ void gexact_store(unsigned long long* acc, int sums, uint64_t* part) {
   __syncthreads();
-  const int64_t ps = set.src[ci];
-  const int h = set.worker[ci];
-  const int64_t n = d.n, mn = (int64_t)d.m * n;
-  const uint32_t* selw = d.sel + s * (d.npad / 32);
-  ExWindow win;
-  for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < mn;
-       x += (int64_t)gridDim.x * blockDim.x) {
-    double best;
-    if (replace) {
-      const int r = (int)(x / n);
-      const int64_t i = x - (int64_t)r * n;
-      const int64_t o = ps * mn + x;
-      best = as_f((d.h1[o] == h) ? d.v2[o] : d.v1[o]);
-      if ((selw[i >> 5] >> (i & 31)) & 1u) {
-        const double q = as_f(saving(d, h, r, i));
-        best = q > best ? q : best;
-      }
-    } else {
-      best = as_f(d.v1[s * mn + x]);
-    }
-    ex_accumulate(acc, win, as_f(d.lam[x]) * best);
-  }
-  ex_flush(acc, win);
-  __syncthreads();
-  if (threadIdx.x == 0) {  // carry the block's limbs: each below 2^32 after
+  if ((int)threadIdx.x < sums) {
+    unsigned long long* a = acc + threadIdx.x * kExLimbs;
     unsigned long long carry = 0;
     for (int q = 0; q < kExLimbs; ++q) {
-      const unsigned long long v = acc[q] + carry;
-      acc[q] = v & 0xFFFFFFFFull;
+      const unsigned long long v = a[q] + carry;
+      a[q] = v & 0xFFFFFFFFull;
       carry = v >> 32;
     }
   }
   __syncthreads();
-  uint64_t* part = d.gxp + ((int64_t)ci * d.gx_blocks + blockIdx.x) * kExLimbs;
-  for (int q = threadIdx.x; q < kExLimbs; q += blockDim.x) part[q] = acc[q];
+  for (int q = threadIdx.x; q < sums * kExLimbs; q += blockDim.x) part[q] = acc[q];
 }
 
-// One block per chain: the exact G from k_gexact's partials (carried into
-// canonical limbs), then
+__global__ void __launch_bounds__(256) k_gexact(ChainSet set, DevState d) {
+  const int ci = blockIdx.y;
+  const int64_t s = set.slot[ci];
+  __shared__ unsigned long long acc[kExLimbs];
+  for (int q = threadIdx.x; q < kExLimbs; q += blockDim.x) acc[q] = 0;
+  __syncthreads();
+  const int64_t mn = (int64_t)d.m * d.n;
+  ExWindow win;
+  for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < mn;
+       x += (int64_t)gridDim.x * blockDim.x)
+    ex_accumulate(acc, win, as_f(d.lam[x]) * as_f(d.v1[s * mn + x]));
+  ex_flush(acc, win);
+  gexact_store(acc, 1, d.gxp + ((int64_t)ci * d.gx_blocks + blockIdx.x) * 2 * kExLimbs);
+}
+
+__global__ void __launch_bounds__(256) k_gexact_change(ChainSet set, DevState d) {
+  const int ci = blockIdx.y;
+  const int64_t s = set.slot[ci];
+  if (d.cs[s].skip || d.cs[s].rejected) return;  // already rejected
+  __shared__ unsigned long long acc[2 * kExLimbs];
+  __shared__ uint32_t s_chunk[256];  // changed chunks, bit 31: joins
+  __shared__ int s_wave[4];
+  const int tid = threadIdx.x, lane = tid % kWave, wv = tid / kWave;
+  for (int q = tid; q < 2 * kExLimbs; q += blockDim.x) acc[q] = 0;
+  const int64_t ps = set.src[ci];
+  const int h = set.worker[ci], m = d.m;
+  const int64_t n = d.n, mn = (int64_t)m * n;
+  const uint32_t* selw = d.sel + s * (d.npad / 32);
+  const uint8_t* th = d.tgt + ps * mn + (int64_t)h * n;
+  ExWindow added, taken;
+  for (int64_t i0 = (int64_t)blockIdx.x * 256; i0 < n; i0 += (int64_t)gridDim.x * 256) {
+    const int64_t c = i0 + tid;
+    uint32_t nv = 0;
+    bool changed = false;
+    if (c < n) {
+      nv = (selw[c >> 5] >> (c & 31)) & 1u;
+      changed = nv != (th[c] != 0 ? 1u : 0u);
+    }
+    const uint64_t b = __ballot(changed);
+    __syncthreads();  // the previous tile's list has been read
+    if (lane == 0) s_wave[wv] = __popcll(b);
+    __syncthreads();
+    int at = 0, count = 0;
+    for (int k = 0; k < 4; ++k) {
+      at += k < wv ? s_wave[k] : 0;
+      count += s_wave[k];
+    }
+    if (changed) s_chunk[at + __popcll(b & ((1ull << lane) - 1u))] = (uint32_t)c | nv << 31;
+    __syncthreads();
+    for (int x = tid; x < count * m; x += blockDim.x) {
+      const int r = x / count;
+      const uint32_t e = s_chunk[x - r * count];
+      const int64_t i = e & 0x7FFFFFFFu;
+      const int64_t o = ps * mn + (int64_t)r * n + i;
+      const double v1 = as_f(d.v1[o]);
+      double best = d.h1[o] == h ? as_f(d.v2[o]) : v1;
+      if (e >> 31) {
+        const double q = as_f(saving(d, h, r, i));
+        best = q > best ? q : best;
+      }
+      if (best != v1) {
+        const double L = as_f(d.lam[(int64_t)r * n + i]);
+        ex_accumulate(acc, added, L * best);
+        ex_accumulate(acc + kExLimbs, taken, L * v1);
+      }
+    }
+  }
+  __syncthreads();
+  ex_flush(acc, added);
+  ex_flush(acc + kExLimbs, taken);
+  gexact_store(acc, 2, d.gxp + ((int64_t)ci * d.gx_blocks + blockIdx.x) * 2 * kExLimbs);
+}
+
+// One block per chain: the exact G from the partials, then
 //   kModeGreedy: the update is adopted: gx[slot][0] = G, acceptance marks;
 //   kModeRefine: Algorithm 1's test, exact G(T_-h, T'_h) > exact G(T) +
 //                eps with G(T) that of the source slot; on acceptance the
@@ -2006,66 +2056,91 @@ __global__ void __launch_bounds__(256) k_gexact(ChainSet set, DevState d, int re
 //                stale, and (in the start's own slot) G(T) updated;
 //   otherwise:   the slot's objective, gx[slot][0] = G and its nearest
 //                double in cs.obj.
-// gx[slot][1] always receives G.
+// gx[slot][1] always receives G.  Updates: G = G(T) + added - taken, on the
+// source slot's exact limbs; the carries run over the limbs that change.
 __global__ void __launch_bounds__(256) k_gexact_final(ChainSet set, DevState d, int mode,
                                                       int nblocks) {
   const int ci = blockIdx.x;
   const int64_t s = set.slot[ci];
   const bool update = mode == kModeGreedy || mode == kModeRefine;
   if (update && (d.cs[s].skip || d.cs[s].rejected)) return;
+  const int64_t ps = set.src[ci];
+  const int tid = threadIdx.x;
   // the blocks' partials are carried limbs (each below 2^32), so a limb's
   // sum over at most kGexactBlocks of them stays below 2^41
-  __shared__ unsigned long long tot[kExLimbs];
-  __shared__ uint32_t g[kExLimbs];
-  for (int q = threadIdx.x; q < kExLimbs; q += blockDim.x) tot[q] = 0;
+  __shared__ unsigned long long tot[2 * kExLimbs];
+  __shared__ uint32_t g[kExLimbs], bar[kExLimbs];
+  __shared__ int s_lo, s_hi, s_accept;
+  const uint32_t* gs = d.gx + (ps * 2) * kExLimbs;
+  for (int q = tid; q < 2 * kExLimbs; q += blockDim.x) tot[q] = 0;
+  if (tid < kExLimbs) bar[tid] = update ? gs[tid] : 0u;  // G(T)
+  if (tid == 0) {
+    s_lo = kExLimbs;
+    s_hi = -1;
+  }
   __syncthreads();
-  const uint64_t* part = d.gxp + (int64_t)ci * d.gx_blocks * kExLimbs;
-  const int count = nblocks * kExLimbs;
+  const uint64_t* part = d.gxp + (int64_t)ci * d.gx_blocks * 2 * kExLimbs;
+  const int words = update ? 2 * kExLimbs : kExLimbs;
+  const int count = nblocks * words;
   constexpr int kUnroll = 4;  // loads in flight per thread
-  for (int x0 = threadIdx.x; x0 < count; x0 += kUnroll * blockDim.x) {
+  for (int x0 = tid; x0 < count; x0 += kUnroll * blockDim.x) {
     uint64_t v[kUnroll];
 #pragma unroll
     for (int k = 0; k < kUnroll; ++k) {
       const int x = x0 + k * blockDim.x;
-      v[k] = x < count ? part[x] : 0;
+      v[k] = x < count ? part[(int64_t)(x / words) * 2 * kExLimbs + x % words] : 0;
     }
 #pragma unroll
     for (int k = 0; k < kUnroll; ++k)
-      if (v[k]) atomicAdd(&tot[(x0 + k * blockDim.x) % kExLimbs], (unsigned long long)v[k]);
+      if (v[k])
+        atomicAdd(&tot[(x0 + k * blockDim.x) % words], (unsigned long long)v[k]);
   }
   __syncthreads();
-  if (threadIdx.x != 0) return;
-  unsigned long long carry = 0;
-  for (int q = 0; q < kExLimbs; ++q) {
-    const unsigned long long v = tot[q] + carry;
-    g[q] = (uint32_t)v;
-    carry = v >> 32;
+  if (tid < kExLimbs) {
+    g[tid] = bar[tid];
+    if (tot[tid] | (update ? tot[kExLimbs + tid] : 0ull)) {
+      atomicMin(&s_lo, tid);
+      atomicMax(&s_hi, tid);
+    }
   }
+  __syncthreads();
+  if (tid == 0) {
+    int64_t carry = 0;
+    for (int q = s_lo; q < kExLimbs && (q <= s_hi || carry != 0); ++q) {
+      const int64_t v = (int64_t)g[q] + (int64_t)tot[q] -
+                        (update ? (int64_t)tot[kExLimbs + q] : 0) + carry;
+      g[q] = (uint32_t)v;
+      carry = v >> 32;  // arithmetic: a borrow is negative
+    }
+    if (mode == kModeRefine) ex_add_double(bar, d.eps);
+    s_accept = mode == kModeGreedy ? 1 : 0;
+  }
+  __syncthreads();
+  if (mode == kModeRefine && tid < kWave) {
+    // the highest limb that differs decides
+    auto cmp = [&](int q) { return q < kExLimbs && g[q] != bar[q]; };
+    const uint64_t lo = __ballot(cmp(tid)), hi = __ballot(cmp(tid + kWave));
+    const int q = hi ? 127 - __builtin_clzll(hi) : lo ? 63 - __builtin_clzll(lo) : -1;
+    if (tid == 0) s_accept = q >= 0 && g[q] > bar[q] ? 1 : 0;
+  }
+  __syncthreads();
   uint32_t* cur = d.gx + (s * 2) * kExLimbs;
   uint32_t* nxt = d.gx + (s * 2 + 1) * kExLimbs;
-  for (int q = 0; q < kExLimbs; ++q) nxt[q] = g[q];
+  if (tid < kExLimbs) {
+    nxt[tid] = g[tid];
+    if (!update || (s_accept && s == ps)) cur[tid] = g[tid];
+  }
+  if (tid != 0) return;
   ChainState* st = d.cs + s;
   if (!update) {
-    for (int q = 0; q < kExLimbs; ++q) cur[q] = g[q];
     st->obj = (int64_t)ex_round_bits(g);
     return;
   }
-  const int64_t ps = set.src[ci];
-  bool accept = true;
-  if (mode == kModeRefine) {
-    uint32_t bar[kExLimbs];
-    const uint32_t* gs = d.gx + (ps * 2) * kExLimbs;
-    for (int q = 0; q < kExLimbs; ++q) bar[q] = gs[q];
-    ex_add_double(bar, d.eps);
-    accept = ex_cmp(g, bar) > 0;
-  }
-  st->accept = accept ? 1 : 0;
-  if (!accept) return;
+  st->accept = s_accept;
+  if (!s_accept) return;
   if (mode == kModeRefine) st->accepts += 1;
   const int h = set.worker[ci];
   for (int q = 0; q < 8; ++q) st->dirty[q] |= q == (h >> 5) ? ~(1u << (h & 31)) : ~0u;
-  if (s == ps)
-    for (int q = 0; q < kExLimbs; ++q) cur[q] = g[q];
 }
 
 inline dim3 grid1(int64_t work, int bs, int rows) {
@@ -2353,11 +2428,16 @@ int32_t gexact_blocks(int32_t n, int32_t m) {
 hipError_t launch_gexact(const ChainSet& set, const DevState& d, int mode,
                          hipStream_t st) {
   if (set.count == 0) return hipSuccess;
-  const int32_t b = gexact_blocks(d.n, d.m);
+  const bool update = mode == kModeGreedy || mode == kModeRefine;
+  int32_t b = gexact_blocks(d.n, d.m);
+  // an update's terms are those of the chunks that change: fewer blocks (each
+  // takes 256 chunks at a time), whose partials are also added up faster
+  if (update) b = std::min<int32_t>(b, std::max<int32_t>(1, std::min((d.n + 255) / 256, 64)));
   if (b > d.gx_blocks) return hipErrorInvalidValue;
-  const int replace = (mode == kModeGreedy || mode == kModeRefine) ? 1 : 0;
-  hipLaunchKernelGGL(k_gexact, dim3((unsigned)b, set.count), dim3(256), 0, st, set, d,
-                     replace);
+  if (update)
+    hipLaunchKernelGGL(k_gexact_change, dim3((unsigned)b, set.count), dim3(256), 0, st, set, d);
+  else
+    hipLaunchKernelGGL(k_gexact, dim3((unsigned)b, set.count), dim3(256), 0, st, set, d);
   hipLaunchKernelGGL(k_gexact_final, dim3(set.count), dim3(256), 0, st, set, d, mode,
                      (int)b);
   return hipGetLastError();

@@ -108,3 +108,25 @@ def test_plan_reduced(oracle_mod, seed):
     eps = float(rng.choice([0.0, 1e-9])) * float(np.sum(lam * w))
     _same(B.pp_plan_f64(inst.parent, lam, w, f, inst.cap, epsilon=eps, **kw),
           oracle_mod.plan_f64(inst.parent, lam, w, f, inst.cap, epsilon=eps, **kw))
+
+
+@pytest.mark.parametrize("n,m,starts", [(64, 3, 70), (130, 16, 33), (255, 17, 2), (256, 33, 1),
+                                        (257, 5, 20), (511, 40, 9)])
+def test_plan_reduced_many(oracle_mod, monkeypatch, n, m, starts):
+    """Launches of more than 16 and 32 chains, more workers than one block
+    keeps, tiles that end in the tree, speculation off and on; the exact
+    objectives' changes over costs whose sums span several limbs."""
+    rng = np.random.default_rng(n * m)
+    inst = W.random_instance(n, m, rng, kmax=n // 4, source_dependent=True, value_range=50)
+    lam, w, f = W.real_valued(inst, n, jitter=0.5)
+    scale = 10.0 ** rng.integers(-40, 40, size=n)
+    w, f = w * scale, f * scale
+    for chains in ("1", "32"):
+        monkeypatch.setenv("PP_SPEC_CHAINS", chains)
+        kw = dict(n_starts=starts, max_rounds=3, order_seed=n)
+        _same(B.pp_plan(inst.parent, inst.demand, inst.recompute_cost, inst.fetch_cost, inst.cap,
+                        **kw),
+              oracle_mod.plan(inst.parent, inst.demand, inst.recompute_cost, inst.fetch_cost,
+                              inst.cap, **kw))
+        _same(B.pp_plan_f64(inst.parent, lam, w, f, inst.cap, epsilon=0.0, **kw),
+              oracle_mod.plan_f64(inst.parent, lam, w, f, inst.cap, epsilon=0.0, **kw))
