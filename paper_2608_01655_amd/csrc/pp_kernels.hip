@@ -1,8 +1,11 @@
 // pp_kernels.hip -- gfx950 kernels of the PrefixPlace worker update.
 //
-// One worker update (Algorithm 1, PrefixPlace procedure) is four launches
+// One worker update (Algorithm 1, PrefixPlace procedure) is a few launches
 // over every active chain (a chain is one start's current update, or one
-// standalone solve):
+// standalone solve).  Trees of 1,024 nodes and more are solved by the reduced
+// solve of pp_reduce.hip, and k_dp and k_backtrack run for the chains that it
+// leaves; refinement keeps profits between updates (k_rows, k_commit) and runs
+// k_gains for greedy positions only:
 //   k_gains      exact marginals p_h(b) (Eq. 7, Proposition 1) from the
 //                top-2 holder state, plus the incumbent's value for the
 //                strict-improvement test (Sec. IV-C)

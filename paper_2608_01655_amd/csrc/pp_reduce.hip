@@ -375,12 +375,24 @@ __device__ __forceinline__ int64_t shr1(int64_t v) {
   return (int64_t)((uint64_t)(uint32_t)hi << 32 | (uint32_t)lo);
 }
 
+__device__ __forceinline__ int64_t lane_of(int64_t v, int l) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l);
+  return (int64_t)((uint64_t)hi << 32 | lo);
+}
+
 // The core DP of one wave, columns 0..64C-1 (lane l: columns lC .. lC+C-1),
-// rows last to first; *out: the last row's value at column col.  A row's word
-// and profit are read two rows ahead, its skip operand one row ahead (the
-// row just computed is never the next row's far operand: that one is a
-// leaf).  Choice masks of core row r (its rank among the core rows):
-// ch[r C + c].
+// rows last to first; *out: the last row's value at column col.  Choice masks
+// of core row r (its rank among the core rows): ch[r C + c].
+// One dependent chain of rows: the words and profits of 64 rows are in
+// registers (lane l: row base - l, the next 64 on their way), and only rows
+// that skip past a subtree wait for LDS, their operand read one row ahead (the
+// row just computed is never the next row's far operand: that one is a leaf).
+// Forced rows that nothing skips to are one addition.  Reading each row's word
+// and operand from LDS took about 120 ns a row, most of the solve at large k'
+// where costs are real-valued: n = 50,000, m = 16, k = 4,096: k_reduce 633 ->
+// 230 us per launch, at k = 128 124 -> 111; integer cores, which have no forced
+// rows, stay where they were (84 and 87 us, 217 and 219).
 template <int C, bool F64>
 __device__ void core_dp(int rows, int core, const int64_t* rp, const uint32_t* rinfo,
                         int64_t* slots, uint64_t* ch, int col, int64_t* out) {
@@ -388,50 +400,85 @@ __device__ void core_dp(int rows, int core, const int64_t* rp, const uint32_t* r
   int64_t D[C], skn[C];
 #pragma unroll
   for (int c = 0; c < C; ++c) D[c] = skn[c] = slots[c * 64 + lane] = 0;
-  uint32_t i0 = rows > 0 ? rinfo[rows - 1] : 0u, i1 = rows > 1 ? rinfo[rows - 2] : 0u;
-  int64_t p0 = rows > 0 ? rp[rows - 1] : 0, p1 = rows > 1 ? rp[rows - 2] : 0;
+  auto far = [&](uint32_t in) {  // the row's skip operand
+#pragma unroll
+    for (int c = 0; c < C; ++c) skn[c] = slots[((in >> 16) * C + c) * 64 + lane];
+  };
+  uint32_t ri = 0;
+  int64_t pi = 0;
+  if (rows > 0) {
+    ri = rinfo[max(rows - 1 - lane, 0)];
+    pi = rp[max(rows - 1 - lane, 0)];
+  }
   int cr = core;
-  for (int r = rows - 1; r >= 0; --r) {
-    const uint32_t in = (uint32_t)uniform((int)i0);
-    const int64_t p = p0;
-    i0 = i1;
-    p0 = p1;
-    if (r > 1) {
-      i1 = rinfo[r - 2];
-      p1 = rp[r - 2];
+  for (int base = rows - 1; base >= 0; base -= 64) {
+    const int cnt = min(64, base + 1);
+    const uint32_t w = ri;
+    const int64_t q = pi;
+    if (base >= 64) {
+      ri = rinfo[max(base - 64 - lane, 0)];
+      pi = rp[max(base - 64 - lane, 0)];
     }
-    int64_t sk[C];
+    // forced, not stored
+    const uint64_t plain =
+        F64 ? __ballot(lane < cnt && (w & kRowForced) && (w & 0xFFFCu) == 0) : 0ull;
+    bool ahead = false;  // row l's operand is in skn
+    for (int l = 0; l < cnt;) {
+      if (F64 && ((plain >> l) & 1u)) {
+        const uint64_t rest = ~(plain >> l);
+        const int end = l + (rest ? __builtin_ctzll(rest) : 64);
+#pragma unroll 4
+        for (; l < end; ++l) {
+          const double p = as_d(lane_of(q, l));
 #pragma unroll
-    for (int c = 0; c < C; ++c) sk[c] = skn[c];
-    const uint32_t ns = (uint32_t)uniform((int)i0) >> 16;
-#pragma unroll
-    for (int c = 0; c < C; ++c) skn[c] = slots[(ns * C + c) * 64 + lane];
-    if (F64 && (in & kRowForced)) {
-#pragma unroll
-      for (int c = 0; c < C; ++c) D[c] = as_l(as_d(p) + as_d(D[c]));
-    } else {
-      --cr;
-      const int64_t left = shr1(D[C - 1]);
-      int64_t t[C];
-#pragma unroll
-      for (int c = 0; c < C; ++c) {
-        const int64_t v = c == 0 ? left : D[c - 1];
-        t[c] = F64 ? as_l(as_d(p) + as_d(v)) : p + v;
-        if (in & kRowLeaf) sk[c] = D[c];
+          for (int c = 0; c < C; ++c) D[c] = as_l(p + as_d(D[c]));
+        }
+        ahead = false;
+        continue;
       }
+      const uint32_t in = (uint32_t)__builtin_amdgcn_readlane((int)w, l);
+      const int64_t p = lane_of(q, l);
+      if (F64 && (in & kRowForced)) {
+        ahead = false;
 #pragma unroll
-      for (int c = 0; c < C; ++c) {
-        // non-negative doubles compare like their bit patterns
-        const bool take = t[c] > sk[c] && (c > 0 || lane > 0);
-        const uint64_t m = __ballot(take);
-        if (lane == 0) ch[cr * C + c] = m;
-        D[c] = take ? t[c] : sk[c];
+        for (int c = 0; c < C; ++c) D[c] = as_l(as_d(p) + as_d(D[c]));
+      } else {
+        int64_t sk[C];
+        if (in & kRowLeaf) {
+#pragma unroll
+          for (int c = 0; c < C; ++c) sk[c] = D[c];
+        } else {
+          if (!ahead) far(in);
+#pragma unroll
+          for (int c = 0; c < C; ++c) sk[c] = skn[c];
+        }
+        const uint32_t nx = l + 1 < cnt ? (uint32_t)__builtin_amdgcn_readlane((int)w, l + 1)
+                                        : kRowLeaf;
+        ahead = (nx & (kRowLeaf | kRowForced)) == 0;
+        if (ahead) far(nx);
+        --cr;
+        const int64_t left = shr1(D[C - 1]);
+        int64_t t[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          const int64_t v = c == 0 ? left : D[c - 1];
+          t[c] = F64 ? as_l(as_d(p) + as_d(v)) : p + v;
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          // non-negative doubles compare like their bit patterns
+          const bool take = t[c] > sk[c] && (c > 0 || lane > 0);
+          const uint64_t m = __ballot(take);
+          if (lane == 0) ch[cr * C + c] = m;
+          D[c] = take ? t[c] : sk[c];
+        }
       }
-    }
-    const uint32_t st = (in >> 2) & 0x3FFFu;
-    if (st != 0) {
+      const uint32_t st = (in >> 2) & 0x3FFFu;
+      if (st != 0) {
 #pragma unroll
-      for (int c = 0; c < C; ++c) slots[(st * C + c) * 64 + lane] = D[c];
+        for (int c = 0; c < C; ++c) slots[(st * C + c) * 64 + lane] = D[c];
+      }
+      ++l;
     }
   }
 #pragma unroll
