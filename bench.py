@@ -244,6 +244,10 @@ def plan_timing(B, ctx, inst, lam, w, f, tgt, steps, warmup, plan_flags=0):
     return dt, step_ms, plans
 
 
+# a reduced solve reads per node: its profit (8), key (4) and parent link (2)
+SOLVE_BYTES_PER_N = 14
+
+
 def dp_figures(inst, plans, dt):
     """Throughput and roofline figures of a series of plans: plan-level
     cells per second (Algorithm 1's count and the cells actually swept), the
@@ -257,6 +261,10 @@ def dp_figures(inst, plans, dt):
     launches = sum(q.dp_launches for q in plans)
     kernel_cps = exec_cells / (dp_ms / 1e3) if dp_ms > 0 else 0.0
     c = max(1, p.dp_lane_cells)
+    # every update solved without a sweep: the sweep's instruction, LDS and
+    # table models say nothing about the kernels that ran
+    swept = p.dp_lane_cells > 0
+    solved = exec_cells / (inst.n * max(1.0, float(inst.cap.clip(max=inst.n).mean())))
     valu = dp_valu_per_step(c, p.dp_fmax, isinstance(p.objective, float))
     issue_ceiling = VALU_PEAK_TOPS * 1e12 * c / valu  # cells/s
     lds_b = dp_lds_bytes_per_cell(c)
@@ -271,19 +279,23 @@ def dp_figures(inst, plans, dt):
         "dp_cells_per_plan_algorithm1": p.dp_cells,
         "dp_cells_per_plan_swept": exec_cells // steps,
         "updates_per_plan": p.updates,
-        "dp_lane_cells": c,
+        "dp_lane_cells": p.dp_lane_cells,
+        "solves_per_plan": solved / steps,
+        # a solve has to read the profits and the tree once
+        "solve_hbm_gbs": solved * SOLVE_BYTES_PER_N * inst.n / (dp_ms / 1e3) / 1e9
+        if dp_ms > 0 else None,
         "dp_launches_per_plan": launches // steps,
         "dp_avg_launch_ms": dp_ms / launches if launches else None,
         "dp_share_of_plan_time": dp_ms / 1e3 / dt,
         "dp_cells_per_s_in_kernel": kernel_cps,
-        "dp_issue_frac": kernel_cps / issue_ceiling,
+        "dp_issue_frac": kernel_cps / issue_ceiling if swept else None,
         "dp_valu_per_row_step": valu,
-        "dp_lds_frac": kernel_cps * lds_b / (LDS_PEAK_GBS * 1e9),
+        "dp_lds_frac": kernel_cps * lds_b / (LDS_PEAK_GBS * 1e9) if swept else None,
         "dp_table_model_hbm_frac": kernel_cps * TABLE_BYTES_PER_CELL
-        / (HBM_PEAK_GBS * 1e9),
+        / (HBM_PEAK_GBS * 1e9) if swept else None,
         "plan_table_model_hbm_frac": plan_bytes_table * steps / dt
-        / (HBM_PEAK_GBS * 1e9),
-        "plan_issue_frac": exec_cells / dt / issue_ceiling,
+        / (HBM_PEAK_GBS * 1e9) if swept else None,
+        "plan_issue_frac": exec_cells / dt / issue_ceiling if swept else None,
         "sweeps_per_start": p.start_sweeps.tolist(),
     }
 
@@ -621,39 +633,9 @@ def main():
     # row step x 64 lanes per 64*C cells), over its measured duration
     achieved = cells_per_launch * valu / c / avg_launch_s / 1e12
     traffic = measured_traffic(inst.name)
-    out = {
-        "metric": METRIC,
-        "value": args.steps / dt,
-        "unit": "plans/s",
-        # Algorithm 1's cells (every update n * min(k_h, n)) per second
-        "dp_cells_per_s": fig["dp_cells_per_s_algorithm1"],
-        # cells the sweeps processed (updates of workers whose inputs did not
-        # change need no sweep; discarded speculative updates add theirs)
-        "dp_cells_executed_per_s": fig["dp_cells_per_s_swept"],
-        "dp_cells_per_s_frac_issue_roofline": fig["plan_issue_frac"],
-        "dp_cells_per_s_frac_hbm_table_model": fig["dp_cells_per_s_swept"]
-        * TABLE_BYTES_PER_CELL / (HBM_PEAK_GBS * 1e9),
-        "plans_per_s_frac_hbm_table_model": fig["plan_table_model_hbm_frac"],
-        "n_gpus": 1,
-        "steps": args.steps,
-        "warmup": args.warmup,
-        "ms_per_step": dt / args.steps * 1e3,
-        "ms_per_step_median": step_ms[len(step_ms) // 2],
-        "ms_per_step_min": step_ms[0],
-        "higher_is_better": True,
-        "scaling": "weak",
-        "vs_baseline": None,
-        "dtype": "int64",
-        "data": "synthetic",
-        "config": {
-            "workload": inst.name, "n": inst.n, "workers": inst.m,
-            "k": [int(x) for x in sorted(set(inst.cap.tolist()))],
-            "starts": inst.n_starts, "max_rounds": inst.max_rounds,
-            "updates_per_plan": p.updates, "dp_cells_per_plan": p.dp_cells,
-            "dp_cells_executed_per_plan": exec_cells // args.steps,
-            "sweeps_per_start": p.start_sweeps.tolist(),
-        },
-        "roofline": {
+    real = "true" if isinstance(p.objective, float) else "false"
+    if p.dp_lane_cells > 0:
+        roofline = {
             "bound": "alu",
             "kernel": f"k_dp<{c}, {'true' if p.dp_fmax else 'false'}, false> "
                       "(rooted-tree DP sweep)",
@@ -688,7 +670,58 @@ def main():
                                 "achieved_gbs": fig["dp_cells_per_s_in_kernel"]
                                 * TABLE_BYTES_PER_CELL / 1e9,
                                 "frac": fig["dp_table_model_hbm_frac"]},
+        }
+    else:
+        # the reduced solve: one block a chain, bound by the serial chain of
+        # its phases; against HBM, the bytes its solves cannot do without
+        roofline = {
+            "bound": "hbm",
+            "kernel": f"k_ladder<{real}> + k_reduce<{real}> (reduced exact tree solve)",
+            "achieved": fig["solve_hbm_gbs"],
+            "peak": HBM_PEAK_GBS,
+            "unit": "GB/s",
+            "frac": fig["solve_hbm_gbs"] / HBM_PEAK_GBS,
+            "traffic": None,
+            "bytes_basis": f"{SOLVE_BYTES_PER_N} bytes a node and solve (profit, key, link)",
+            "cells_per_launch": cells_per_launch,
+            "dp_launches_per_plan": launches // args.steps,
+            "avg_launch_ms": avg_launch_s * 1e3,
+            "dp_cells_per_s_in_kernel": fig["dp_cells_per_s_in_kernel"],
+            "dp_share_of_plan_time": fig["dp_share_of_plan_time"],
+        }
+    out = {
+        "metric": METRIC,
+        "value": args.steps / dt,
+        "unit": "plans/s",
+        # Algorithm 1's cells (every update n * min(k_h, n)) per second
+        "dp_cells_per_s": fig["dp_cells_per_s_algorithm1"],
+        # cells the sweeps processed (updates of workers whose inputs did not
+        # change need no sweep; discarded speculative updates add theirs)
+        "dp_cells_executed_per_s": fig["dp_cells_per_s_swept"],
+        "dp_cells_per_s_frac_issue_roofline": fig["plan_issue_frac"],
+        "dp_cells_per_s_frac_hbm_table_model": fig["dp_cells_per_s_swept"]
+        * TABLE_BYTES_PER_CELL / (HBM_PEAK_GBS * 1e9) if p.dp_lane_cells > 0 else None,
+        "plans_per_s_frac_hbm_table_model": fig["plan_table_model_hbm_frac"],
+        "n_gpus": 1,
+        "steps": args.steps,
+        "warmup": args.warmup,
+        "ms_per_step": dt / args.steps * 1e3,
+        "ms_per_step_median": step_ms[len(step_ms) // 2],
+        "ms_per_step_min": step_ms[0],
+        "higher_is_better": True,
+        "scaling": "weak",
+        "vs_baseline": None,
+        "dtype": "int64",
+        "data": "synthetic",
+        "config": {
+            "workload": inst.name, "n": inst.n, "workers": inst.m,
+            "k": [int(x) for x in sorted(set(inst.cap.tolist()))],
+            "starts": inst.n_starts, "max_rounds": inst.max_rounds,
+            "updates_per_plan": p.updates, "dp_cells_per_plan": p.dp_cells,
+            "dp_cells_executed_per_plan": exec_cells // args.steps,
+            "sweeps_per_start": p.start_sweeps.tolist(),
         },
+        "roofline": roofline,
         "parity_vs_golden": gold_ok,
         **({"safeguards": {"run": p.safeguards_run, "returned": p.best_start,
                            "objectives": list(p.safeguard_objective)}}

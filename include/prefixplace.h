@@ -120,13 +120,18 @@ typedef struct {
     int64_t *standalone;       /* out [m]: standalone score per worker */
     int32_t *orders;           /* out [S][m]: start orders used */
     double dp_kernel_ms;       /* out with PP_F_TIME_KERNELS: summed duration
-                                  of the DP-sweep launches */
+                                  of the solve launches: a reduced solve's two
+                                  kernels (with its incumbents' values and
+                                  decisions) count as one, each sweep as one */
     int32_t dp_launches;       /* out with PP_F_TIME_KERNELS */
     int32_t safeguards_run;    /* out: 1 if the PP_F_SAFEGUARDS candidates were
                                   evaluated (requester-side costs) */
     int64_t safeguard_objective[3]; /* out: their objectives (Independent,
                                   Popularity, LocalDedup), 0 if not run */
-    int64_t dp_cells_executed; /* out: DP cells actually swept.  A refinement
+    int64_t dp_cells_executed; /* out: DP cells (n * min(k, n) each) of the
+                                  updates actually solved, whether by the
+                                  reduced solve, which proves most of them away
+                                  without visiting them, or by a sweep.  A refinement
                                   update of a worker whose inputs have not
                                   changed since its last sweep (no other
                                   worker's set changed) would find the same
