@@ -1056,7 +1056,10 @@ int choose_cells(int32_t total_stage_cells_c1, int dev, int32_t slots_lds) {
 
 // Dynamic LDS of a reduced solve's block on this tree, 0 where every update
 // is swept: trees of at least kReduceMinN nodes (below, the n row steps of a
-// sweep take less than the reduced solve's fixed passes) with a level order
+// sweep take less than the reduced solve's fixed passes; whole plans of 4
+// workers and 4 starts, reduced against swept: 512 nodes 1.1-1.6 against
+// 0.53-0.89 ms, 1,023 nodes 1.1-1.3 against 0.87-1.27 ms, 2,000 nodes 1.21
+// against 1.60-1.87 ms, 4,000 nodes 1.22-1.33 against 2.5-3.5 ms) with a level order
 // whose tables fit.  Forcing the sweep's lane width or its spin limit (test
 // hooks) asks for the sweep itself.
 constexpr int32_t kReduceMinN = 1024;
@@ -1573,7 +1576,9 @@ int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) ==
             hipSuccess && cus > 0)
       spec_blocks = 3 * cus;
-    // (reduced solves have no stages: as many updates as a launch holds)
+    // (reduced solves have no stages: kSpecChains updates.  8, 16, 24 and 32
+    // took 18.1, 17.0, 20.5 and 20.6 ms at n = 50,000 and 4.1, 3.8, 3.7 and
+    // 3.7 ms at n = 10,000: past 16 the ladder has half the rungs)
     if (reduce_lds_for(t, c->device)) spec_blocks = INT32_MAX;
     spec_blocks = env_int("PP_SPEC_BLOCKS", spec_blocks);
   }
