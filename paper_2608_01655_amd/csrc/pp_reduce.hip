@@ -277,9 +277,13 @@ __global__ void __launch_bounds__(kRThreads) k_ladder(ChainSet set, DevState d, 
   const int unit = t > 0.0 ? 1 << d.lv_bits : 0;
   const double inv = t > 0.0 ? (double)unit / t : 0.0;
   const double clipd = (double)(clip - 2);
-  // p - t in units, rounded up (price 0: only whether there is a profit)
+  // p - t in units, rounded up (price 0: only whether there is a profit).
+  // inv is infinite for prices below about 2^lv_bits / DBL_MAX: then every
+  // profit is clipped, and no profit (padding slots among them), whose product
+  // with inv would be NaN, stays worth nothing.
   auto up = [&](uint32_t x) -> int {
     if (t == 0.0) return x ? clip : 0;
+    if (x == 0) return 2 - unit;
     return (int)fmin(__builtin_bit_cast(double, (uint64_t)x << 32) * inv, clipd) + 2 - unit;
   };
   for (int q = tid; q < leaf0; q += kRThreads) cs[q] = 0;

@@ -81,6 +81,23 @@ def test_rooted_dp_reduced_sizes(oracle_mod, n, k, tree):
     np.testing.assert_array_equal(sel, osel)
 
 
+@pytest.mark.parametrize("n", [1024, 1100, 2111])
+def test_rooted_dp_reduced_tiny_profits(oracle_mod, n):
+    """Real-valued profits so small that a ladder price's reciprocal overflows
+    (below about 6e-303), into the subnormals; many chunks without a profit."""
+    rng = np.random.default_rng(n)
+    for tname, parent in _trees(n, rng):
+        for scale in (1e-301, 1e-303, 1e-305, 1e-307, 1e-310, 1e-318):
+            for dense in (0.1, 0.7, 1.0):
+                p = rng.uniform(0.1, 10.0, size=n) * scale * (rng.random(n) < dense)
+                for k in (1, 20, 64, n // 8):
+                    sel, val = B.pp_rooted_dp_f64(parent, p, k)
+                    osel, oval = oracle_mod.rooted_dp_f64(parent, p, k)
+                    assert val == oval, (tname, scale, dense, k)
+                    np.testing.assert_array_equal(sel, osel,
+                                                  err_msg=f"{tname} {scale} {dense} {k}")
+
+
 def _same(g, o):
     assert g.objective == o.objective
     np.testing.assert_array_equal(g.target, o.target)
