@@ -68,8 +68,8 @@ int stall_fail() {
 struct DevBuf {
   void* p = nullptr;
   size_t cap = 0;
-  // Grow to at least `bytes`; zero the new memory when `zero`.
-  int ensure(size_t bytes, bool zero = false) {
+  // Grow to at least `bytes`.
+  int ensure(size_t bytes) {
     if (bytes == 0) bytes = 64;
     if (bytes <= cap) return PP_OK;
     if (p) (void)hipFree(p);
@@ -79,8 +79,18 @@ struct DevBuf {
       return fail(PP_E_NOMEM, "device allocation of " + std::to_string(bytes) +
                                   " bytes failed");
     cap = bytes;
-    if (zero && hipMemset(p, 0, bytes) != hipSuccess)
-      return fail(PP_E_DEVICE, "hipMemset failed");
+    return PP_OK;
+  }
+  // The same, new memory zeroed on `st`, ahead of the work that uses it there
+  // (a clear on the null stream would not be ordered with a non-blocking
+  // stream).
+  int ensure_zeroed(size_t bytes, hipStream_t st) {
+    const size_t old = cap;
+    PP_TRY(ensure(bytes));
+    if (cap != old && hipMemsetAsync(p, 0, cap, st) != hipSuccess) {
+      release();
+      return fail(PP_E_DEVICE, "hipMemsetAsync failed");
+    }
     return PP_OK;
   }
   void release() {
@@ -784,7 +794,7 @@ int ensure_sweep(pp_ctx* c, const TreeLayout& t, DevState& d, int32_t slots, int
   PP_TRY(c->bits.ensure((size_t)slots * stages * cells * npad * 8));
   // ring words carry a launch tag; fresh memory is zeroed so that no stale
   // word can ever carry a live tag (tags start at 1)
-  PP_TRY(c->ring.ensure((size_t)slots * stages * npad * 16, true));
+  PP_TRY(c->ring.ensure_zeroed((size_t)slots * stages * npad * 16, st));
   d.bits = c->bits.as<uint64_t>();
   d.ring = c->ring.as<uint64_t>();
   d.stages = stages;

@@ -147,3 +147,34 @@ def test_plan_reduced_many(oracle_mod, monkeypatch, n, m, starts):
                               inst.cap, **kw))
         _same(B.pp_plan_f64(inst.parent, lam, w, f, inst.cap, epsilon=0.0, **kw),
               oracle_mod.plan_f64(inst.parent, lam, w, f, inst.cap, epsilon=0.0, **kw))
+
+
+def _tied(n, m, k):
+    """A flat tree of equal chunks: every core holds all of them, so the
+    reduced solve leaves every update to the sweep."""
+    parent = np.full(n, -1, np.int32)
+    lam = np.full((m, n), 3, np.int64)
+    w = np.tile(np.arange(5, 5 + m, dtype=np.int64)[:, None], (1, n))
+    f = np.full((m, m, n), 2, np.int64)
+    return parent, lam, w, f, np.full(m, k, np.int32)
+
+
+def test_plan_swept_on_a_fresh_context(oracle_mod):
+    """A sweep that is set up in the middle of a plan, its memory with it, on
+    the caller's stream."""
+    torch = pytest.importorskip("torch")
+    dev = torch.device("cuda", torch.cuda.current_device())
+    stream = torch.cuda.Stream(dev)
+    for n, k in ((3000, 700), (9001, 64), (20_000, 1500)):
+        parent, lam, w, f, cap = _tied(n, 3, k)
+        ref = oracle_mod.plan(parent, lam, w, f, cap, n_starts=2, order_seed=1)
+        dl, dw, df = (torch.from_numpy(x).to(dev) for x in (lam, w, f))
+        tgt = torch.zeros((3, n), dtype=torch.uint8, device=dev)
+        torch.cuda.synchronize()
+        ctx = B.Context(dev.index)
+        got = ctx.pp_plan_device(parent, dl, dw, df, cap, tgt, n_starts=2, order_seed=1,
+                                 stream=stream)
+        np.testing.assert_array_equal(tgt.cpu().numpy(), ref.target)
+        assert got.objective == ref.objective
+        assert got.dp_lane_cells > 0 and got.dp_restarts == 0
+        ctx.close()
