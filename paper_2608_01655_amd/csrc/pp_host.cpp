@@ -887,6 +887,15 @@ struct Engine {
   uint32_t spin_limit;
   int fmax = 0;  // every DP value < 2^62: max via v_max_f64
   int reduce_lds = 0;  // LDS of a reduced solve's block, 0: sweep every update
+  int32_t reach = 0;   // largest k' the reduced solve can settle
+  // Launches that are swept without trying the reduced solve, and how many
+  // the next hold is for.  Where the reduced solve keeps leaving its chains
+  // (tied profits, cores too wide), a launch pays it, a read-back and the
+  // sweep: after kFailsHeld such launches in a row the next kHoldFirst go
+  // straight to the sweep, twice as many after each further failure, up to
+  // kHoldMost.
+  int fails = 0, hold = 0, hold_next = kHoldFirst;
+  static constexpr int kFailsHeld = 3, kHoldFirst = 4, kHoldMost = 64;
   hipStream_t st;
   Timer timer;
 
@@ -965,53 +974,84 @@ struct Engine {
     return timer_mark(c, timer, false, st);
   }
 
-  // The sweep, walk and decision of the chains of `set` that the reduced
-  // solve left unsolved (cs[k]: chain k's state after it); *swept: how many.
-  int sweep_rest(const ChainSet& set, const ChainState* const* cs, int mode, int* swept,
-                 ChainSet* rest_out = nullptr) {
-    ChainSet rest;
-    std::memset(&rest, 0, sizeof rest);
+  static void append(ChainSet& to, const ChainSet& from, int32_t k) {
+    const int32_t q = to.count++;
+    to.slot[q] = from.slot[k];
+    to.src[q] = from.src[k];
+    to.worker[q] = from.worker[k];
+    to.kprime[q] = from.kprime[k];
+    to.row[q] = from.row[k];
+  }
+
+  // The next launch tries the reduced solve.
+  bool reducing() const { return reduce_lds && hold == 0; }
+
+  int32_t stage_blocks(const ChainSet& set) const {
+    int32_t b = 0;
     for (int32_t k = 0; k < set.count; ++k)
-      if (!cs[k]->skip && !cs[k]->solved) {
-        const int32_t q = rest.count++;
-        rest.slot[q] = set.slot[k];
-        rest.src[q] = set.src[k];
-        rest.worker[q] = set.worker[k];
-        rest.kprime[q] = set.kprime[k];
-        rest.row[q] = set.row[k];
-      }
-    *swept = rest.count;
-    if (rest.count > 0) {
-      PP_TRY(dp(rest, 1));
-      PP_HIP(launch_backtrack(rest, d, mode, st));
+      b += (set.kprime[k] + 64 * d.cells - 1) / (64 * d.cells);
+    return b;
+  }
+
+  // After a launch of `all` through the reduced solve that left `left` to the
+  // sweep: it was of no use if sweeping everything would have taken no more
+  // sweep launches.
+  void note_reduced(const ChainSet& all, const ChainSet& left) {
+    if (left.count == 0 || (stage_blocks(left) + resident - 1) / resident <
+                               (stage_blocks(all) + resident - 1) / resident) {
+      fails = 0;
+      hold_next = kHoldFirst;
+    } else if (++fails >= kFailsHeld) {
+      hold = hold_next;
+      hold_next = std::min(2 * hold_next, kHoldMost);
+      fails = kFailsHeld - 1;
     }
-    if (rest_out) *rest_out = rest;
+  }
+
+  int sweep(const ChainSet& set, int mode) {
+    if (set.count == 0) return PP_OK;
+    PP_TRY(dp(set, 1));
+    PP_HIP(launch_backtrack(set, d, mode, st));
     return PP_OK;
+  }
+
+  // The chains of `set` within the reduced solve's reach in `near`, the
+  // others in `far` (all of them where it is not in use or held off; a hold
+  // is used up by one launch).
+  void split(const ChainSet& set, ChainSet& near, ChainSet& far) {
+    std::memset(&near, 0, sizeof near);
+    std::memset(&far, 0, sizeof far);
+    const bool on = reducing();
+    if (hold > 0) --hold;
+    for (int32_t k = 0; k < set.count; ++k)
+      append(on && set.kprime[k] <= reach ? near : far, set, k);
   }
 
   // The DP of every chain of `set` (its profits are in place) and the walk.
   int solve(const ChainSet& set, int mode) {
-    if (!reduce_lds) {
-      PP_TRY(dp(set, 1));
-      PP_HIP(launch_backtrack(set, d, mode, st));
-      return PP_OK;
-    }
-    PP_TRY(reduce(set, mode));
+    ChainSet near, far, left;
+    split(set, near, far);
+    if (near.count > 0) PP_TRY(reduce(near, mode));
+    PP_TRY(sweep(far, mode));
+    if (near.count == 0) return PP_OK;
     int32_t lo = INT32_MAX, hi = -1;
-    for (int32_t k = 0; k < set.count; ++k) {
-      lo = std::min(lo, set.slot[k]);
-      hi = std::max(hi, set.slot[k]);
+    for (int32_t k = 0; k < near.count; ++k) {
+      lo = std::min(lo, near.slot[k]);
+      hi = std::max(hi, near.slot[k]);
     }
-    if (hi < lo) return PP_OK;
     const size_t span = (size_t)(hi - lo + 1);
     PP_TRY(ensure_cs_pin(c, span));
     PP_HIP(hipMemcpyAsync(c->cs_pin, d.cs + lo, sizeof(ChainState) * span,
                           hipMemcpyDeviceToHost, st));
     PP_TRY(poll_stream(st));
-    const ChainState* cs[kMaxChains];
-    for (int32_t k = 0; k < set.count; ++k) cs[k] = c->cs_pin + (set.slot[k] - lo);
-    int swept = 0;
-    return sweep_rest(set, cs, mode, &swept);
+    std::memset(&left, 0, sizeof left);
+    for (int32_t k = 0; k < near.count; ++k) {
+      const ChainState& x = c->cs_pin[near.slot[k] - lo];
+      if (!x.skip && !x.solved) append(left, near, k);
+    }
+    PP_TRY(sweep(left, mode));
+    note_reduced(near, left);
+    return PP_OK;
   }
 
   // One worker update (gains, DP, accept + backtrack, commit) for every
@@ -1270,8 +1310,14 @@ int run_safeguards(Engine& e, int32_t m, const std::vector<int32_t>& kp,
 // the next launch.  A start whose sweep has accepted an update goes on into
 // its next sweep the same way once the rest of the sweep is in the launch.
 // Results are those of the sequential sweeps.
+// A launch goes through the reduced solve with up to `reduce_budget` updates,
+// or is swept with up to `sweep_budget` and, beyond the starts' own updates,
+// at most `spec_blocks` stage blocks (all of them resident).  Of the updates
+// that the reduced solve leaves, only those that can still count are swept:
+// none after an accepted one of its start, and speculative ones only within
+// the stage blocks; a start's results end before the first that is left.
 int refine_starts(Engine& e, const std::vector<int32_t>& starts, int32_t spare_base,
-                  int32_t budget, int32_t block_budget, int32_t m,
+                  int32_t reduce_budget, int32_t sweep_budget, int32_t spec_blocks, int32_t m,
                   const std::vector<int32_t>& kp, int32_t max_rounds, PlanResult& res) {
   DevState& d = e.d;
   const int32_t A = (int32_t)starts.size();
@@ -1361,8 +1407,16 @@ int refine_starts(Engine& e, const std::vector<int32_t>& starts, int32_t spare_b
     // speculative updates: at most `budget` updates in all (one spare slot
     // each; budget - 1 spare slots exist) and, beyond the starts' own
     // updates, at most `block_budget` DP stage blocks in the launch
-    const int32_t cellsw = 64 * std::max(d.cells, 1);
-    auto blocks_of = [&](int32_t h) { return (kp[h] + cellsw - 1) / cellsw; };
+    const bool reducing = e.reducing();
+    const int32_t budget = reducing ? reduce_budget : sweep_budget;
+    int32_t block_budget = std::min(spec_blocks, e.resident);
+    auto stages_of = [&](int32_t h) {
+      const int32_t cellsw = 64 * std::max(d.cells, 1);
+      return (kp[h] + cellsw - 1) / cellsw;
+    };
+    auto blocks_of = [&](int32_t h) {
+      return reducing && kp[h] <= e.reach ? 0 : stages_of(h);
+    };
     int32_t blocks = 0;
     for (const Item& it : items) blocks += blocks_of(it.worker);
     int32_t spares = 0;
@@ -1420,12 +1474,11 @@ int refine_starts(Engine& e, const std::vector<int32_t>& starts, int32_t spare_b
       set.row[k] = rows ? d.row0 + items[k].q * m + items[k].worker : items[k].slot;
     }
     if (!rows) PP_HIP(launch_gains(set, d, e.st, kGainsMarginal, 1));
-    if (e.reduce_lds) {
-      PP_TRY(e.reduce(set, kModeRefine, rows ? 1 : 0));
-    } else {
-      PP_TRY(e.dp(set, 1));
-      PP_HIP(launch_backtrack(set, d, kModeRefine, e.st));
-    }
+    ChainSet near, far;
+    e.split(set, near, far);
+    if (near.count > 0) PP_TRY(e.reduce(near, kModeRefine, rows ? 1 : 0));
+    if (rows) PP_HIP(launch_incumbents(far, d, e.st));
+    PP_TRY(e.sweep(far, kModeRefine));
     if (d.f64) PP_HIP(launch_gexact(set, d, kModeRefine, e.st));
     // the launch's results, to pinned memory in one copy: the starts' slots
     // (consecutive) through the last spare slot used (the slots between
@@ -1445,16 +1498,55 @@ int refine_starts(Engine& e, const std::vector<int32_t>& starts, int32_t spare_b
       return PP_OK;
     };
     PP_TRY(read_states());
-    if (e.reduce_lds) {
-      const ChainState* at[kMaxChains];
-      for (int32_t k = 0; k < set.count; ++k) at[k] = &cs[k];
-      int swept = 0;
-      ChainSet rest;
-      PP_TRY(e.sweep_rest(set, at, kModeRefine, &swept, &rest));
-      if (swept > 0) {
-        if (d.f64) PP_HIP(launch_gexact(rest, d, kModeRefine, e.st));
+    // what the reduced solve left (open: not decided)
+    std::vector<char> open(items.size(), 0);
+    if (near.count > 0) {
+      ChainSet left, again;
+      std::memset(&left, 0, sizeof left);
+      std::memset(&again, 0, sizeof again);
+      for (int32_t k = 0; k < set.count; ++k)
+        if (reducing && set.kprime[k] <= e.reach && !cs[k].skip && !cs[k].solved) {
+          open[k] = 1;
+          Engine::append(left, set, k);
+        }
+      if (left.count > 0) {
+        PP_TRY(e.set_up_sweep());
+        block_budget = std::min(spec_blocks, e.resident);
+        int32_t used = 0;
+        for (int pass = 0; pass < 2; ++pass) {  // the starts' next ones first
+          int32_t q = -1;
+          bool first = true, past = false;
+          for (size_t k = 0; k < items.size(); ++k) {
+            if (items[k].q != q) {
+              q = items[k].q;
+              first = true;
+              past = false;
+            }
+            if (past) continue;
+            if (!open[k]) {
+              past = cs[k].accept != 0;
+              continue;
+            }
+            const int32_t b = stages_of(items[k].worker);
+            if (first == (pass == 0)) {
+              if (pass == 1 && used + b > block_budget) {
+                past = true;
+                continue;
+              }
+              used += b;
+              Engine::append(again, set, (int32_t)k);
+            }
+            first = false;
+          }
+        }
+        PP_TRY(e.sweep(again, kModeRefine));
+        if (d.f64) PP_HIP(launch_gexact(again, d, kModeRefine, e.st));
         PP_TRY(read_states());
+        for (int32_t k = 0; k < again.count; ++k)
+          for (size_t i = 0; i < items.size(); ++i)
+            if (items[i].slot == again.slot[k]) open[i] = 0;
       }
+      e.note_reduced(near, left);
     }
     // decisions, in each start's order
     std::vector<int32_t> csl, cwk, ckp;
@@ -1466,13 +1558,17 @@ int refine_starts(Engine& e, const std::vector<int32_t>& starts, int32_t spare_b
       uint32_t ran[8] = {0, 0, 0, 0, 0, 0, 0, 0};
       const Item* take = nullptr;
       int32_t last = x.pos - 1;  // last position resolved in this launch
-      bool in_next = false;
+      bool in_next = false, cut = false;
       for (; k < items.size() && items[k].q == q; ++k) {
         const Item& it = items[k];
         const ChainState& c = cs[k];
         if (c.status) return stall_fail();
-        if (take) {  // computed against a placement that has changed
-          if (!c.skip) res.spec_cells += (int64_t)d.n * kp[it.worker];
+        if (take || cut) {  // computed against a placement that has changed
+          if (!c.skip && !open[k]) res.spec_cells += (int64_t)d.n * kp[it.worker];
+          continue;
+        }
+        if (open[k]) {  // not decided: the start goes on from here
+          cut = true;
           continue;
         }
         if (it.next && !in_next) {
@@ -1586,10 +1682,6 @@ int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) ==
             hipSuccess && cus > 0)
       spec_blocks = 3 * cus;
-    // (reduced solves have no stages: kSpecChains updates.  8, 16, 24 and 32
-    // took 18.1, 17.0, 20.5 and 20.6 ms at n = 50,000 and 4.1, 3.8, 3.7 and
-    // 3.7 ms at n = 10,000: past 16 the ladder has half the rungs)
-    if (reduce_lds_for(t, c->device)) spec_blocks = INT32_MAX;
     spec_blocks = env_int("PP_SPEC_BLOCKS", spec_blocks);
   }
   // speculative refinement: up to kSpecChains updates per launch (each
@@ -1598,14 +1690,20 @@ int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
   // many chains of the widest capacity (stages at one cell per lane) fit
   // the launch's stage blocks -- small capacities, whose launches take the
   // same time with more chains
+  // (reduced solves have no stages: kSpecChains updates.  8, 16, 24 and 32
+  // took 18.1, 17.0, 20.5 and 20.6 ms at n = 50,000 and 4.1, 3.8, 3.7 and
+  // 3.7 ms at n = 10,000: past 16 the ladder has half the rungs)
   const int32_t wide_stages = std::max(1, (kmax + 63) / 64);
-  const int32_t spec_default =
-      spec_blocks < INT32_MAX && 2 * kSpecChains * wide_stages <= spec_blocks ? 2 * kSpecChains
-                                                                              : kSpecChains;
-  const int32_t spec_chains =  // updates per refinement launch
-      env_int("PP_NO_SPEC", 0) ? 1
-                               : std::max(1, std::min(kMaxChains, env_int("PP_SPEC_CHAINS",
-                                                                          spec_default)));
+  auto spec_of = [&](int32_t dflt) {  // updates per refinement launch
+    return env_int("PP_NO_SPEC", 0)
+               ? 1
+               : std::max(1, std::min(kMaxChains, env_int("PP_SPEC_CHAINS", dflt)));
+  };
+  const int reduce_lds = reduce_lds_for(t, c->device);
+  const int32_t sweep_budget =
+      spec_of(2 * kSpecChains * wide_stages <= spec_blocks ? 2 * kSpecChains : kSpecChains);
+  const int32_t reduce_budget = reduce_lds ? spec_of(kSpecChains) : 1;
+  const int32_t spec_chains = std::max(sweep_budget, reduce_budget);
   const int32_t spare_base = slot_b + (sg_asked ? 4 : 0) + extra_slots;
   const int32_t slots = spare_base + (spec_chains > 1 ? spec_chains - 1 : 0);
   res.extra_slot = extra_slots > 0 ? slot_b + (sg_asked ? 4 : 0) : -1;
@@ -1643,7 +1741,8 @@ int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
       d.role_max_blocks = 4 * cus;
   }
   e.fmax = fmax_ok && env_int("PP_DP_NO_FMAX", 0) == 0;
-  e.reduce_lds = reduce_lds_for(t, c->device);
+  e.reduce_lds = reduce_lds;
+  if (reduce_lds) e.reach = reduce_reach(n, f64 ? 1 : 0, reduce_lds);
   res.fmax = (e.fmax || f64) ? 1 : 0;
   // profit rows of every (start, worker) of a refinement batch, unless they
   // take more than kRowBytes or nothing is refined
@@ -1658,8 +1757,9 @@ int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
     PP_TRY(ensure_exact(c, d, slots));
   }
   if (e.reduce_lds) PP_TRY(ensure_reduce(c, t, d, slots, st, rows));
-  // trees whose tables are laid out already (see build_tree)
-  if (!e.reduce_lds || !t.ce.empty()) PP_TRY(e.set_up_sweep());
+  // trees whose tables are laid out already (see build_tree), and capacities
+  // that are swept
+  if (!e.reduce_lds || !t.ce.empty() || kmax > e.reach) PP_TRY(e.set_up_sweep());
 
   // --- standalone scores: each worker against the empty placement
   res.standalone.assign(m, 0);
@@ -1719,10 +1819,12 @@ int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
     std::vector<int32_t> active;
     for (int32_t s = lo; s < hi; ++s) active.push_back(s);
     {
-      std::vector<int32_t> sl(active);
-      for (int32_t q = spare_base; q < slots; ++q) sl.push_back(q);
-      std::vector<int32_t> wk(sl.size(), 0), kk(sl.size(), 0);
-      PP_HIP(launch_init_slots(chain_set(sl, wk, kk, 0, sl.size()), d, 1, st));
+      const std::vector<int32_t> z(active.size(), 0);
+      PP_HIP(launch_init_slots(chain_set(active, z, z, 0, z.size()), d, 1, st));
+      // spare slots hold no placement
+      if (slots > spare_base)
+        PP_HIP(hipMemsetAsync(d.cs + spare_base, 0, sizeof(ChainState) * (slots - spare_base),
+                              st));
     }
     auto position_set = [&](const std::vector<int32_t>& act, int32_t a) {
       std::vector<int32_t> sl, wk, kk;
@@ -1743,8 +1845,7 @@ int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
     for (int32_t a = 1; a < m; ++a)
       PP_TRY(e.update(position_set(active, a), kModeGreedy));
     if (!(o.flags & PP_F_NO_REFINE))
-      PP_TRY(refine_starts(e, active, spare_base, spec_chains,
-                           e.reduce_lds ? spec_blocks : std::min(spec_blocks, e.resident), m, kp,
+      PP_TRY(refine_starts(e, active, spare_base, reduce_budget, sweep_budget, spec_blocks, m, kp,
                            o.max_rounds, res));
     std::vector<int32_t> sl, wk, kk;
     for (int32_t s = lo; s < hi; ++s) {
@@ -2590,7 +2691,8 @@ static int rooted_dp_impl(int32_t n, const int32_t* parent, const void* profit_v
     e.stage64 = (kp + 63) / 64;
     e.fmax = tot < kFmaxBound && env_int("PP_DP_NO_FMAX", 0) == 0;
     e.reduce_lds = reduce_lds;
-    if (!reduce_lds || !t.ce.empty()) PP_TRY(e.set_up_sweep());
+    if (reduce_lds) e.reach = reduce_reach(n, f64 ? 1 : 0, reduce_lds);
+    if (!reduce_lds || !t.ce.empty() || kp > e.reach) PP_TRY(e.set_up_sweep());
     std::vector<uint32_t> pre(d.npad / 32);
     ChainState out{};
     for (int attempt = 0;; ++attempt) {  // again, with a longer wait, if it stalled

@@ -330,6 +330,12 @@ size_t ladder_lds(int32_t nlv, int32_t levels, int32_t leaf0);
 // launch_gains.  lds: dynamic LDS bytes per block.
 hipError_t launch_reduce(const ChainSet& set, const DevState& d, int mode, int prep, int lds,
                          hipStream_t st);
+// Only the incumbents' values (prep), for chains that go straight to the sweep.
+hipError_t launch_incumbents(const ChainSet& set, const DevState& d, hipStream_t st);
+// The largest k' that a block of `lds` bytes can settle on trees of n nodes: n
+// where the node list holds every node, else as many chunks as leave room for
+// the nodes needed above price 0 and, real-valued, a row per forced node.
+int32_t reduce_reach(int32_t n, int f64, int lds);
 
 // Host-side launchers (pp_kernels.hip).  All enqueue on `st`.
 hipError_t launch_gather(const int64_t* src, int64_t* dst, int32_t rows,

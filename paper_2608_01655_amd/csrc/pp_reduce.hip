@@ -69,6 +69,9 @@ constexpr int kMaxSearch = 40;  // evaluations of one price search
 constexpr uint32_t kNone = 0xFFFFu;
 constexpr int kChunks = kReduceActive / kRThreads;
 
+// The active nodes a solve of k' chunks asks for above price 0.
+__host__ __device__ constexpr int64_t nodes_needed(int64_t kp) { return kp + kp / 16 + 160; }
+
 // Bins of the entry widths: exact below 4, then four per factor of two.
 constexpr int kWidthBins = 256;
 __device__ __forceinline__ int width_bin(int64_t a) {
@@ -612,7 +615,7 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
   }
   __syncthreads();
   // the highest rung with clearly more than k' nodes, else price 0
-  const int need = kp + kp / 16 + 160;
+  const int need = (int)nodes_needed(kp);
   int j = 0;
   while (j < rungs - 1 && count[j] < need && price[j] > 0.0) ++j;
   const int nwords = d.npad / 32;
@@ -1120,6 +1123,38 @@ size_t reduce_lds_min(int32_t n, int32_t nlv, int32_t levels, int32_t leaf0) {
   const size_t solve = kReduceRedBytes + 4 * nw + 16 + 4 * (size_t)kReduceActive +
                        12 * (size_t)nlv / 64 + 64;
   return std::max(solve, ladder_lds(nlv, levels, leaf0));
+}
+
+int32_t reduce_reach(int32_t n, int f64, int lds) {
+  const int64_t nw = ((int64_t)n + 31) / 32;
+  const int64_t wbytes = lds - ((kReduceRedBytes + 4 * nw + 15) & ~(int64_t)15);
+  const int64_t acap = std::min<int64_t>(kReduceActive, wbytes / 8 - 4);
+  if (n <= acap) return n;
+  auto fits = [&](int64_t kp) {
+    const int64_t a = nodes_needed(kp);
+    // child sums, core nodes as found, one row of the core's table;
+    // real-valued costs: a row per forced node and the rows' bitmaps
+    return a <= acap &&
+           8 * a + 4 * kCoreMax + 512 + (f64 ? 12 * kp + 8 * nw : 0) <= wbytes;
+  };
+  int64_t lo = 0, hi = n;  // fits(lo)
+  while (lo < hi) {
+    const int64_t k = (lo + hi + 1) / 2;
+    if (fits(k)) lo = k;
+    else hi = k - 1;
+  }
+  return (int32_t)lo;
+}
+
+hipError_t launch_incumbents(const ChainSet& set, const DevState& d, hipStream_t st) {
+  if (set.count == 0) return hipSuccess;
+  if (d.f64)
+    hipLaunchKernelGGL(k_ladder<true>, dim3(set.count), dim3(kRThreads), kReduceRedBytes, st, set,
+                       d, 0, 1);
+  else
+    hipLaunchKernelGGL(k_ladder<false>, dim3(set.count), dim3(kRThreads), kReduceRedBytes, st, set,
+                       d, 0, 1);
+  return hipGetLastError();
 }
 
 hipError_t launch_reduce(const ChainSet& set, const DevState& d, int mode, int prep, int lds,

@@ -178,3 +178,69 @@ def test_plan_swept_on_a_fresh_context(oracle_mod):
         assert got.objective == ref.objective
         assert got.dp_lane_cells > 0 and got.dp_restarts == 0
         ctx.close()
+
+
+def _deep_caps(n, m, k, seed):
+    rng = np.random.default_rng(seed)
+    parent = _gw(n, rng)
+    lam = rng.integers(1, 1000, size=(m, n))
+    w = rng.integers(1, 1000, size=(m, n))
+    f = rng.integers(0, 1000, size=(m, m, n))
+    return parent, lam, w, f, np.full(m, k, np.int32)
+
+
+@pytest.mark.parametrize("case", ["reach", "reach_f64", "tied", "tied_f64"])
+def test_plan_beyond_the_reduced_solve(oracle_mod, monkeypatch, case):
+    """Capacities that the reduced solve cannot hold go straight to the sweep,
+    and a plan whose chains it keeps leaving stops trying: no more solve
+    launches than the swept plan but for a few tries, and no more cells."""
+    f64 = case.endswith("f64")
+    if case.startswith("tied"):
+        x = _tied(3000, 8, 200)
+    else:
+        x = _deep_caps(16_500, 2, 7_600 if f64 else 15_000, 5)
+    if f64:
+        rng = np.random.default_rng(3)
+        scale = 1.0 if case == "tied_f64" else rng.uniform(0.5, 1.5, size=x[1].shape)
+        x = (x[0], x[1] * scale, x[2] / 1000.0, x[3] / 1000.0, x[4])
+        run = lambda **kw: B.pp_plan_f64(*x, epsilon=0.0, **kw)
+        ref = lambda **kw: oracle_mod.plan_f64(*x, epsilon=0.0, **kw)
+    else:
+        run = lambda **kw: B.pp_plan(*x, **kw)
+        ref = lambda **kw: oracle_mod.plan(*x, **kw)
+    kw = dict(n_starts=1 if case.startswith("reach") else 4, order_seed=2)
+    got = run(flags=B.PP_F_TIME_KERNELS, **kw)
+    _same(got, ref(**kw))
+    assert got.dp_lane_cells > 0
+    monkeypatch.setenv("PP_REDUCE_MIN_N", str(1 << 30))
+    swept = run(flags=B.PP_F_TIME_KERNELS, **kw)
+    _same(got, swept)
+    tries = 0 if case.startswith("reach") else 3 + swept.dp_launches // 4
+    assert swept.dp_launches <= got.dp_launches <= swept.dp_launches + tries
+    assert got.dp_cells_executed <= swept.dp_cells_executed
+
+
+@pytest.mark.parametrize("blocks", ["1", "4", "1000"])
+def test_refinement_of_left_updates(oracle_mod, monkeypatch, blocks):
+    """Refinement launches with solved and left updates side by side, and more
+    left ones than are swept at once: half of the tree is tied."""
+    monkeypatch.setenv("PP_SPEC_BLOCKS", blocks)
+    for seed in range(6):
+        rng = np.random.default_rng(100 + seed)
+        n, m = int(rng.integers(1500, 2500)), 5
+        half = n // 2
+        parent = np.concatenate([_gw(half, rng), np.full(n - half, -1, np.int32)])
+        lam = rng.integers(1, 50, size=(m, n))
+        lam[seed % m, half:] = 40
+        w = rng.integers(1, 50, size=(m, n))
+        w[:, half:] = 30
+        f = rng.integers(0, 40, size=(m, m, n))
+        f[:, :, half:] = 7
+        lam[:, half:] = lam[:, half:half + 1]
+        cap = rng.integers(20, 200, size=m).astype(np.int32)
+        kw = dict(n_starts=int(rng.integers(1, 6)), order_seed=seed, max_rounds=4)
+        _same(B.pp_plan(parent, lam, w, f, cap, **kw),
+              oracle_mod.plan(parent, lam, w, f, cap, **kw))
+        x = (lam * 1.0, w / 8.0, f / 8.0, cap)
+        _same(B.pp_plan_f64(parent, *x, epsilon=0.0, **kw),
+              oracle_mod.plan_f64(parent, *x, epsilon=0.0, **kw))
