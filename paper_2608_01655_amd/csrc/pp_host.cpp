@@ -891,11 +891,11 @@ struct Engine {
   // Launches that are swept without trying the reduced solve, and how many
   // the next hold is for.  Where the reduced solve keeps leaving its chains
   // (tied profits, cores too wide), a launch pays it, a read-back and the
-  // sweep: after kFailsHeld such launches in a row the next kHoldFirst go
-  // straight to the sweep, twice as many after each further failure, up to
-  // kHoldMost.
+  // sweep: after one launch of which it settles no chain, or kFailsHeld in a
+  // row that are of no use, the next kHoldFirst go straight to the sweep,
+  // twice as many after each further failure, up to kHoldMost.
   int fails = 0, hold = 0, hold_next = kHoldFirst;
-  static constexpr int kFailsHeld = 3, kHoldFirst = 4, kHoldMost = 64;
+  static constexpr int kFailsHeld = 3, kHoldFirst = 8, kHoldMost = 64;
   hipStream_t st;
   Timer timer;
 
@@ -1001,7 +1001,7 @@ struct Engine {
                                (stage_blocks(all) + resident - 1) / resident) {
       fails = 0;
       hold_next = kHoldFirst;
-    } else if (++fails >= kFailsHeld) {
+    } else if (++fails >= kFailsHeld || left.count == all.count) {
       hold = hold_next;
       hold_next = std::min(2 * hold_next, kHoldMost);
       fails = kFailsHeld - 1;
@@ -1699,7 +1699,19 @@ int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
                ? 1
                : std::max(1, std::min(kMaxChains, env_int("PP_SPEC_CHAINS", dflt)));
   };
-  const int reduce_lds = reduce_lds_for(t, c->device);
+  // Where more than an eighth of the workers hold more than the reduced solve
+  // can settle, nearly every launch of 16 updates has one to sweep, and the
+  // others cost less in that sweep than in launches of their own (n = 50,000,
+  // 8 starts, k = 1,000 and 16,000 for 1, 2 and 4 of 16 workers: 172, 257 and
+  // 329 ms with both, 234, 261 and 319 ms swept; 8 workers with 8,000 to
+  // 20,000: 114 and 104 ms)
+  int reduce_lds = reduce_lds_for(t, c->device);
+  int32_t reach = 0;
+  if (reduce_lds) {
+    reach = reduce_reach(n, f64 ? 1 : 0, reduce_lds);
+    const auto far = std::count_if(kp.begin(), kp.end(), [&](int32_t k) { return k > reach; });
+    if (8 * far > m) reduce_lds = 0;
+  }
   const int32_t sweep_budget =
       spec_of(2 * kSpecChains * wide_stages <= spec_blocks ? 2 * kSpecChains : kSpecChains);
   const int32_t reduce_budget = reduce_lds ? spec_of(kSpecChains) : 1;
@@ -1742,7 +1754,7 @@ int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
   }
   e.fmax = fmax_ok && env_int("PP_DP_NO_FMAX", 0) == 0;
   e.reduce_lds = reduce_lds;
-  if (reduce_lds) e.reach = reduce_reach(n, f64 ? 1 : 0, reduce_lds);
+  e.reach = reach;
   res.fmax = (e.fmax || f64) ? 1 : 0;
   // profit rows of every (start, worker) of a refinement batch, unless they
   // take more than kRowBytes or nothing is refined
@@ -2672,7 +2684,9 @@ static int rooted_dp_impl(int32_t n, const int32_t* parent, const void* profit_v
     d.nextpos = c->nextpos;
     d.f64 = f64 ? 1 : 0;
     PP_TRY(ensure_slots(c, d, 1));
-    const int reduce_lds = reduce_lds_for(t, c->device);
+    int reduce_lds = reduce_lds_for(t, c->device);
+    const int32_t reach = reduce_lds ? reduce_reach(n, f64 ? 1 : 0, reduce_lds) : 0;
+    if (kp > reach) reduce_lds = 0;
     if (reduce_lds) PP_TRY(ensure_reduce(c, t, d, 1, st));
     PP_TRY(c->up_lam.ensure((size_t)n * 8));
     PP_HIP(hipMemcpyAsync(c->up_lam.p, profit, (size_t)n * 8, hipMemcpyHostToDevice, st));
@@ -2691,8 +2705,8 @@ static int rooted_dp_impl(int32_t n, const int32_t* parent, const void* profit_v
     e.stage64 = (kp + 63) / 64;
     e.fmax = tot < kFmaxBound && env_int("PP_DP_NO_FMAX", 0) == 0;
     e.reduce_lds = reduce_lds;
-    if (reduce_lds) e.reach = reduce_reach(n, f64 ? 1 : 0, reduce_lds);
-    if (!reduce_lds || !t.ce.empty() || kp > e.reach) PP_TRY(e.set_up_sweep());
+    if (reduce_lds) e.reach = reach;
+    if (!reduce_lds || !t.ce.empty()) PP_TRY(e.set_up_sweep());
     std::vector<uint32_t> pre(d.npad / 32);
     ChainState out{};
     for (int attempt = 0;; ++attempt) {  // again, with a longer wait, if it stalled

@@ -220,6 +220,17 @@ def test_plan_beyond_the_reduced_solve(oracle_mod, monkeypatch, case):
     assert got.dp_cells_executed <= swept.dp_cells_executed
 
 
+def test_plan_with_one_far_worker(oracle_mod):
+    """One worker of eight beyond the reduced solve's reach: its updates are
+    swept next to the others' reduced solves."""
+    parent, lam, w, f, cap = _deep_caps(16_500, 8, 60, 6)
+    cap[3] = 14_800
+    kw = dict(n_starts=2, order_seed=2, max_rounds=2)
+    got = B.pp_plan(parent, lam, w, f, cap, **kw)
+    _same(got, oracle_mod.plan(parent, lam, w, f, cap, **kw))
+    assert got.dp_lane_cells > 0
+
+
 @pytest.mark.parametrize("blocks", ["1", "4", "1000"])
 def test_refinement_of_left_updates(oracle_mod, monkeypatch, blocks):
     """Refinement launches with solved and left updates side by side, and more
