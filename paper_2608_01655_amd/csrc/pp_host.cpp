@@ -145,16 +145,19 @@ struct TreeLayout {
 int layout_sweep(TreeLayout& t);
 int layout_sweep_spilled(TreeLayout& t, int32_t pad, int32_t nsteps);
 void layout_levels(TreeLayout& t, const int32_t* parent, const std::vector<int32_t>& posof,
-                   const std::vector<int32_t>& head);
+                   const std::vector<int32_t>& head, int32_t k);
+int env_int(const char* name, int dflt);
 
 int layout_sweep_tables(TreeLayout& t);
 
-// kmax >= 0: a call whose updates the reduced solve may settle, with
-// capacities up to kmax: the sweep's tables are left for when one needs it
-// (layout_sweep_tables), on trees where neither they nor the sweep's launch
-// can be refused -- at most 64 levels, so at most 64 + 16 LDS rows, three
-// stage blocks per compute unit and 64 columns each.
-int build_tree(int32_t n, const int32_t* parent, TreeLayout& t, int32_t kmax = -1) {
+// cap != nullptr: a call that solves, with these m capacities.  Where the
+// reduced solve may settle its updates (layout_levels), the sweep's tables are
+// left for when one needs it (layout_sweep_tables), on trees where neither
+// they nor the sweep's launch can be refused -- no node deeper than 64, so at
+// most 65 + 16 LDS rows, three stage blocks per compute unit and 64 columns
+// each.
+int build_tree(int32_t n, const int32_t* parent, TreeLayout& t, const int32_t* cap = nullptr,
+               int32_t m = 0) {
   for (int32_t v = 0; v < n; ++v) {
     const int32_t p = parent[v];
     if (p < -1 || p >= n || p == v)
@@ -196,8 +199,18 @@ int build_tree(int32_t n, const int32_t* parent, TreeLayout& t, int32_t kmax = -
     t.nextpos[q] = q + size[q];
     if (t.order[q] != q) t.identity = false;
   }
-  layout_levels(t, parent, posof, head);
-  if (kmax >= 0 && kmax <= 32768 && !t.lvtab.empty() && t.max_depth <= 64) return PP_OK;
+  if (cap) {
+    int64_t sum = 0;
+    int32_t kmax = 0, count = 0;
+    for (int32_t h = 0; h < m; ++h) {
+      const int32_t k = std::min(cap[h], n);
+      kmax = std::max(kmax, k);
+      sum += k;
+      count += k > 0 ? 1 : 0;
+    }
+    layout_levels(t, parent, posof, head, count > 0 ? (int32_t)(sum / count) : 0);
+    if (kmax <= 32768 && !t.lvtab.empty() && t.max_depth <= 64) return PP_OK;
+  }
   return layout_sweep_tables(t);
 }
 
@@ -225,14 +238,41 @@ int layout_sweep_tables(TreeLayout& t) {
   return layout_sweep(t);
 }
 
-// Level order for the reduced solve, left empty beyond its limits: depth,
+// Whether the reduced solve is the faster one, by nodes, depth of the deepest
+// node and (mean) capacity.  A sweep takes n row steps; a reduced solve a few
+// passes with a barrier per level, several of them, and on few, deep nodes it
+// also needs wider cores, up to as many rows as there are nodes.  Whole plans
+// of 6 workers and 4 starts (integer costs), reduced against swept:
+//   depth 5    n = 1,024 / 1,448 / 2,048, k = 4%: 1.58 / 1.49 / 1.47 against
+//              1.28 / 1.59 / 1.99 ms
+//   depth 10   1.70 / 1.36 / 1.71 against 1.20 / 1.28 / 2.14 ms
+//   depth 32   n = 2,048 / 2,896 / 4,096: 3.93 / 2.35 / 2.85 against
+//              1.84 / 2.53 / 3.97 ms
+//   depth 60   n = 5,792 / 8,192 / 11,585: 5.28 / 8.33 / 5.50 against
+//              5.03 / 7.03 / 9.26 ms
+//   depth 90   n = 8,192 / 23,170: 7.63 / 8.00 against 6.70 / 17.9 ms
+// A few chunks per worker leave a gap that is a large part of a price, so
+// cores are wide or fail: k = 20 of 2,048 and 28 of 2,896 at depth 10: 3.21
+// and 2.68 against 1.75 and 1.78 ms, k = 17 of 5,792 2.90 against 3.59; k = 24
+// of 8,192 at depth 32 5.57 against 4.76 ms, k = 60 of 20,000 2.99 against
+// 11.6.  One solve on host arrays crosses at the same sizes.
+// PP_REDUCE_MIN_N (a test hook) asks for it from that many nodes on.
+bool reduce_pays(int32_t n, int32_t depth, int32_t k) {
+  const int forced = env_int("PP_REDUCE_MIN_N", -1);
+  if (forced >= 0) return n >= forced;
+  const int64_t line = 1500 + 2 * (int64_t)depth * depth;
+  return n >= (k >= 30 + 3 * depth / 4 ? line : 3 * line);
+}
+
+// Level order for the reduced solve, left empty where the sweep is faster
+// (reduce_pays, k: mean capacity) and beyond the solve's limits: depth,
 // nodes, 16-bit internal numbers, and child sums of k_ladder that fit 31
 // bits with at least 8 bits below one price (its clip is more than one price
 // per level, and a node adds up to max degree + 1 clipped values).
 void layout_levels(TreeLayout& t, const int32_t* parent, const std::vector<int32_t>& posof,
-                   const std::vector<int32_t>& head) {
+                   const std::vector<int32_t>& head, int32_t k) {
   const int32_t n = t.n;
-  if (n > kLadderSlots) return;
+  if (n > kLadderSlots || !reduce_pays(n, 0, INT32_MAX)) return;
   std::vector<uint8_t> depth(n);
   int32_t maxd = 0;
   int64_t maxdeg = 0;
@@ -244,6 +284,7 @@ void layout_levels(TreeLayout& t, const int32_t* parent, const std::vector<int32
     maxd = std::max(maxd, dep);
     maxdeg = std::max<int64_t>(maxdeg, head[v + 1] - head[v]);
   }
+  if (!reduce_pays(n, maxd, k)) return;
   t.max_depth = maxd;
   const int64_t clip = ((int64_t)1 << 31) / (maxdeg + 2) - 4;
   int bits = 0;
@@ -1105,19 +1146,14 @@ int choose_cells(int32_t total_stage_cells_c1, int dev, int32_t slots_lds) {
 }
 
 // Dynamic LDS of a reduced solve's block on this tree, 0 where every update
-// is swept: trees of at least kReduceMinN nodes (below, the n row steps of a
-// sweep take less than the reduced solve's fixed passes; whole plans of 4
-// workers and 4 starts, reduced against swept: 512 nodes 1.1-1.6 against
-// 0.53-0.89 ms, 1,023 nodes 1.1-1.3 against 0.87-1.27 ms, 2,000 nodes 1.21
-// against 1.60-1.87 ms, 4,000 nodes 1.22-1.33 against 2.5-3.5 ms) with a level order
-// whose tables fit.  Forcing the sweep's lane width or its spin limit (test
-// hooks) asks for the sweep itself.
-constexpr int32_t kReduceMinN = 1024;
+// is swept: trees without a level order, or whose tables do not fit.  Forcing
+// the sweep's lane width or its spin limit (test hooks) asks for the sweep
+// itself.
 // device memory a batch's profit rows may take (12 bytes per chunk)
 constexpr int64_t kRowBytes = (int64_t)4 << 30;
 int reduce_lds_for(const TreeLayout& t, int dev) {
   if (std::getenv("PP_DP_CELLS") || std::getenv("PP_SPIN_LIMIT")) return 0;
-  if (t.lvtab.empty() || t.n < env_int("PP_REDUCE_MIN_N", kReduceMinN)) return 0;
+  if (t.lvtab.empty()) return 0;
   int lds = 0;
   if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
     return 0;
@@ -1970,10 +2006,6 @@ int check_values_f64(int32_t n, int32_t m, const double* lam, const double* w,
   return PP_OK;
 }
 
-int32_t max_cap(int32_t m, const int32_t* cap) {
-  return *std::max_element(cap, cap + m);
-}
-
 int check_f64_options(double eps) {
   if (!finite_nonneg(eps)) return fail(PP_E_ARG, "epsilon must be finite and >= 0");
   return PP_OK;
@@ -2449,7 +2481,7 @@ int pp_plan_device(pp_ctx* ctx, int32_t n, int32_t m, const int32_t* parent,
                            ctx->partial.as<uint64_t>(), &nb, st));
     PP_HIP(hipMemcpyAsync(ctx->val_pin, ctx->partial.p, 16 * (size_t)nb,
                           hipMemcpyDeviceToHost, st));
-    const int trc = build_tree(n, parent, t, max_cap(m, cap));
+    const int trc = build_tree(n, parent, t, cap, m);
     if (trc != PP_OK) {
       PP_TRY(poll_stream(st));
       return trc;
@@ -2493,7 +2525,7 @@ int pp_plan(int32_t n, int32_t m, const int32_t* parent, const int64_t* demand,
     unsigned __int128 tot = 0;
     PP_TRY(check_values(n, m, demand, recompute_cost, fetch_cost, &tot));
     TreeLayout t;
-    PP_TRY(build_tree(n, parent, t, o.flags & PP_F_VALIDATE_ONLY ? -1 : max_cap(m, cap)));
+    PP_TRY(build_tree(n, parent, t, o.flags & PP_F_VALIDATE_ONLY ? nullptr : cap, m));
     if (o.flags & PP_F_VALIDATE_ONLY) return PP_OK;
     int rc = PP_OK;
     pp_ctx* c = thread_ctx(rc);
@@ -2536,7 +2568,7 @@ int pp_plan_f64_device(pp_ctx* ctx, int32_t n, int32_t m, const int32_t* parent,
                                ctx->partial.as<uint64_t>(), &nb, st));
     PP_HIP(hipMemcpyAsync(ctx->val_pin, ctx->partial.p, 8 * (size_t)nb,
                           hipMemcpyDeviceToHost, st));
-    const int trc = build_tree(n, parent, t, max_cap(m, cap));
+    const int trc = build_tree(n, parent, t, cap, m);
     if (trc != PP_OK) {
       PP_TRY(poll_stream(st));
       return trc;
@@ -2575,7 +2607,7 @@ int pp_plan_f64(int32_t n, int32_t m, const int32_t* parent, const double* deman
       if (cap[h] < 0) return fail(PP_E_RANGE, "negative capacity");
     PP_TRY(check_values_f64(n, m, demand, recompute_cost, fetch_cost));
     TreeLayout t;
-    PP_TRY(build_tree(n, parent, t, o.flags & PP_F_VALIDATE_ONLY ? -1 : max_cap(m, cap)));
+    PP_TRY(build_tree(n, parent, t, o.flags & PP_F_VALIDATE_ONLY ? nullptr : cap, m));
     if (o.flags & PP_F_VALIDATE_ONLY) return PP_OK;
     int rc = PP_OK;
     pp_ctx* c = thread_ctx(rc);
@@ -2612,7 +2644,7 @@ int pp_replan(int32_t n, int32_t m, const int32_t* parent, const int64_t* demand
     unsigned __int128 tot = 0;
     PP_TRY(check_values(n, m, demand, recompute_cost, fetch_cost, &tot));
     TreeLayout t;
-    PP_TRY(build_tree(n, parent, t, o.flags & PP_F_VALIDATE_ONLY ? -1 : max_cap(m, cap)));
+    PP_TRY(build_tree(n, parent, t, o.flags & PP_F_VALIDATE_ONLY ? nullptr : cap, m));
     if (o.flags & PP_F_VALIDATE_ONLY) return PP_OK;
     int rc = PP_OK;
     pp_ctx* c = thread_ctx(rc);
@@ -2665,7 +2697,7 @@ static int rooted_dp_impl(int32_t n, const int32_t* parent, const void* profit_v
         return fail(PP_E_OVERFLOW, "sum of profits exceeds INT64_MAX");
     }
     TreeLayout t;
-    PP_TRY(build_tree(n, parent, t, k));
+    PP_TRY(build_tree(n, parent, t, &k, 1));
     const int32_t kp = std::min(k, n);
     if (kp == 0) {
       std::memset(selected, 0, n);
@@ -2747,7 +2779,7 @@ int pp_replan_f64(int32_t n, int32_t m, const int32_t* parent, const double* dem
       if (incumbent[x] > 1) return fail(PP_E_ARG, "incumbent entries must be 0 or 1");
     PP_TRY(check_values_f64(n, m, demand, recompute_cost, fetch_cost));
     TreeLayout t;
-    PP_TRY(build_tree(n, parent, t, o.flags & PP_F_VALIDATE_ONLY ? -1 : max_cap(m, cap)));
+    PP_TRY(build_tree(n, parent, t, o.flags & PP_F_VALIDATE_ONLY ? nullptr : cap, m));
     if (o.flags & PP_F_VALIDATE_ONLY) return PP_OK;
     int rc = PP_OK;
     pp_ctx* c = thread_ctx(rc);

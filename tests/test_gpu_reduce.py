@@ -255,3 +255,32 @@ def test_refinement_of_left_updates(oracle_mod, monkeypatch, blocks):
         x = (lam * 1.0, w / 8.0, f / 8.0, cap)
         _same(B.pp_plan_f64(parent, *x, epsilon=0.0, **kw),
               oracle_mod.plan_f64(parent, *x, epsilon=0.0, **kw))
+
+
+@pytest.mark.parametrize("tree,n,k,swept", [
+    ("gw", 1_300, 100, True),      # few nodes
+    ("gw", 2_000, 256, False),
+    ("gw", 4_000, 12, True),       # a few chunks per worker
+    ("gw", 20_000, 200, False),
+    ("chat", 5_000, 400, True),    # deep for its size
+    ("chat", 20_000, 1_500, False),
+    ("forest", 1_499, 300, True)])
+def test_which_trees_are_reduced(oracle_mod, monkeypatch, tree, n, k, swept):
+    """The choice by nodes, depth and capacity, on both sides of its lines."""
+    monkeypatch.delenv("PP_REDUCE_MIN_N")
+    rng = np.random.default_rng(n)
+    if tree == "gw":
+        parent = _gw(n, rng)
+    elif tree == "chat":
+        parent = W._relabel_preorder(W.chain_tree(n, (7 * n) // 10, 2.2, 16, 64, rng))[0]
+    else:
+        parent = W.random_forest(n, rng)
+    m = 2
+    lam = rng.integers(1, 10 ** 6, size=(m, n))
+    w = rng.integers(1, 10 ** 6, size=(m, n))
+    f = rng.integers(0, 10 ** 6, size=(m, m, n))
+    cap = np.full(m, k, np.int32)
+    kw = dict(n_starts=1, max_rounds=1)
+    got = B.pp_plan(parent, lam, w, f, cap, **kw)
+    _same(got, oracle_mod.plan(parent, lam, w, f, cap, **kw))
+    assert (got.dp_lane_cells > 0) == swept
