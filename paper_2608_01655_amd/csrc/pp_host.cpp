@@ -683,11 +683,13 @@ struct pp_ctx {
   // problem, preorder layout
   DevBuf lam, w, f, meta;
   // tree tables in one allocation (one upload): next positions, preorder
-  // (position -> caller id); the backtrack's skip-chain table in `ce`, the
-  // reduced solve's level order in `lvl`
+  // (position -> caller id) and, where the sweep's tables are laid out by
+  // then, the backtrack's skip-chain table (else it goes to `ce` when a sweep
+  // is set up); the reduced solve's level order in `lvl`
   DevBuf tree;
   int32_t* nextpos = nullptr;
   int32_t* order = nullptr;
+  uint32_t* chains = nullptr;  // the skip-chain table, once uploaded
   // uploads for host-pointer entry points (caller order)
   DevBuf up_lam, up_w, up_f, up_u8;
   // per-slot state
@@ -840,9 +842,12 @@ int ensure_sweep(pp_ctx* c, const TreeLayout& t, DevState& d, int32_t slots, int
   d.ring = c->ring.as<uint64_t>();
   d.stages = stages;
   d.cells = cells;
-  PP_TRY(c->ce.ensure(t.ce.size() * 4));
-  PP_TRY(stage_h2d(c, c->ce.p, t.ce.data(), t.ce.size() * 4, st));
-  d.ce = c->ce.as<uint32_t>();
+  if (!c->chains) {
+    PP_TRY(c->ce.ensure(t.ce.size() * 4));
+    PP_TRY(stage_h2d(c, c->ce.p, t.ce.data(), t.ce.size() * 4, st));
+    c->chains = c->ce.as<uint32_t>();
+  }
+  d.ce = c->chains;
   PP_TRY(upload_meta(c, t, cells, st));
   d.meta = c->meta.as<uint32_t>();  // upload_meta may have (re)allocated it
   return upload_spills(c, t, d, slots, st);
@@ -2055,14 +2060,16 @@ pp_ctx* thread_ctx(int& rc) {
 // Upload the tree layout and (already gathered or identity) inputs.
 int upload_tree(pp_ctx* c, const TreeLayout& t, hipStream_t st) {
   const size_t n = (size_t)t.n;
-  const size_t a = (n * 4 + 255) & ~(size_t)255;
+  const size_t a = (n * 4 + 255) & ~(size_t)255, ceb = t.ce.size() * 4;
   std::vector<uint8_t>& h = c->tree_host;
-  h.assign(2 * a, 0);
+  h.assign(2 * a + ceb, 0);
   std::memcpy(h.data(), t.nextpos.data(), n * 4);
   std::memcpy(h.data() + a, t.order.data(), n * 4);
+  if (ceb > 0) std::memcpy(h.data() + 2 * a, t.ce.data(), ceb);
   PP_TRY(c->tree.ensure(h.size()));
   c->nextpos = c->tree.as<int32_t>();
   c->order = (int32_t*)(c->tree.as<uint8_t>() + a);
+  c->chains = ceb > 0 ? (uint32_t*)(c->tree.as<uint8_t>() + 2 * a) : nullptr;
   return stage_h2d(c, c->tree.p, h.data(), h.size(), st);
 }
 
