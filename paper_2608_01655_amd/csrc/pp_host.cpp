@@ -65,6 +65,16 @@ int stall_fail() {
 
 // ------------------------------------------------------------ buffers ---
 
+int env_int(const char* name, int dflt) {
+  const char* v = std::getenv(name);
+  return (v && *v) ? std::atoi(v) : dflt;
+}
+
+// This thread's device allocations since the plan began, and the one to fail
+// (PP_FAIL_ALLOC, a test hook; looked at only where memory is allocated).
+thread_local int g_allocations = 0;
+int fail_allocation() { return env_int("PP_FAIL_ALLOC", 0); }
+
 struct DevBuf {
   void* p = nullptr;
   size_t cap = 0;
@@ -75,9 +85,12 @@ struct DevBuf {
     if (p) (void)hipFree(p);
     p = nullptr;
     cap = 0;
-    if (hipMalloc(&p, bytes) != hipSuccess)
+    if (++g_allocations == fail_allocation() || hipMalloc(&p, bytes) != hipSuccess) {
+      p = nullptr;
+      (void)hipGetLastError();  // the caller may go on with less
       return fail(PP_E_NOMEM, "device allocation of " + std::to_string(bytes) +
                                   " bytes failed");
+    }
     cap = bytes;
     return PP_OK;
   }
@@ -146,7 +159,6 @@ int layout_sweep(TreeLayout& t);
 int layout_sweep_spilled(TreeLayout& t, int32_t pad, int32_t nsteps);
 void layout_levels(TreeLayout& t, const int32_t* parent, const std::vector<int32_t>& posof,
                    const std::vector<int32_t>& head, int32_t k);
-int env_int(const char* name, int dflt);
 
 int layout_sweep_tables(TreeLayout& t);
 
@@ -670,11 +682,6 @@ void make_orders(int32_t m, int32_t n_starts, uint64_t seed,
 
 // ------------------------------------------------------------ context ---
 
-int env_int(const char* name, int dflt) {
-  const char* v = std::getenv(name);
-  return (v && *v) ? std::atoi(v) : dflt;
-}
-
 }  // namespace
 
 struct pp_ctx {
@@ -1150,12 +1157,18 @@ int choose_cells(int32_t total_stage_cells_c1, int dev, int32_t slots_lds) {
   return best ? best : most;
 }
 
+// Device memory a batch's profit rows may take: 8 bytes per chunk and 4 per
+// level-order slot.  PP_ROW_MB: a test hook.
+constexpr int64_t kRowBytes = (int64_t)4 << 30;
+int64_t row_bytes() {
+  const int mb = env_int("PP_ROW_MB", -1);
+  return mb >= 0 ? (int64_t)mb << 20 : kRowBytes;
+}
+
 // Dynamic LDS of a reduced solve's block on this tree, 0 where every update
 // is swept: trees without a level order, or whose tables do not fit.  Forcing
 // the sweep's lane width or its spin limit (test hooks) asks for the sweep
 // itself.
-// device memory a batch's profit rows may take (12 bytes per chunk)
-constexpr int64_t kRowBytes = (int64_t)4 << 30;
 int reduce_lds_for(const TreeLayout& t, int dev) {
   if (std::getenv("PP_DP_CELLS") || std::getenv("PP_SPIN_LIMIT")) return 0;
   if (t.lvtab.empty()) return 0;
@@ -1168,7 +1181,8 @@ int reduce_lds_for(const TreeLayout& t, int dev) {
              : 0;
 }
 
-// The reduced solve's tables and per-slot scratch for `slots` chain slots.
+// The reduced solve's tables, its profit keys for `slots` chain slots (and
+// `rows` more profit rows) and scratch for the chains of one launch.
 int ensure_reduce(pp_ctx* c, const TreeLayout& t, DevState& d, int32_t slots, hipStream_t st,
                   int64_t rows = 0) {
   const size_t n = (size_t)t.n, nlv = t.lvpos.size(), levels = t.lvtab.size() - 1;
@@ -1185,10 +1199,11 @@ int ensure_reduce(pp_ctx* c, const TreeLayout& t, DevState& d, int32_t slots, hi
   PP_TRY(c->key_lv.ensure((slots + rows) * nlv * 4));
   // the padding slots between levels are never written and hold no profit
   PP_HIP(hipMemsetAsync(c->key_lv.p, 0, (slots + rows) * nlv * 4, st));
-  PP_TRY(c->lad_pre.ensure(slots * (size_t)kLadderRungs * (nlv / 16)));
-  PP_TRY(c->lad_bits.ensure(slots * (size_t)kLadderRungs * (nlv / 8)));
-  PP_TRY(c->lad_stat.ensure(slots * (size_t)kLadderRungs * 12));
-  PP_TRY(c->lad_list.ensure(slots * (size_t)kReduceActive * 16));
+  const size_t chains = (size_t)std::min(slots, kMaxChains);
+  PP_TRY(c->lad_pre.ensure(chains * kLadderRungs * (nlv / 16)));
+  PP_TRY(c->lad_bits.ensure(chains * kLadderRungs * (nlv / 8)));
+  PP_TRY(c->lad_stat.ensure(chains * kLadderRungs * 12));
+  PP_TRY(c->lad_list.ensure(chains * kReduceActive * 16));
   const uint8_t* base = c->lvl.as<uint8_t>();
   d.lvslot = (const int32_t*)base;
   d.lvpos = (const uint32_t*)(base + a);
@@ -1203,7 +1218,7 @@ int ensure_reduce(pp_ctx* c, const TreeLayout& t, DevState& d, int32_t slots, hi
   d.lad_pre = c->lad_pre.as<uint32_t>();
   d.lad_bits = c->lad_bits.as<uint32_t>();
   d.lad_price = c->lad_stat.as<double>();
-  d.lad_count = (int32_t*)(c->lad_stat.as<double>() + slots * (size_t)kLadderRungs);
+  d.lad_count = (int32_t*)(c->lad_stat.as<double>() + chains * kLadderRungs);
   d.lad_list = c->lad_list.as<uint32_t>();
   return PP_OK;
 }
@@ -1661,22 +1676,38 @@ int refine_starts(Engine& e, const std::vector<int32_t>& starts, int32_t spare_b
 
 int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
                   const pp_options& o, bool fmax_ok, hipStream_t st, PlanResult& res,
-                  int32_t extra_slots, bool f64, double eps, int attempt);
+                  int32_t extra_slots, bool f64, double eps, int attempt, int without);
+
+// What a plan does without when device memory runs short: the kept profit
+// rows, then the reduced solve.
+enum { kAll = 0, kNoRows = 1, kNoReduce = 2 };
 
 // Algorithm 1 on the context's inputs, run again (identical results: the
-// plan is deterministic) if a DP sweep stalled.
+// plan is deterministic) if a DP sweep stalled, or with less memory if an
+// allocation failed.
 int run_plan(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
              const pp_options& o, bool fmax_ok, hipStream_t st,
              PlanResult& res, int32_t extra_slots = 0, bool f64 = false,
              double eps = 0.0) {
-  for (int attempt = 0;; ++attempt) {
+  int without = kAll;
+  g_allocations = 0;
+  for (int attempt = 0;;) {
     g_stall = false;
     res = PlanResult{};
     const int rc = run_plan_once(c, t, m, cap, o, fmax_ok, st, res, extra_slots, f64, eps,
-                                 attempt);
+                                 attempt, without);
     res.restarts = attempt;
+    if (rc == PP_E_NOMEM && without < kNoReduce && !t.lvtab.empty()) {
+      PP_TRY(poll_stream(st));
+      for (DevBuf* b : {&c->profit, &c->key_lv}) b->release();
+      if (++without == kNoReduce)
+        for (DevBuf* b : {&c->lvl, &c->lad_bits, &c->lad_pre, &c->lad_stat, &c->lad_list})
+          b->release();
+      continue;
+    }
     if (rc == PP_OK || !g_stall || attempt >= kStallRetries) return rc;
     PP_TRY(poll_stream(st));
+    ++attempt;
   }
 }
 
@@ -1696,7 +1727,7 @@ uint32_t spin_limit_for(int attempt) {
 // double, so the comparisons below (orders, best start) hold unchanged.
 int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
                   const pp_options& o, bool fmax_ok, hipStream_t st, PlanResult& res,
-                  int32_t extra_slots, bool f64, double eps, int attempt) {
+                  int32_t extra_slots, bool f64, double eps, int attempt, int without) {
   const int32_t n = t.n;
   const int32_t S = num_starts(m, o.n_starts);
   res.S = S;
@@ -1746,7 +1777,7 @@ int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
   // 8 starts, k = 1,000 and 16,000 for 1, 2 and 4 of 16 workers: 172, 257 and
   // 329 ms with both, 234, 261 and 319 ms swept; 8 workers with 8,000 to
   // 20,000: 114 and 104 ms)
-  int reduce_lds = reduce_lds_for(t, c->device);
+  int reduce_lds = without < kNoReduce ? reduce_lds_for(t, c->device) : 0;
   int32_t reach = 0;
   if (reduce_lds) {
     reach = reduce_reach(n, f64 ? 1 : 0, reduce_lds);
@@ -1797,10 +1828,12 @@ int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
   e.reduce_lds = reduce_lds;
   e.reach = reach;
   res.fmax = (e.fmax || f64) ? 1 : 0;
-  // profit rows of every (start, worker) of a refinement batch, unless they
-  // take more than kRowBytes or nothing is refined
+  // profit rows (and their keys) of every (start, worker) of a refinement
+  // batch, unless they take more than kRowBytes, memory is short or nothing is
+  // refined
   int64_t rows = (int64_t)std::min(S, kMaxChains) * m;
-  if (!e.reduce_lds || (o.flags & PP_F_NO_REFINE) || rows * n * 12 > kRowBytes || slots < 1)
+  if (!e.reduce_lds || (o.flags & PP_F_NO_REFINE) || without >= kNoRows ||
+      rows * (8 * (int64_t)n + 4 * (int64_t)t.lvpos.size()) > row_bytes())
     rows = 0;
   PP_TRY(ensure_slots(c, d, slots, rows));
   d.row0 = rows > 0 ? slots : 0;
@@ -2726,7 +2759,15 @@ static int rooted_dp_impl(int32_t n, const int32_t* parent, const void* profit_v
     int reduce_lds = reduce_lds_for(t, c->device);
     const int32_t reach = reduce_lds ? reduce_reach(n, f64 ? 1 : 0, reduce_lds) : 0;
     if (kp > reach) reduce_lds = 0;
-    if (reduce_lds) PP_TRY(ensure_reduce(c, t, d, 1, st));
+    if (reduce_lds) {
+      const int rrc = ensure_reduce(c, t, d, 1, st);
+      if (rrc == PP_E_NOMEM) {  // swept then
+        reduce_lds = 0;
+        d.key_lv = nullptr;
+      } else if (rrc != PP_OK) {
+        return rrc;
+      }
+    }
     PP_TRY(c->up_lam.ensure((size_t)n * 8));
     PP_HIP(hipMemcpyAsync(c->up_lam.p, profit, (size_t)n * 8, hipMemcpyHostToDevice, st));
     PP_HIP(launch_gather(c->up_lam.as<int64_t>(), d.profit, 1, n,

@@ -242,11 +242,11 @@ struct DevState {
                             // height at which values are clipped
   uint32_t* key_lv;         // [rows][nlv]   upper halves of the profits as
                             //            doubles, rounded up
-  uint32_t* lad_bits;       // [slots][kLadderRungs][nlv / 32] S_t per rung
-  uint32_t* lad_pre;        // [slots][kLadderRungs][nlv / 64] its prefix
-  double* lad_price;        // [slots][kLadderRungs]
-  int32_t* lad_count;       // [slots][kLadderRungs]
-  uint32_t* lad_list;       // [slots][4 kReduceActive] active nodes
+  uint32_t* lad_bits;       // [chains of a launch][kLadderRungs][nlv / 32] S_t per rung
+  uint32_t* lad_pre;        // [chains][kLadderRungs][nlv / 64] its prefix
+  double* lad_price;        // [chains][kLadderRungs]
+  int32_t* lad_count;       // [chains][kLadderRungs]
+  uint32_t* lad_list;       // [chains][4 kReduceActive] active nodes
   const uint32_t* ce;       // [nce][4]   backtrack skip chain of q in its
                             //            32-row window (bit per row), the
                             //            first row of that chain past the

@@ -359,14 +359,14 @@ __global__ void __launch_bounds__(kRThreads) k_ladder(ChainSet set, DevState d, 
     for (int i = leaf0 + tid; i < nlv; i += kRThreads) keep(i, par[i]);
     lds_barrier();
   }
-  uint32_t* out = d.lad_bits + (slot * kLadderRungs + rung) * (int64_t)nlw;
+  uint32_t* out = d.lad_bits + ((int64_t)ci * kLadderRungs + rung) * nlw;
   for (int w = tid; w < nlw; w += kRThreads) out[w] = bits[w];
   uint32_t tot;
   const uint32_t run = block_scan(tid < n64 ? __popcll(bits64[tid]) : 0, red->wsum, &tot);
-  if (tid < n64) d.lad_pre[(slot * kLadderRungs + rung) * (int64_t)n64 + tid] = run;
+  if (tid < n64) d.lad_pre[((int64_t)ci * kLadderRungs + rung) * n64 + tid] = run;
   if (tid == 0) {
-    d.lad_price[slot * kLadderRungs + rung] = t;
-    d.lad_count[slot * kLadderRungs + rung] = (int32_t)tot;
+    d.lad_price[ci * kLadderRungs + rung] = t;
+    d.lad_count[ci * kLadderRungs + rung] = (int32_t)tot;
   }
 }
 
@@ -591,7 +591,7 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
   // the active nodes, leaves first, then the deepest level: position, parent's
   // index | level << 16 (leaves: d.levels), integer profit (an entry is
   // written and read by one thread)
-  uint32_t* apos = d.lad_list + slot * (int64_t)(4 * kReduceActive);
+  uint32_t* apos = d.lad_list + ci * (int64_t)(4 * kReduceActive);
   uint32_t* amd = apos + kReduceActive;
   int64_t* aq = (int64_t*)(amd + kReduceActive);
 
@@ -610,8 +610,8 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
   double* price = red->price;
   int32_t* count = red->count;
   if (tid < rungs) {
-    price[tid] = d.lad_price[slot * kLadderRungs + tid];
-    count[tid] = d.lad_count[slot * kLadderRungs + tid];
+    price[tid] = d.lad_price[ci * kLadderRungs + tid];
+    count[tid] = d.lad_count[ci * kLadderRungs + tid];
   }
   __syncthreads();
   // the highest rung with clearly more than k' nodes, else price 0
@@ -638,7 +638,7 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
       uint64_t* lb = (uint64_t*)(list + kReduceActive);
       uint32_t* lp = (uint32_t*)(lb + n64);
       if (tid < n64) {
-        const int64_t o = (slot * kLadderRungs + j) * (int64_t)n64 + tid;
+        const int64_t o = ((int64_t)ci * kLadderRungs + j) * n64 + tid;
         const uint64_t m = ((const uint64_t*)d.lad_bits)[o];
         int x = A - 1 - (int)d.lad_pre[o];
         lb[tid] = m;

@@ -284,3 +284,62 @@ def test_which_trees_are_reduced(oracle_mod, monkeypatch, tree, n, k, swept):
     got = B.pp_plan(parent, lam, w, f, cap, **kw)
     _same(got, oracle_mod.plan(parent, lam, w, f, cap, **kw))
     assert (got.dp_lane_cells > 0) == swept
+
+
+@pytest.mark.parametrize("seed", range(8))
+def test_plan_without_kept_rows(oracle_mod, monkeypatch, seed):
+    """Refinement whose profits are made anew in every launch, as where the
+    rows would take too much memory."""
+    monkeypatch.setenv("PP_ROW_MB", "0")
+    rng = np.random.default_rng(900 + seed)
+    m, n = int(rng.integers(2, 9)), int(rng.integers(60, 1500))
+    inst = W.random_instance(n, m, rng, kmax=int(rng.choice([10, n // 4 + 1])),
+                             source_dependent=bool(seed % 2),
+                             value_range=int(rng.choice([5, 10 ** 6])))
+    kw = dict(n_starts=int(rng.integers(1, 9)), order_seed=seed)
+    _same(B.pp_plan(inst.parent, inst.demand, inst.recompute_cost, inst.fetch_cost, inst.cap,
+                    **kw),
+          oracle_mod.plan(inst.parent, inst.demand, inst.recompute_cost, inst.fetch_cost,
+                          inst.cap, **kw))
+    lam, w, f = W.real_valued(inst, seed, jitter=0.5)
+    _same(B.pp_plan_f64(inst.parent, lam, w, f, inst.cap, epsilon=0.0, **kw),
+          oracle_mod.plan_f64(inst.parent, lam, w, f, inst.cap, epsilon=0.0, **kw))
+
+
+@pytest.mark.parametrize("real", [False, True])
+def test_plan_short_of_memory(oracle_mod, monkeypatch, real):
+    """Each device allocation of a plan on a fresh context failing once: the
+    plan goes on without kept rows or without the reduced solve, or is refused
+    as out of memory, and the context plans again afterwards."""
+    torch = pytest.importorskip("torch")
+    dev = torch.device("cuda", torch.cuda.current_device())
+    rng = np.random.default_rng(4)
+    inst = W.random_instance(700, 4, rng, kmax=60, source_dependent=True, value_range=1000)
+    kw = dict(n_starts=3, order_seed=1)
+    if real:
+        arrays = W.real_valued(inst, 4, jitter=0.5)
+        ref = oracle_mod.plan_f64(inst.parent, *arrays, inst.cap, epsilon=0.0, **kw)
+        kw["epsilon"] = 0.0
+    else:
+        arrays = (inst.demand, inst.recompute_cost, inst.fetch_cost)
+        ref = oracle_mod.plan(inst.parent, *arrays, inst.cap, **kw)
+    on_dev = [torch.from_numpy(np.ascontiguousarray(x)).to(dev) for x in arrays]
+    refused, planned = [], []
+    for q in range(1, 40):
+        ctx = B.Context(dev.index)
+        plan = ctx.pp_plan_f64_device if real else ctx.pp_plan_device
+        tgt = torch.zeros((4, 700), dtype=torch.uint8, device=dev)
+        monkeypatch.setenv("PP_FAIL_ALLOC", str(q))
+        try:
+            got = plan(inst.parent, *on_dev, inst.cap, tgt, **kw)
+            planned.append(q)
+        except B.PPError as err:
+            assert err.code == B.PP_E_NOMEM, err
+            refused.append(q)
+            monkeypatch.delenv("PP_FAIL_ALLOC")
+            got = plan(inst.parent, *on_dev, inst.cap, tgt, **kw)
+        assert got.objective == ref.objective
+        np.testing.assert_array_equal(tgt.cpu().numpy(), ref.target)
+        ctx.close()
+    # (allocations before the plan itself are refused as they are)
+    assert set(range(2, 15)) <= set(planned), refused
