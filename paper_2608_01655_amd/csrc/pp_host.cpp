@@ -944,11 +944,11 @@ struct Engine {
   // Launches that are swept without trying the reduced solve, and how many
   // the next hold is for.  Where the reduced solve keeps leaving its chains
   // (tied profits, cores too wide), a launch pays it, a read-back and the
-  // sweep: after one launch of which it settles no chain, or kFailsHeld in a
-  // row that are of no use, the next kHoldFirst go straight to the sweep,
-  // twice as many after each further failure, up to kHoldMost.
+  // sweep: after one launch of at least kManyChains of which it settles none,
+  // or kFailsHeld in a row that are of no use, the next kHoldFirst go straight
+  // to the sweep, twice as many after each further failure, up to kHoldMost.
   int fails = 0, hold = 0, hold_next = kHoldFirst;
-  static constexpr int kFailsHeld = 3, kHoldFirst = 8, kHoldMost = 64;
+  static constexpr int kFailsHeld = 3, kHoldFirst = 8, kHoldMost = 64, kManyChains = 4;
   hipStream_t st;
   Timer timer;
 
@@ -1054,7 +1054,8 @@ struct Engine {
                                (stage_blocks(all) + resident - 1) / resident) {
       fails = 0;
       hold_next = kHoldFirst;
-    } else if (++fails >= kFailsHeld || left.count == all.count) {
+    } else if (++fails >= kFailsHeld ||
+               (left.count == all.count && all.count >= kManyChains)) {
       hold = hold_next;
       hold_next = std::min(2 * hold_next, kHoldMost);
       fails = kFailsHeld - 1;
