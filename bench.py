@@ -248,12 +248,34 @@ def plan_timing(B, ctx, inst, lam, w, f, tgt, steps, warmup, plan_flags=0):
 SOLVE_BYTES_PER_N = 14
 
 
-def dp_figures(inst, plans, dt):
+def all_swept(B, ctx, inst, lam, w, f, tgt, p, plan_flags=0):
+    """Whether every solve of plan `p` was a DP sweep: one ran, and a plan
+    with the reduced solve switched off takes the same launches for the same
+    cells."""
+    if p.dp_lane_cells == 0:
+        return False
+    before = os.environ.get("PP_REDUCE_MIN_N")
+    os.environ["PP_REDUCE_MIN_N"] = str(1 << 30)
+    try:
+        q = ctx.pp_plan_device(inst.parent, lam, w, f, inst.cap, tgt,
+                               n_starts=inst.n_starts, max_rounds=inst.max_rounds,
+                               order_seed=inst.order_seed,
+                               flags=B.PP_F_TIME_KERNELS | plan_flags)
+    finally:
+        if before is None:
+            del os.environ["PP_REDUCE_MIN_N"]
+        else:
+            os.environ["PP_REDUCE_MIN_N"] = before
+    return (q.dp_launches, q.dp_cells_executed) == (p.dp_launches, p.dp_cells_executed)
+
+
+def dp_figures(inst, plans, dt, swept):
     """Throughput and roofline figures of a series of plans: plan-level
-    cells per second (Algorithm 1's count and the cells actually swept), the
-    DP sweep's cells per second inside its launches, its fraction of the
-    vector-issue ceiling, of the LDS peak and, under the table model, of
-    HBM."""
+    cells per second (Algorithm 1's count, and that of the updates solved:
+    n * k each, whether a sweep visits them or a reduced solve proves them
+    away), the same per second inside the solve launches and, where every
+    solve is a sweep (`swept`), its fraction of the vector-issue ceiling, of
+    the LDS peak and, under the table model, of HBM."""
     p = plans[-1]
     steps = len(plans)
     exec_cells = sum(q.dp_cells_executed for q in plans)
@@ -261,9 +283,6 @@ def dp_figures(inst, plans, dt):
     launches = sum(q.dp_launches for q in plans)
     kernel_cps = exec_cells / (dp_ms / 1e3) if dp_ms > 0 else 0.0
     c = max(1, p.dp_lane_cells)
-    # every update solved without a sweep: the sweep's instruction, LDS and
-    # table models say nothing about the kernels that ran
-    swept = p.dp_lane_cells > 0
     solved = exec_cells / (inst.n * max(1.0, float(inst.cap.clip(max=inst.n).mean())))
     valu = dp_valu_per_step(c, p.dp_fmax, isinstance(p.objective, float))
     issue_ceiling = VALU_PEAK_TOPS * 1e12 * c / valu  # cells/s
@@ -275,9 +294,9 @@ def dp_figures(inst, plans, dt):
         "plans_per_s": steps / dt,
         "ms_per_plan": dt / steps * 1e3,
         "dp_cells_per_s_algorithm1": p.dp_cells * steps / dt,
-        "dp_cells_per_s_swept": exec_cells / dt,
+        "dp_cells_per_s_solved": exec_cells / dt,
         "dp_cells_per_plan_algorithm1": p.dp_cells,
-        "dp_cells_per_plan_swept": exec_cells // steps,
+        "dp_cells_per_plan_solved": exec_cells // steps,
         "updates_per_plan": p.updates,
         "dp_lane_cells": p.dp_lane_cells,
         "solves_per_plan": solved / steps,
@@ -329,7 +348,8 @@ def configs_leg(B, W, ctx, names, with_oracle):
         t1, _, _ = plan_timing(B, ctx, inst, lam, w, f, tgt, 1, 1)
         steps = int(max(3, min(200, 1.0 / max(t1, 1e-4))))
         dt, step_ms, plans = plan_timing(B, ctx, inst, lam, w, f, tgt, steps, 0)
-        fig = dp_figures(inst, plans, dt)
+        swept = all_swept(B, ctx, inst, lam, w, f, tgt, plans[-1])
+        fig = dp_figures(inst, plans, dt, swept)
         fig["steps"] = steps
         fig["ms_per_plan_median"] = step_ms[len(step_ms) // 2]
         fig["ms_per_plan_min"] = step_ms[0]
@@ -621,7 +641,8 @@ def main():
     objectives = {q.objective for q in plans}
     gold = golden_plan(inst.name)
     gold_ok = (objectives == {gold["objective"]}) if gold else None
-    fig = dp_figures(inst, plans, dt)
+    swept = all_swept(B, ctx, inst, lam, w, f, tgt, p, plan_flags)
+    fig = dp_figures(inst, plans, dt, swept)
     exec_cells = sum(q.dp_cells_executed for q in plans)
     dp_ms = sum(q.dp_kernel_ms for q in plans)
     launches = sum(q.dp_launches for q in plans)
@@ -634,7 +655,7 @@ def main():
     achieved = cells_per_launch * valu / c / avg_launch_s / 1e12
     traffic = measured_traffic(inst.name)
     real = "true" if isinstance(p.objective, float) else "false"
-    if p.dp_lane_cells > 0:
+    if swept:
         roofline = {
             "bound": "alu",
             "kernel": f"k_dp<{c}, {'true' if p.dp_fmax else 'false'}, false> "
@@ -676,7 +697,8 @@ def main():
         # its phases; against HBM, the bytes its solves cannot do without
         roofline = {
             "bound": "hbm",
-            "kernel": f"k_ladder<{real}> + k_reduce<{real}> (reduced exact tree solve)",
+            "kernel": f"k_ladder<{real}> + k_reduce<{real}> (reduced exact tree solve)"
+                      + (", k_dp where it leaves a chain" if p.dp_lane_cells else ""),
             "achieved": fig["solve_hbm_gbs"],
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
@@ -695,12 +717,13 @@ def main():
         "unit": "plans/s",
         # Algorithm 1's cells (every update n * min(k_h, n)) per second
         "dp_cells_per_s": fig["dp_cells_per_s_algorithm1"],
-        # cells the sweeps processed (updates of workers whose inputs did not
-        # change need no sweep; discarded speculative updates add theirs)
-        "dp_cells_executed_per_s": fig["dp_cells_per_s_swept"],
+        # n * k of the updates solved, by a reduced solve or a sweep (updates of
+        # workers whose inputs did not change need none; discarded
+        # speculative updates add theirs)
+        "dp_cells_executed_per_s": fig["dp_cells_per_s_solved"],
         "dp_cells_per_s_frac_issue_roofline": fig["plan_issue_frac"],
-        "dp_cells_per_s_frac_hbm_table_model": fig["dp_cells_per_s_swept"]
-        * TABLE_BYTES_PER_CELL / (HBM_PEAK_GBS * 1e9) if p.dp_lane_cells > 0 else None,
+        "dp_cells_per_s_frac_hbm_table_model": fig["dp_cells_per_s_solved"]
+        * TABLE_BYTES_PER_CELL / (HBM_PEAK_GBS * 1e9) if swept else None,
         "plans_per_s_frac_hbm_table_model": fig["plan_table_model_hbm_frac"],
         "n_gpus": 1,
         "steps": args.steps,

@@ -937,6 +937,7 @@ struct Engine {
   int attempt = 0;
   int32_t slots_lds = 0;
   int resident = 0;   // DP blocks resident at once (0: no sweep set up)
+  bool swept = false; // a sweep ran
   uint32_t spin_limit;
   int fmax = 0;  // every DP value < 2^62: max via v_max_f64
   int reduce_lds = 0;  // LDS of a reduced solve's block, 0: sweep every update
@@ -976,6 +977,7 @@ struct Engine {
   // launches whose stages all fit on the device at once.
   int dp(const ChainSet& in, int store_bits) {
     PP_TRY(set_up_sweep());
+    swept = swept || in.count > 0;
     if (!d.meta || !d.profit || !d.bits || !d.ring || !d.cs)
       return fail(PP_E_DEVICE, "internal: DP sweep buffers are not set");
     const int cellsw = 64 * d.cells;
@@ -1953,7 +1955,6 @@ int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
       res.skipped_cells += fin[s - lo].skipped_cells;
     }
   }
-  res.lane_cells = d.cells;
   res.best = 0;
   if (f64) {
     // real-valued costs: starts compare exact objective values
@@ -1977,6 +1978,7 @@ int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
     res.cells += cells_pass * (1 + res.sweeps[s]);
   }
   if (sg_asked) PP_TRY(run_safeguards(e, m, kp, slot_b, cells_pass, st, res));
+  res.lane_cells = e.swept ? d.cells : 0;
   if (e.timer.on) {
     float tot = 0.f;
     for (auto& mk : e.timer.marks) {

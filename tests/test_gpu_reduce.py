@@ -343,3 +343,19 @@ def test_plan_short_of_memory(oracle_mod, monkeypatch, real):
         ctx.close()
     # (allocations before the plan itself are refused as they are)
     assert set(range(2, 15)) <= set(planned), refused
+
+
+@pytest.mark.parametrize("depth", [40, 120])
+def test_lane_cells_only_where_a_sweep_ran(depth):
+    """The statistic says whether a sweep ran, also on trees whose sweep
+    tables are laid out beforehand (deeper than 64)."""
+    rng = np.random.default_rng(depth)
+    n = 6_000
+    parent = np.array([v - 1 if v % depth else -1 for v in range(n)], np.int32)
+    lam = rng.integers(1, 10 ** 6, size=(2, n))
+    w = rng.integers(1, 10 ** 6, size=(2, n))
+    f = rng.integers(0, 10 ** 6, size=(2, 2, n))
+    got = B.pp_plan(parent, lam, w, f, np.full(2, 400, np.int32), n_starts=1)
+    assert got.dp_lane_cells == 0
+    none = B.pp_plan(parent, lam, w, f, np.zeros(2, np.int32), n_starts=1)
+    assert none.dp_lane_cells == 0 and none.objective == 0
