@@ -1171,10 +1171,12 @@ int64_t row_bytes() {
 // Dynamic LDS of a reduced solve's block on this tree, 0 where every update
 // is swept: trees without a level order, or whose tables do not fit.  Forcing
 // the sweep's lane width or its spin limit (test hooks) asks for the sweep
-// itself.
+// itself, unless the reduced solve is forced too (PP_REDUCE_MIN_N).
 int reduce_lds_for(const TreeLayout& t, int dev) {
-  if (std::getenv("PP_DP_CELLS") || std::getenv("PP_SPIN_LIMIT")) return 0;
   if (t.lvtab.empty()) return 0;
+  if ((std::getenv("PP_DP_CELLS") || std::getenv("PP_SPIN_LIMIT")) &&
+      !std::getenv("PP_REDUCE_MIN_N"))
+    return 0;
   int lds = 0;
   if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
     return 0;

@@ -359,3 +359,76 @@ def test_lane_cells_only_where_a_sweep_ran(depth):
     assert got.dp_lane_cells == 0
     none = B.pp_plan(parent, lam, w, f, np.zeros(2, np.int32), n_starts=1)
     assert none.dp_lane_cells == 0 and none.objective == 0
+
+
+@pytest.mark.parametrize("hook", ["spin", "cells1", "cells2", "cells4"])
+def test_sweeps_after_the_reduced_solve(oracle_mod, monkeypatch, hook):
+    """Sweeps of left chains, at every lane width, and with a wait that gives
+    up at once (the plan runs again): in the standalone and greedy solves and
+    in refinement, next to solved chains, for one plan and one tree solve."""
+    if hook == "spin":
+        monkeypatch.setenv("PP_SPIN_LIMIT", "1")
+    else:
+        monkeypatch.setenv("PP_DP_CELLS", hook[-1])
+    rng = np.random.default_rng(77)
+    half, n, m = 900, 2000, 4
+    parent = np.concatenate([_gw(half, rng), np.full(n - half, -1, np.int32)])
+    lam = rng.integers(1, 50, size=(m, n))
+    w = rng.integers(1, 50, size=(m, n))
+    f = rng.integers(0, 40, size=(m, m, n))
+    lam[:, half:] = 40
+    w[:, half:] = 30
+    f[:, :, half:] = 7
+    cap = np.array([30, 700, 300, 90], np.int32)
+    kw = dict(n_starts=5, order_seed=3)
+    got = B.pp_plan(parent, lam, w, f, cap, **kw)
+    _same(got, oracle_mod.plan(parent, lam, w, f, cap, **kw))
+    assert got.dp_lane_cells == (1 if hook == "spin" else int(hook[-1]))
+    assert (got.dp_restarts > 0) == (hook == "spin")
+    x = (lam * 1.0, w / 8.0, f / 8.0, cap)
+    _same(B.pp_plan_f64(parent, *x, epsilon=0.0, **kw),
+          oracle_mod.plan_f64(parent, *x, epsilon=0.0, **kw))
+    profit = np.full(n, 5, np.int64)
+    sel, val = B.pp_rooted_dp(parent, profit, 700)
+    osel, oval = oracle_mod.rooted_dp(parent, profit, 700)
+    assert val == oval
+    np.testing.assert_array_equal(sel, osel)
+
+
+def test_typical_plans_need_no_sweep(oracle_mod):
+    """The reduced solve settles every update of ordinary plans by itself:
+    greedy, refinement with acceptance, and rejection by its upper bound."""
+    for seed, (tree, n, m, k) in enumerate([("gw", 3000, 4, 256), ("gw", 6000, 3, 500),
+                                            ("forest", 4000, 5, 300)]):
+        rng = np.random.default_rng(seed)
+        parent = _gw(n, rng) if tree == "gw" else W.random_forest(n, rng)
+        parent = W._relabel_preorder(parent.tolist())[0]
+        lam = W.zipf_leaf_demand(parent, m, 1.0, 2000 * n, rng)
+        w = W.depth_linear_recompute(W._depths(parent), W.H10_CYCLE[np.arange(m) % 3])
+        f = W.pairwise_fetch(m, n, 1.0, 25.0, rng)
+        cap = np.full(m, k, np.int32)
+        kw = dict(n_starts=4, order_seed=seed)
+        got = B.pp_plan(parent, lam, w, f, cap, **kw)
+        _same(got, oracle_mod.plan(parent, lam, w, f, cap, **kw))
+        assert got.dp_lane_cells == 0, (tree, n)
+        assert sum(got.start_accepts) > 0
+        jit = rng.uniform(0.75, 1.25, size=lam.shape)
+        x = (lam * jit, w / 1000.0 * jit, f / 1000.0 * jit[None], cap)
+        gf = B.pp_plan_f64(parent, *x, epsilon=0.0, **kw)
+        _same(gf, oracle_mod.plan_f64(parent, *x, epsilon=0.0, **kw))
+        assert gf.dp_lane_cells == 0, (tree, n, "f64")
+
+
+@pytest.mark.parametrize("name", ["tree2k", "rag10k", "tree50k", "chat50k"])
+def test_large_workloads_swept(monkeypatch, name):
+    """The full sweep on the large workloads, whose updates the reduced solve
+    settles by default: the same plan."""
+    inst = W.make_workload(name)
+    args = (inst.parent, inst.demand, inst.recompute_cost, inst.fetch_cost, inst.cap)
+    kw = dict(n_starts=inst.n_starts, max_rounds=inst.max_rounds, order_seed=inst.order_seed)
+    monkeypatch.delenv("PP_REDUCE_MIN_N")
+    reduced = B.pp_plan(*args, **kw)
+    monkeypatch.setenv("PP_REDUCE_MIN_N", str(1 << 30))
+    swept = B.pp_plan(*args, **kw)
+    assert swept.dp_lane_cells > 0
+    _same(reduced, swept)
