@@ -100,8 +100,14 @@ struct Red {  // block-wide scratch words in LDS
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // Barrier where only LDS is exchanged: global loads stay in flight across it.
+// The fence waits for accesses that the compiler knows to be LDS (ds_*).  A
+// pointer into LDS that has been through an integer is a generic one, its
+// accesses are flat_* and the fence alone lets them pass the barrier; so LDS
+// is addressed by offsets from its base, and the wait (lgkmcnt(0), vmcnt as
+// it is) is also stated.
 __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_waitcnt(0xC07F);
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
@@ -597,8 +603,9 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
 
   Red* red = (Red*)lds;
   uint32_t* sel = (uint32_t*)((char*)lds + kReduceRedBytes);  // selection, n bits
-  int64_t* W = (int64_t*)(((size_t)(sel + nw) + 15) & ~(size_t)15);
-  const int wbytes = lds_bytes - (int)((char*)W - (char*)lds);
+  const int woff = (kReduceRedBytes + 4 * nw + 15) & ~15;
+  int64_t* W = (int64_t*)((char*)lds + woff);
+  const int wbytes = lds_bytes - woff;
   const int acap = min(kReduceActive, wbytes / 8 - 4);
 
   if (tid == 0) {  // undecided, until solved here or swept
