@@ -799,7 +799,8 @@ int stage_h2d(pp_ctx* c, void* dst, const void* src, size_t bytes, hipStream_t s
   return PP_OK;
 }
 
-// Waits for `st` by polling (every wait of the library): the host decides
+// Waits for `st` by polling (every wait of the library but the allocation-free
+// objective's): the host decides
 // the next launches from what it reads back (after each refinement launch,
 // the chain states), so the wake-up delay of a blocking wait would leave
 // the device idle, and for small trees it is a large part of a call.
@@ -1768,8 +1769,11 @@ int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
   // the launch's stage blocks -- small capacities, whose launches take the
   // same time with more chains
   // (reduced solves have no stages: kSpecChains updates.  8, 16, 24 and 32
-  // took 18.1, 17.0, 20.5 and 20.6 ms at n = 50,000 and 4.1, 3.8, 3.7 and
-  // 3.7 ms at n = 10,000: past 16 the ladder has half the rungs)
+  // took 18.0, 16.4, 16.6 and 16.5 ms at n = 50,000, m = 16, k = 4,096, 14.1,
+  // 12.4, 12.9 and 13.1 at k = 128 real-valued, 3.95, 3.60, 3.63 and 3.67 at
+  // n = 10,000, m = 8: past 16 the ladder has half the rungs.  Where the starts
+  // alone are more than 16 the ladder is short anyway and more would do: 54.3,
+  // 53.5, 53.1 and 52.5 ms with 32 starts, 2.30, 2.30, 2.18 and 2.23 with 24)
   const int32_t wide_stages = std::max(1, (kmax + 63) / 64);
   auto spec_of = [&](int32_t dflt) {  // updates per refinement launch
     return env_int("PP_NO_SPEC", 0)

@@ -2,10 +2,11 @@
 //
 // One worker update (Algorithm 1, PrefixPlace procedure) is a few launches
 // over every active chain (a chain is one start's current update, or one
-// standalone solve).  Trees of 1,024 nodes and more are solved by the reduced
-// solve of pp_reduce.hip, and k_dp and k_backtrack run for the chains that it
-// leaves; refinement keeps profits between updates (k_rows, k_commit) and runs
-// k_gains for greedy positions only:
+// standalone solve).  Larger trees are solved by the reduced solve of
+// pp_reduce.hip (reduce_pays in pp_host.cpp), and k_dp and k_backtrack run for
+// the others and for the chains that it leaves; with it refinement keeps
+// profits between updates (k_rows, k_commit) and runs k_gains for greedy
+// positions only:
 //   k_gains      exact marginals p_h(b) (Eq. 7, Proposition 1) from the
 //                top-2 holder state, plus the incumbent's value for the
 //                strict-improvement test (Sec. IV-C)

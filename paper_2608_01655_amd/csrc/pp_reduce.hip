@@ -44,8 +44,11 @@
 // Both kernels read the tree in level order (DevState::lvpos): internal
 // nodes level by level from the roots, then every leaf.  Child sums live in
 // LDS; leaves add theirs in one pass, internal nodes level by level with one
-// barrier each.  What bounds them is instruction issue and, for code that
-// runs once per launch, instruction fetch, so loops are kept rolled.
+// barrier each.  Counters at n = 50,000, m = 16, k = 4,096 (shares of the
+// waves' time, four waves a SIMD): k_ladder waits 70% (loads, LDS atomics,
+// barriers) and issues 21%, so a SIMD issues most of the time and its vector
+// unit is in use 40%; k_reduce waits 70% and issues 16%, vector 26%.  Loops
+// that run once per launch are kept rolled (an unrolled ladder was slower).
 
 #include <algorithm>
 
@@ -69,7 +72,11 @@ constexpr int kMaxSearch = 40;  // evaluations of one price search
 constexpr uint32_t kNone = 0xFFFFu;
 constexpr int kChunks = kReduceActive / kRThreads;
 
-// The active nodes a solve of k' chunks asks for above price 0.
+// The active nodes a solve of k' chunks asks for above price 0.  Too few and
+// the rung's price lies so near the final one that the gap passes it and the
+// solve starts again lower; too many and every pass is longer.  Plans with
+// k'/64 + 40, k'/16 + 160, k'/8 + 160: n = 50,000, k = 4,096 16.2, 16.4, 16.6 ms;
+// k = 128 real-valued 13.4, 12.4, 12.3; conversations, 32 starts 64.0, 53.3, 54.2.
 __host__ __device__ constexpr int64_t nodes_needed(int64_t kp) { return kp + kp / 16 + 160; }
 
 // Bins of the entry widths: exact below 4, then four per factor of two.
@@ -168,11 +175,13 @@ __device__ __forceinline__ int rung_rank16(int rung, int rungs) {
 // S_t: values are clipped at a height that leaves every ancestor positive
 // (the clip exceeds one price per level).  Integer sums: the same bits
 // whatever the order of the atomics.
-// Bound by instruction issue of one block's passes over all nodes (histogram,
-// up, down) and the barriers between levels: 48 us at n = 50,000, m = 16, 17 us
-// at n = 10,000, 79 us on deep conversation trees of 50,000 (7 rungs, 32
-// chains); blocks of different rungs run side by side, so more rungs cost
-// nothing until chains x rungs pass the 256 compute units.
+// Bound by one block's passes over all nodes (histogram, up, down), in about
+// equal parts issue and waits, and the barriers between levels: 48 us at
+// n = 50,000, m = 16, 17 us at n = 10,000, 79 us on deep conversation trees of
+// 50,000 (7 rungs, 32 chains).  The leaf passes take one value at a time: the
+// ballots in them keep the compiler from unrolling.  Blocks of different rungs
+// run side by side, so more rungs cost nothing until chains x rungs pass the
+// 256 compute units.
 // With `prep` set, one more block per chain sums the incumbent's value
 // sum over T_h of p_h of a refinement update (what k_gains leaves in inc;
 // real-valued costs: also the scale wsum, from the start's gwo).
@@ -247,7 +256,9 @@ __global__ void __launch_bounds__(kRThreads) k_ladder(ChainSet set, DevState d, 
     __syncthreads();
   }
   // Ranks of many hundreds are estimated from every fourth profit: the rungs
-  // need not be exact.
+  // need not be exact (all profits: 17.15 against 16.4 ms a plan at n =
+  // 50,000, m = 16, k = 4,096, 55.3 against 53.3 on conversations with 32
+  // starts; below k' = 1,024 a sample would move the small ranks).
   const int every = kp >= 1024 ? 4 : 1;
 #pragma unroll 8
   for (int i = tid * every + (tid & (every - 1)); i < nlv; i += kRThreads * every) {
@@ -302,7 +313,6 @@ __global__ void __launch_bounds__(kRThreads) k_ladder(ChainSet set, DevState d, 
     if (lane == 0) bits64[i >> 6] = m;
   };
   // up: the leaves at once, then the levels from the deepest
-#pragma unroll 8
   for (int i = leaf0 + tid; i < nlv; i += kRThreads) {
     const int v = up(key[i]);
     const uint32_t pr = par[i];
@@ -361,7 +371,6 @@ __global__ void __launch_bounds__(kRThreads) k_ladder(ChainSet set, DevState d, 
       }
     }
     lds_barrier();
-#pragma unroll 8
     for (int i = leaf0 + tid; i < nlv; i += kRThreads) keep(i, par[i]);
     lds_barrier();
   }
@@ -445,7 +454,6 @@ __device__ void core_dp(int rows, int core, const int64_t* rp, const uint32_t* r
       if (F64 && ((plain >> l) & 1u)) {
         const uint64_t rest = ~(plain >> l);
         const int end = l + (rest ? __builtin_ctzll(rest) : 64);
-#pragma unroll 4
         for (; l < end; ++l) {
           const double p = as_d(lane_of(q, l));
 #pragma unroll
@@ -569,10 +577,12 @@ __device__ void finish_update(ChainState* st, const DevState& d, int h, int kp, 
 }
 
 // One block per chain: list, price search, entry widths, core, DP and walk.
-// Bound by the chain of these phases, each 10 to 20 us of one block's issue and
-// latency, with 8 to 32 of 256 compute units in use: 87 us a launch at
-// n = 50,000, k = 4,096 (the sweep and walk it replaces: 2,160 + 320 us), 56 us
-// at n = 10,000, k = 1,024 (430 us), 111 us real-valued at k = 128 (1,890 us).
+// Bound by the chain of these phases, each 10 to 20 us of one block's waits
+// (barriers, LDS, the one wave of the core DP), with 8 to 32 of 256 compute
+// units in use; 8 (real-valued) to 28 vector registers spill (36 to 116 bytes
+// of scratch a lane at 16 waves a block).  78 us a launch at
+// n = 50,000, k = 4,096 (the sweep and walk it replaces: 2,160 + 320 us), 51 us
+// at n = 10,000, k = 1,024 (430 us), 83 us real-valued at k = 128 (1,890 us).
 template <bool F64>
 __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, int mode,
                                                       int lds_bytes, int rungs) {
@@ -690,7 +700,7 @@ __global__ void __launch_bounds__(kRThreads) k_reduce(ChainSet set, DevState d, 
     };
     // a price in these units, rounded up
     auto price_q = [&](double v) -> int64_t {
-      return (int64_t)min(ceil(ldexp(v, scale)), 0x1p48);
+      return (int64_t)fmin(ceil(ldexp(v, scale)), 0x1p48);
     };
     const int64_t tq = price_q(t);
     if (F64 || shift > 0)
