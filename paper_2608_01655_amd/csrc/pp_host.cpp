@@ -267,12 +267,14 @@ int layout_sweep_tables(TreeLayout& t) {
 // cores are wide or fail: k = 20 of 2,048 and 28 of 2,896 at depth 10: 3.21
 // and 2.68 against 1.75 and 1.78 ms, k = 17 of 5,792 2.90 against 3.59; k = 24
 // of 8,192 at depth 32 5.57 against 4.76 ms, k = 60 of 20,000 2.99 against
-// 11.6.  One solve on host arrays crosses at the same sizes.
+// 11.6.  Many chunks are several stages of the sweep: k = 168 of 1,351 at
+// depth 5 (2 workers and starts, real-valued) 1.00 against 1.12 ms.  One solve on
+// host arrays crosses at the same sizes.
 // PP_REDUCE_MIN_N (a test hook) asks for it from that many nodes on.
 bool reduce_pays(int32_t n, int32_t depth, int32_t k) {
   const int forced = env_int("PP_REDUCE_MIN_N", -1);
   if (forced >= 0) return n >= forced;
-  const int64_t line = 1500 + 2 * (int64_t)depth * depth;
+  const int64_t line = (k >= 128 ? 1250 : 1500) + 2 * (int64_t)depth * depth;
   return n >= (k >= 30 + 3 * depth / 4 ? line : 3 * line);
 }
 
@@ -284,7 +286,7 @@ bool reduce_pays(int32_t n, int32_t depth, int32_t k) {
 void layout_levels(TreeLayout& t, const int32_t* parent, const std::vector<int32_t>& posof,
                    const std::vector<int32_t>& head, int32_t k) {
   const int32_t n = t.n;
-  if (n > kLadderSlots || !reduce_pays(n, 0, INT32_MAX)) return;
+  if (n > kLadderSlots || !reduce_pays(n, 0, k)) return;
   std::vector<uint8_t> depth(n);
   int32_t maxd = 0;
   int64_t maxdeg = 0;
@@ -1914,12 +1916,13 @@ int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
     std::vector<int32_t> active;
     for (int32_t s = lo; s < hi; ++s) active.push_back(s);
     {
-      const std::vector<int32_t> z(active.size(), 0);
-      PP_HIP(launch_init_slots(chain_set(active, z, z, 0, z.size()), d, 1, st));
-      // spare slots hold no placement
-      if (slots > spare_base)
-        PP_HIP(hipMemsetAsync(d.cs + spare_base, 0, sizeof(ChainState) * (slots - spare_base),
-                              st));
+      // spare slots hold no placement: only their states are cleared
+      std::vector<int32_t> sl(active);
+      for (int32_t q = spare_base; q < slots; ++q) sl.push_back(q);
+      const std::vector<int32_t> z(sl.size(), 0);
+      for (size_t a = 0; a < sl.size(); a += kMaxChains)
+        PP_HIP(launch_init_slots(chain_set(sl, z, z, a, std::min(sl.size(), a + kMaxChains)), d, 1,
+                                 st, spare_base));
     }
     auto position_set = [&](const std::vector<int32_t>& act, int32_t a) {
       std::vector<int32_t> sl, wk, kk;

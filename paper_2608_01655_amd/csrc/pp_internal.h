@@ -373,8 +373,10 @@ int32_t gexact_blocks(int32_t n, int32_t m);
 // any other mode: G of each slot's own placement (gx[slot][0], cs.obj).
 hipError_t launch_gexact(const ChainSet& set, const DevState& d, int mode,
                          hipStream_t st);
+// bare_from: slots from here on hold no placement, only their states (and
+// exact sums) are cleared
 hipError_t launch_init_slots(const ChainSet& set, const DevState& d,
-                             int clear_tgt, hipStream_t st);
+                             int clear_tgt, hipStream_t st, int bare_from = INT32_MAX);
 hipError_t launch_holder_build(const ChainSet& set, const DevState& d,
                                hipStream_t st);
 // may_skip: refinement updates, which resolve a clean worker's update

@@ -305,10 +305,10 @@ __global__ void k_validate_f64(const double* __restrict__ lam,
   if (threadIdx.x == 0) flags[blockIdx.x] = any ? 1 : 0;
 }
 
-__global__ void k_init_slots(ChainSet set, DevState d, int clear_tgt) {
+__global__ void k_init_slots(ChainSet set, DevState d, int clear_tgt, int bare_from) {
   const int ci = blockIdx.y;
   const int64_t s = set.slot[ci];
-  const int64_t mn = (int64_t)d.m * d.n;
+  const int64_t mn = s < bare_from ? (int64_t)d.m * d.n : 0;
   for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < mn;
        x += (int64_t)gridDim.x * blockDim.x) {
     if (clear_tgt) d.tgt[s * mn + x] = 0;
@@ -2229,12 +2229,12 @@ hipError_t launch_validate_f64(const double* lam, const double* w,
 }
 
 hipError_t launch_init_slots(const ChainSet& set, const DevState& d,
-                             int clear_tgt, hipStream_t st) {
+                             int clear_tgt, hipStream_t st, int bare_from) {
   int64_t mn = (int64_t)d.m * d.n;
   int64_t b = (mn + 255) / 256;
   if (b > 2048) b = 2048;
   hipLaunchKernelGGL(k_init_slots, dim3((unsigned)b, set.count), dim3(256), 0,
-                     st, set, d, clear_tgt);
+                     st, set, d, clear_tgt, bare_from);
   return hipGetLastError();
 }
 

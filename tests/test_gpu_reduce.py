@@ -264,7 +264,8 @@ def test_refinement_of_left_updates(oracle_mod, monkeypatch, blocks):
     ("gw", 20_000, 200, False),
     ("chat", 5_000, 400, True),    # deep for its size
     ("chat", 20_000, 1_500, False),
-    ("forest", 1_499, 300, True)])
+    ("forest", 1_499, 60, True),
+    ("rag", 1_351, 168, False)])    # several stages of the sweep
 def test_which_trees_are_reduced(oracle_mod, monkeypatch, tree, n, k, swept):
     """The choice by nodes, depth and capacity, on both sides of its lines."""
     monkeypatch.delenv("PP_REDUCE_MIN_N")
@@ -273,6 +274,8 @@ def test_which_trees_are_reduced(oracle_mod, monkeypatch, tree, n, k, swept):
         parent = _gw(n, rng)
     elif tree == "chat":
         parent = W._relabel_preorder(W.chain_tree(n, (7 * n) // 10, 2.2, 16, 64, rng))[0]
+    elif tree == "rag":
+        parent = W._relabel_preorder(W.rag_tree(n, 40, rng))[0]
     else:
         parent = W.random_forest(n, rng)
     m = 2
