@@ -260,8 +260,10 @@ int layout_sweep_tables(TreeLayout& t) {
 //   depth 10   1.70 / 1.36 / 1.71 against 1.20 / 1.28 / 2.14 ms
 //   depth 32   n = 2,048 / 2,896 / 4,096: 3.93 / 2.35 / 2.85 against
 //              1.84 / 2.53 / 3.97 ms
-//   depth 60   n = 5,792 / 8,192 / 11,585: 5.28 / 8.33 / 5.50 against
-//              5.03 / 7.03 / 9.26 ms
+//   depth 60   swept over reduced, n = 3,600 / 4,600 / 5,600 / 6,600 / 7,600 /
+//              8,600 / 9,600, geometric means of 4 trees, 4 capacities and both
+//              value types: 0.77 / 0.94 / 1.01 / 1.13 / 1.22 / 1.20 / 1.35 (one
+//              case 0.5 to 2.4: whether some core fails)
 //   depth 90   n = 8,192 / 23,170: 7.63 / 8.00 against 6.70 / 17.9 ms
 // A few chunks per worker leave a gap that is a large part of a price, so
 // cores are wide or fail: k = 20 of 2,048 and 28 of 2,896 at depth 10: 3.21
@@ -274,8 +276,8 @@ int layout_sweep_tables(TreeLayout& t) {
 bool reduce_pays(int32_t n, int32_t depth, int32_t k) {
   const int forced = env_int("PP_REDUCE_MIN_N", -1);
   if (forced >= 0) return n >= forced;
-  const int64_t line = (k >= 128 ? 1250 : 1500) + 2 * (int64_t)depth * depth;
-  return n >= (k >= 30 + 3 * depth / 4 ? line : 3 * line);
+  const int64_t line = (k >= 96 ? 1250 : 1500) + 5 * (int64_t)depth * depth / 4;
+  return n >= (k >= 30 + depth / 3 ? line : 3 * line);
 }
 
 // Level order for the reduced solve, left empty where the sweep is faster
