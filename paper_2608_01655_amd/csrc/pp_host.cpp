@@ -1376,14 +1376,13 @@ int run_safeguards(Engine& e, int32_t m, const std::vector<int32_t>& kp,
 // the next launch.  A start whose sweep has accepted an update goes on into
 // its next sweep the same way once the rest of the sweep is in the launch.
 // Results are those of the sequential sweeps.
-// A launch goes through the reduced solve with up to `reduce_budget` updates,
-// or is swept with up to `sweep_budget` and, beyond the starts' own updates,
-// at most `spec_blocks` stage blocks (all of them resident).  Of the updates
-// that the reduced solve leaves, only those that can still count are swept:
-// none after an accepted one of its start, and speculative ones only within
-// the stage blocks; a start's results end before the first that is left.
+// A launch goes through the reduced solve, or is swept with, beyond the starts'
+// own updates, at most `spec_blocks` stage blocks (all of them resident).  Of
+// the updates that the reduced solve leaves, only those that can still count
+// are swept: none after an accepted one of its start, and speculative ones only
+// within the stage blocks; a start's results end before the first that is left.
 int refine_starts(Engine& e, const std::vector<int32_t>& starts, int32_t spare_base,
-                  int32_t reduce_budget, int32_t sweep_budget, int32_t spec_blocks, int32_t m,
+                  int32_t budget, int32_t spec_blocks, int32_t m,
                   const std::vector<int32_t>& kp, int32_t max_rounds, PlanResult& res) {
   DevState& d = e.d;
   const int32_t A = (int32_t)starts.size();
@@ -1474,7 +1473,6 @@ int refine_starts(Engine& e, const std::vector<int32_t>& starts, int32_t spare_b
     // each; budget - 1 spare slots exist) and, beyond the starts' own
     // updates, at most `block_budget` DP stage blocks in the launch
     const bool reducing = e.reducing();
-    const int32_t budget = reducing ? reduce_budget : sweep_budget;
     int32_t block_budget = std::min(spec_blocks, e.resident);
     auto stages_of = [&](int32_t h) {
       const int32_t cellsw = 64 * std::max(d.cells, 1);
@@ -1797,10 +1795,10 @@ int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
     const auto far = std::count_if(kp.begin(), kp.end(), [&](int32_t k) { return k > reach; });
     if (8 * far > m) reduce_lds = 0;
   }
-  const int32_t sweep_budget =
-      spec_of(2 * kSpecChains * wide_stages <= spec_blocks ? 2 * kSpecChains : kSpecChains);
-  const int32_t reduce_budget = reduce_lds ? spec_of(kSpecChains) : 1;
-  const int32_t spec_chains = std::max(sweep_budget, reduce_budget);
+  // (the swept launches of a plan that tries the reduced solve keep to its
+  // number: 16 more spare slots would make a new context's first plan 5% longer)
+  const int32_t spec_chains = spec_of(
+      !reduce_lds && 2 * kSpecChains * wide_stages <= spec_blocks ? 2 * kSpecChains : kSpecChains);
   const int32_t spare_base = slot_b + (sg_asked ? 4 : 0) + extra_slots;
   const int32_t slots = spare_base + (spec_chains > 1 ? spec_chains - 1 : 0);
   res.extra_slot = extra_slots > 0 ? slot_b + (sg_asked ? 4 : 0) : -1;
@@ -1945,8 +1943,8 @@ int run_plan_once(pp_ctx* c, TreeLayout& t, int32_t m, const int32_t* cap,
     for (int32_t a = 1; a < m; ++a)
       PP_TRY(e.update(position_set(active, a), kModeGreedy));
     if (!(o.flags & PP_F_NO_REFINE))
-      PP_TRY(refine_starts(e, active, spare_base, reduce_budget, sweep_budget, spec_blocks, m, kp,
-                           o.max_rounds, res));
+      PP_TRY(refine_starts(e, active, spare_base, spec_chains, spec_blocks, m, kp, o.max_rounds,
+                           res));
     std::vector<int32_t> sl, wk, kk;
     for (int32_t s = lo; s < hi; ++s) {
       sl.push_back(s);
